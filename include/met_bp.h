@@ -265,7 +265,13 @@ int met_decode_workspace_bytes(const met_code *c, int32_t B, uint32_t flags, int
  *   workspace: dev, 256-byte aligned, at least met_decode_workspace_bytes();
  *              its contents need not be initialised
  * The first call on a device uploads the adjacency (allocates); later calls
- * allocate nothing.  Errors: MET_EINVAL, MET_EHIP. */
+ * allocate nothing.
+ * Small decodes run as one launch in which the workgroups of each accelerator
+ * die (XCD) decode small groups of frames from set-up to outputs; large ones as
+ * launches per check class and variable update.  Which one depends on the
+ * sizes, the results do not.  MET_NO_COMPACT, MET_NO_DEG1_SKIP and a met_tuning
+ * that names a launch shape (met_decode_ex) select the launches.
+ * Errors: MET_EINVAL, MET_EHIP. */
 int met_decode(const met_code *c, const float *llr, const uint8_t *syn, int32_t B, int32_t max_iter,
                uint32_t flags, uint8_t *bits, int32_t *iters, uint8_t *converged, float *posterior,
                void *workspace, size_t ws_bytes, void *stream);

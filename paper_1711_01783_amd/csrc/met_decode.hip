@@ -43,6 +43,7 @@
 // emptied groups.  A frame's arithmetic does not depend on its lane, so the
 // results are identical with and without compaction.
 #include "met_gpu.h"
+#include "met_team.h"
 
 namespace met {
 
@@ -442,6 +443,13 @@ int device_code(const met_code *cc, const DeviceCode **out) {
     *out = &d;
     return MET_OK;
   }
+  std::vector<int32_t> plane(c->E12);  // edge -> its plane-wise position
+  for (const CheckClass &k : c->classes)
+    for (int64_t i = 0; i < k.n_checks; ++i)
+      for (int64_t e = c->chk_msg_ptr[k.first_check + i], m = 0; e < c->chk_msg_ptr[k.first_check + i + 1]; ++e, ++m)
+        plane[e] = (int32_t)(k.shape == kShapeGeneric ? e : k.first_msg + m * k.n_checks + i);
+  std::vector<int32_t> vn_plane(c->vn_edges.size());
+  for (size_t i = 0; i < vn_plane.size(); ++i) vn_plane[i] = plane[c->vn_edges[i]];
   struct Part {
     const void *src;
     size_t bytes;
@@ -454,7 +462,7 @@ int device_code(const met_code *cc, const DeviceCode **out) {
       {c->msg_vn_user.data(), c->msg_vn_user.size() * 4, 0}, {c->vn_slot.data(), c->vn_slot.size() * 4, 0},
       {c->chk_msg_ptr.data(), c->chk_msg_ptr.size() * 4, 0}, {c->chk_leaf_ptr.data(), c->chk_leaf_ptr.size() * 4, 0},
       {c->vn.data(), c->vn.size() * 4, 0},                   {c->chk_ptr.data(), c->chk_ptr.size() * 4, 0},
-      {c->chk_pos.data(), c->chk_pos.size() * 4, 0},
+      {c->chk_pos.data(), c->chk_pos.size() * 4, 0},         {vn_plane.data(), vn_plane.size() * 4, 0},
   };
   size_t total = 0;
   for (Part &p : parts) {
@@ -488,6 +496,7 @@ int device_code(const met_code *cc, const DeviceCode **out) {
   d.all_vn = reinterpret_cast<const int32_t *>(b + parts[10].off);
   d.all_ptr = reinterpret_cast<const int32_t *>(b + parts[11].off);
   d.chk_pos = reinterpret_cast<const int32_t *>(b + parts[12].off);
+  d.vn_edges_plane = reinterpret_cast<const int32_t *>(b + parts[13].off);
   d.ready = true;
   *out = &d;
   return MET_OK;
@@ -566,10 +575,12 @@ extern "C" int met_decode_workspace_bytes(const met_code *c, int32_t B, uint32_t
   });
 }
 
-extern "C" int met_decode_ex(const met_code *c, const float *llr, const uint8_t *syn, int32_t B, int32_t max_iter,
-                             uint32_t flags, uint8_t *bits, int32_t *iters, uint8_t *converged, float *posterior,
-                             void *workspace, size_t ws_bytes, const met_tuning *tuning, void *stream) { return met::guarded("met_decode_ex", [&]() -> int {
-  met::clear_error();
+// `whole`: the workspace must hold all that met_decode_workspace_bytes counts;
+// otherwise what the launches need is enough (and the team decoder is used
+// where it fits).
+static int decode_checked(const met_code *c, const float *llr, const uint8_t *syn, int32_t B, int32_t max_iter,
+                          uint32_t flags, uint8_t *bits, int32_t *iters, uint8_t *converged, float *posterior,
+                          void *workspace, size_t ws_bytes, bool whole, const met_tuning *tuning, void *stream) {
   int rc = validate_decode(c, B, flags);
   if (rc) return rc;
   if (!llr || !syn || !bits || !iters || !converged || !workspace) return fail(MET_EINVAL, "NULL buffer");
@@ -593,10 +604,21 @@ extern "C" int met_decode_ex(const met_code *c, const float *llr, const uint8_t 
   if (rc) return rc;
   const int W = met::choose_interleave(B);
   const met::Plan pl = met::make_plan(c, B, posterior != nullptr, false, W, c2v_bytes(flags));
-  if (ws_bytes < pl.total) return fail(MET_EINVAL, "workspace of %zu bytes, %zu needed", ws_bytes, pl.total);
+  const size_t need = whole ? pl.total : pl.launch_total;
+  if (ws_bytes < need) return fail(MET_EINVAL, "workspace of %zu bytes, %zu needed", ws_bytes, need);
   const met::DeviceCode *d = nullptr;
   rc = met::device_code(c, &d);
   if (rc) return rc;
+  // Small decodes run in teams (same results); a call that asks for launch
+  // shapes, for uncompacted groups or for degree-1 nodes iterated gets the
+  // launches it asks for.
+  const bool shaped = tuning && (tuning->check_steps_per_wave || tuning->variable_chunk);
+  if (!shaped && !(flags & (MET_NO_COMPACT | MET_NO_DEG1_SKIP))) {
+    const int tw = met::team_width(c, B, posterior != nullptr, c2v_bytes(flags), !(flags & MET_FIXED_ITERS), ws_bytes);
+    if (tw)
+      return met::team_decode(c, d, tw, llr, syn, B, max_iter, flags, bits, iters, converged, posterior,
+                              static_cast<char *>(workspace), (hipStream_t)stream);
+  }
   met::Decoder dec{c, d, pl, static_cast<char *>(workspace), (hipStream_t)stream, B, ipw, chunk};
   if (flags & MET_C2V_FP16)
     return dec.run<64, met::half_t>(llr, syn, max_iter, flags, bits, iters, converged, posterior, nullptr, 0);
@@ -611,6 +633,14 @@ extern "C" int met_decode_ex(const met_code *c, const float *llr, const uint8_t 
     case 32: return dec.run<32>(llr, syn, max_iter, flags, bits, iters, converged, posterior, nullptr, 0);
     default: return dec.run<64>(llr, syn, max_iter, flags, bits, iters, converged, posterior, nullptr, 0);
   }
+}
+
+extern "C" int met_decode_ex(const met_code *c, const float *llr, const uint8_t *syn, int32_t B, int32_t max_iter,
+                             uint32_t flags, uint8_t *bits, int32_t *iters, uint8_t *converged, float *posterior,
+                             void *workspace, size_t ws_bytes, const met_tuning *tuning, void *stream) { return met::guarded("met_decode_ex", [&]() -> int {
+  met::clear_error();
+  return decode_checked(c, llr, syn, B, max_iter, flags, bits, iters, converged, posterior, workspace, ws_bytes, true,
+                        tuning, stream);
   });
 }
 
@@ -660,8 +690,8 @@ extern "C" int met_decode_noalloc(const met_code *c, const float *llr, const uin
   if (flags & MET_NO_DEG1_SKIP)
     return fail(MET_EINVAL, "MET_NO_DEG1_SKIP builds a second layout of the code (allocates): not here");
   const met::Plan pl = met::make_plan(c, B, posterior != nullptr, false, met::choose_interleave(B), c2v_bytes(flags));
-  if (pl.total > kScratchBytes)
-    return fail(MET_EINVAL, "decode needs %zu bytes of workspace, the fixed scratch array holds %zu", pl.total,
+  if (pl.launch_total > kScratchBytes)
+    return fail(MET_EINVAL, "decode needs %zu bytes of workspace, the fixed scratch array holds %zu", pl.launch_total,
                 kScratchBytes);
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
@@ -680,8 +710,8 @@ extern "C" int met_decode_noalloc(const met_code *c, const float *llr, const uin
   void *ws = nullptr;
   rc = scratch_address(&ws);
   if (rc) return rc;
-  return met_decode_ex(c, llr, syn, B, max_iter, flags, bits, iters, converged, posterior, ws, kScratchBytes,
-                       nullptr, stream);
+  return decode_checked(c, llr, syn, B, max_iter, flags, bits, iters, converged, posterior, ws, kScratchBytes, false,
+                        nullptr, stream);
   });
 }
 

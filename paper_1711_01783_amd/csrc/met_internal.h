@@ -62,6 +62,9 @@ struct DeviceCode {
   const int8_t *edge_type = nullptr;     // [E12]
   const int32_t *vn_ptr = nullptr;       // [N2+1]
   const int32_t *vn_edges = nullptr;     // [E12] message edge positions, grouped by VN
+  // the same lists with the message edges of each fixed-shape class counted
+  // plane by plane: edge m of check i at first_msg + m n_checks + i (team decoder)
+  const int32_t *vn_edges_plane = nullptr;
   const int32_t *leaf_vn = nullptr;      // [EL] user index of each leaf edge's VN (check order)
   const int8_t *leaf_type = nullptr;     // [EL]
   const int32_t *msg_vn_user = nullptr;  // [N2]

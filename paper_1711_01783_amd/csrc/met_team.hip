@@ -1,0 +1,1014 @@
+// Decoding in teams: one launch decodes a whole batch, each frame group by the
+// workgroups of one accelerator die (XCD).
+//
+// Frames are independent, so a batch of B frames is cut into small groups of W
+// frames and each group is decoded from set-up to outputs by one team: the
+// workgroups that run on one XCD.  A group's state (messages, posteriors, leaf
+// inputs) lives in that die's L2, the phases of an iteration (Methods, Steps
+// 3-5: check update, variable update) are separated by a barrier among the
+// team's workgroups alone, and a team whose frames have all stopped takes the
+// next group.  No launch, host round trip or device-wide barrier remains
+// inside a decode, and a frame that needs many iterations holds up only the
+// few frames of its group.
+//
+// Coherence inside a team.  All workgroups of a team share one L2, so data
+// written by one is visible to the others once its stores are acknowledged
+// (vmcnt(0)) if the readers bypass their own first-level cache: loads of words
+// that other workgroups write carry the sc1 (device scope) bit, which this
+// cache does not serve and the L2 does.  No cache is flushed or invalidated (an
+// acquire fence costs 1.8 us for each wave that issues it).  The barrier is one
+// store and a poll of all members' flags: 0.46 us for 32 workgroups.
+//
+// Forming teams.  A workgroup reads the number of its XCD and registers with
+// that XCD's counter.  The first to register waits until the expected number
+// has arrived, or 20 us, and closes the registration; the team is who has
+// registered by then.  A workgroup that comes later exits.  Nobody ever waits
+// for a workgroup that is not running, so concurrent launches on other streams
+// or in other processes cannot block each other; they only make teams smaller.
+//
+// The arithmetic is that of met_gpu.h's kernels, operation by operation, so
+// the results equal the per-phase launches' bit for bit.
+#include <cmath>
+
+#include "met_gpu.h"
+#include "met_team.h"
+
+namespace met {
+namespace {
+
+constexpr int kTeamBlock = 1024;
+constexpr int kTeamWaves = kTeamBlock / 64;
+constexpr int kXccIds = 16;             // values of the XCC_ID register
+constexpr int kMaxTeam = 64;            // workgroups of one team
+constexpr uint32_t kClosed = 0x80000000u;
+constexpr uint64_t kFormTicks = 2000;   // 20 us of the 100 MHz counter
+constexpr uint32_t kPollLimit = 1u << 22;  // polls of about 0.4 us
+
+// Control words at the start of the workspace, cleared before the launch.
+struct TeamControl {
+  uint32_t next_slot, pad0[31];
+  uint32_t next_group, pad1[31];
+  struct {
+    uint32_t count, pad0[31];
+    uint32_t pub, pad1[31];             // members + 256 (slot + 1), set once
+  } reg[kXccIds];
+  uint64_t flag[kXccIds][2][kMaxTeam];  // epoch in the low word, payload in the high one
+};
+
+__global__ __launch_bounds__(kBlock) void k_team_clear(uint32_t *ctl) {
+  for (size_t i = threadIdx.x; i < sizeof(TeamControl) / 4; i += kBlock) ctl[i] = 0u;
+}
+
+// ---- Memory -----------------------------------------------------------------
+// State arrays are addressed as buffers: a descriptor in scalar registers and a
+// 32-bit byte offset per lane; reads past the end return 0.
+
+using rsrc_t = __amdgpu_buffer_rsrc_t;
+constexpr int kSc1 = 16;                 // cache policy bit of the buffer instructions
+// Offsets past the end of every array, also after the scaling of element
+// numbers to bytes (1, 2 or 4 per element); kMaxSlotBytes keeps arrays below.
+constexpr uint32_t kNowhere = 0xFFFFFFF0u;
+constexpr size_t kMaxTeamBytes = 192u << 20;  // states of all slots: within the Infinity Cache
+constexpr size_t kMaxSlotBytes = kNowhere / 4u - 1024u;
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ rsrc_t buffer_of(const void *p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
+}
+
+template <int F, int AUX>
+__device__ __forceinline__ void ld_f32(rsrc_t r, uint32_t off, float (&v)[F]) {
+  if constexpr (F == 4) {
+    const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX);
+#pragma unroll
+    for (int f = 0; f < 4; ++f) v[f] = __uint_as_float(t[f]);
+  } else if constexpr (F == 2) {
+    const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, AUX);
+    v[0] = __uint_as_float(t[0]);
+    v[1] = __uint_as_float(t[1]);
+  } else {
+    v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, AUX));
+  }
+}
+
+template <int F>
+__device__ __forceinline__ void st_f32(rsrc_t r, uint32_t off, const float (&v)[F]) {
+  if constexpr (F == 4) {
+    u32x4 t;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) t[f] = __float_as_uint(v[f]);
+    __builtin_amdgcn_raw_buffer_store_b128(t, r, off, 0, 0);
+  } else if constexpr (F == 2) {
+    u32x2 t;
+    t[0] = __float_as_uint(v[0]);
+    t[1] = __float_as_uint(v[1]);
+    __builtin_amdgcn_raw_buffer_store_b64(t, r, off, 0, 0);
+  } else {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[0]), r, off, 0, 0);
+  }
+}
+
+// Tables of the 8-bit storage in LDS.
+struct Tables {
+  const float *q8;       // [128] grid values
+  const float *phi;      // [kLutSize] (table-driven check update)
+  const uint8_t *code;   // [kLutSize]
+};
+
+__device__ __forceinline__ float q8_value(uint32_t c, const Tables &tab) {
+  const float m = tab.q8[c & 127u];
+  return (c & 128u) ? -m : m;
+}
+
+// F messages of storage type CT; F > 1 reads one aligned word.
+template <int F, typename CT, int AUX>
+__device__ __forceinline__ void ld_msgs(rsrc_t r, uint32_t elem, const Tables &tab, float (&v)[F]) {
+  if constexpr (std::is_same<CT, float>::value) {
+    ld_f32<F, AUX>(r, elem * 4u, v);
+  } else if constexpr (std::is_same<CT, half_t>::value) {
+    static_assert(F == 4 || F == 1, "half rows are read by one or four frames");
+    if constexpr (F == 4) {
+      const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(r, elem * 2u, 0, AUX);
+#pragma unroll
+      for (int f = 0; f < 4; ++f)
+        v[f] = (float)__builtin_bit_cast(half_t, (uint16_t)(t[f / 2] >> (16 * (f & 1))));
+    } else {
+      v[0] = (float)__builtin_bit_cast(half_t, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, elem * 2u, 0, AUX));
+    }
+  } else {
+    static_assert(F == 4 || F == 1, "8-bit rows are read by one or four frames");
+    if constexpr (F == 4) {
+      const uint32_t t = __builtin_amdgcn_raw_buffer_load_b32(r, elem, 0, AUX);
+#pragma unroll
+      for (int f = 0; f < 4; ++f) v[f] = q8_value(t >> (8 * f), tab);
+    } else {
+      v[0] = q8_value((uint8_t)__builtin_amdgcn_raw_buffer_load_b8(r, elem, 0, AUX), tab);
+    }
+  }
+}
+
+template <int F, typename CT>
+__device__ __forceinline__ void st_msgs(rsrc_t r, uint32_t elem, const float (&v)[F]) {
+  if constexpr (std::is_same<CT, float>::value) {
+    st_f32<F>(r, elem * 4u, v);
+  } else if constexpr (std::is_same<CT, half_t>::value) {
+    uint16_t h[F];
+#pragma unroll
+    for (int f = 0; f < F; ++f) h[f] = __builtin_bit_cast(uint16_t, (half_t)v[f]);
+    if constexpr (F == 4) {
+      u32x2 t;
+      t[0] = h[0] | ((uint32_t)h[1] << 16);
+      t[1] = h[2] | ((uint32_t)h[3] << 16);
+      __builtin_amdgcn_raw_buffer_store_b64(t, r, elem * 2u, 0, 0);
+    } else {
+      __builtin_amdgcn_raw_buffer_store_b16(h[0], r, elem * 2u, 0, 0);
+    }
+  } else {
+    uint32_t t = 0;
+#pragma unroll
+    for (int f = 0; f < F; ++f) t |= q8_encode(v[f]) << (8 * f);
+    if constexpr (F == 4)
+      __builtin_amdgcn_raw_buffer_store_b32(t, r, elem, 0, 0);
+    else
+      __builtin_amdgcn_raw_buffer_store_b8((uint8_t)t, r, elem, 0, 0);
+  }
+}
+
+// ---- One group's work ---------------------------------------------------------
+
+// Lanes of a wave in the check phase: an item (check) takes W / F lanes, each of
+// which holds F frames in registers, so that an index is read once for F frames
+// and rows are read as whole words.
+template <int W>
+constexpr int kFramesPerLane = W < 4 ? W : 4;
+
+struct GroupState {
+  const TeamJob *job;
+  char *base;
+  rsrc_t c2v, P, L2, Lphi, syn, B1;
+  uint32_t b1_half;  // bytes of one of the two buffers of B1
+  // arrays of decodes with posterior output
+  __device__ rsrc_t Lraw() const { return buffer_of(base + job->off_Lraw, job->off_P1 - job->off_Lraw); }
+  __device__ rsrc_t P1(int it) const {
+    const uint32_t half = (job->off_syn - job->off_P1) / 2;
+    return buffer_of(base + job->off_P1 + ((it & 1) ? half : 0u), half);
+  }
+};
+
+// The frames named by `lanes`, a mask over lanes of which each holds frames
+// FL (lane % (W / FL)) + f of its check.
+template <int W, int FL>
+__device__ __forceinline__ uint32_t frames_of(const uint64_t (&lanes)[FL]) {
+  constexpr int LPI = W / FL;
+  uint32_t word = 0;
+#pragma unroll
+  for (int f = 0; f < FL; ++f)
+#pragma unroll
+    for (int wl = 0; wl < LPI; ++wl) {
+      uint64_t those = 0;
+#pragma unroll
+      for (int l = wl; l < 64; l += LPI) those |= 1ull << l;
+      word |= (lanes[f] & those) ? 1u << (wl * FL + f) : 0u;
+    }
+  return word;
+}
+
+// What a phase does besides the message update.
+struct Phase {
+  bool first;   // iteration 1: P = L, c2v = 0
+  bool test;    // syndrome test of the previous iteration
+  bool decide;  // leaf decisions of this iteration are needed
+  bool post;    // leaf posteriors of this iteration are needed
+  int it;
+  uint32_t act; // frames of the group that run
+};
+
+// Wide checks take one lane per frame (a tile of them would otherwise be the
+// longest chain of a phase), narrow ones kFramesPerLane frames per lane.
+template <int W, int NM, int NL, typename CT>
+__device__ __forceinline__ void check_tile(const GroupState &s, const int32_t *edge_msgvn, const TeamClass &c,
+                                           uint32_t tile, const Phase &ph, const Tables &tab, uint32_t &unsat) {
+  constexpr int F = NM > 4 ? 1 : kFramesPerLane<W>, LPI = W / F, D = NM + NL;
+  constexpr int FW = kFramesPerLane<W>, WPI = W / FW;  // decisions and syndrome bits: WPI bytes of FW bits
+  static_assert(NL == 0 || F == FW, "a lane owns whole bytes of decisions");
+  constexpr bool lut = std::is_same<CT, q8lut_t>::value;
+  const uint32_t lane = threadIdx.x & 63, wl = lane % LPI;
+  const uint32_t i = tile * (64 / LPI) + lane / LPI;
+  const bool valid = i < (uint32_t)c.n_checks;
+  const uint32_t item = valid ? i : 0u;
+  const uint32_t m0 = (uint32_t)c.first_msg + item * NM, l0 = (uint32_t)c.first_leaf + item * NL;
+  const uint32_t chk = (uint32_t)c.first_check + item;
+  // the class's messages lie plane by plane (edge m of every check together),
+  // so that a wave's rows are contiguous: rows of 16 bytes at a stride of 48
+  // were stored at the rate of scattered ones (1.9 ns per row and CU)
+  const uint32_t p0 = (uint32_t)c.first_msg + item;
+  const bool partial = ph.act != (uint32_t)wmask<W>();
+  const uint32_t b1_in = ((ph.it - 1) & 1) ? s.b1_half : 0u, b1_out = (ph.it & 1) ? s.b1_half : 0u;
+  float x[NM][F], cv[NM][F], lf[NL > 0 ? NL : 1][F];
+  uint32_t b1[NL > 0 ? NL : 1], old[NL > 0 ? NL : 1];
+  uint32_t vi[NM];
+#pragma unroll
+  for (int m = 0; m < NM; ++m) vi[m] = (uint32_t)edge_msgvn[m0 + m];
+  uint32_t sb = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(s.syn, chk * WPI + wl * F / FW, 0, kSc1);
+#pragma unroll
+  for (int m = 0; m < NM; ++m) ld_f32<F, kSc1>(ph.first ? s.L2 : s.P, (vi[m] * W + wl * F) * 4u, x[m]);
+#pragma unroll
+  for (int m = 0; m < NM; ++m) {
+    // this thread's own words of the previous iteration
+    if (!ph.first) {
+      ld_msgs<F, CT, 0>(s.c2v, (p0 + m * (uint32_t)c.n_checks) * W + wl * F, tab, cv[m]);
+    } else {
+#pragma unroll
+      for (int f = 0; f < F; ++f) cv[m][f] = 0.0f;
+    }
+  }
+#pragma unroll
+  for (int l = 0; l < NL; ++l) {
+    ld_f32<F, kSc1>(s.Lphi, ((l0 + l) * W + wl * F) * 4u, lf[l]);
+    b1[l] = ph.test ? (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(s.B1, b1_in + (l0 + l) * WPI + wl, 0, kSc1) : 0u;
+    old[l] = ph.decide && partial
+                 ? (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(s.B1, b1_out + (l0 + l) * WPI + wl, 0, kSc1)
+                 : 0u;
+  }
+  if constexpr (F != FW) sb >>= wl % FW;
+  const uint64_t mvalid = __ballot(valid);
+  uint32_t tb = sb;  // parity of the syndrome bit and the leaf decisions
+#pragma unroll
+  for (int l = 0; l < NL; ++l) tb ^= b1[l];
+  // Signs, parities and decisions are lane masks in scalar registers (one
+  // vector compare each, the logic on the scalar unit).
+  uint64_t bad[F];
+#pragma unroll
+  for (int f = 0; f < F; ++f) {
+    bad[f] = __ballot(tb & (1u << f));
+#pragma unroll
+    for (int m = 0; m < NM; ++m) bad[f] ^= __ballot(x[m][f] < 0.0f);
+    bad[f] &= mvalid;
+  }
+  if (ph.test) unsat |= frames_of<W, F>(bad);
+#pragma unroll
+  for (int m = 0; m < NM; ++m)
+#pragma unroll
+    for (int f = 0; f < F; ++f) x[m][f] = clamp_llr(x[m][f] - cv[m][f]);
+  uint32_t dec[NL > 0 ? NL : 1], code[NM];
+  float Sl[NL > 0 ? NL : 1][F];  // phi-domain sum of a leaf's message, with that message's sign
+#pragma unroll
+  for (int l = 0; l < NL; ++l) dec[l] = 0;
+#pragma unroll
+  for (int m = 0; m < NM; ++m) code[m] = 0;
+#pragma unroll
+  for (int f = 0; f < F; ++f) {
+    float A[D];
+    uint32_t sg[D], tot = sb << (31 - f);
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      if constexpr (lut)
+        A[m] = tab.phi[lut_index(fabsf(x[m][f]))];
+      else
+        A[m] = phi(fabsf(x[m][f]));
+      sg[m] = __float_as_uint(x[m][f]);
+      tot ^= sg[m];
+    }
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+      A[NM + l] = fabsf(lf[l][f]);
+      sg[NM + l] = __float_as_uint(lf[l][f]);
+      tot ^= sg[NM + l];
+    }
+    // leave-one-out sums by prefix and suffix sums, as check_fixed_body
+    float pre[D], suf[D], S[D];
+    pre[1] = A[0];
+#pragma unroll
+    for (int m = 2; m < D; ++m) pre[m] = pre[m - 1] + A[m - 1];
+    suf[D - 2] = A[D - 1];
+#pragma unroll
+    for (int m = D - 3; m >= 0; --m) suf[m] = suf[m + 1] + A[m + 1];
+    S[0] = suf[0];
+    S[D - 1] = pre[D - 1];
+#pragma unroll
+    for (int m = 1; m < D - 1; ++m) S[m] = pre[m] + suf[m];
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      if constexpr (lut) {
+        code[m] |= (tab.code[lut_index(S[m])] | (((tot ^ sg[m]) >> 24) & 128u)) << (8 * f);
+      } else {
+        const uint32_t mag = __float_as_uint(phi(S[m]));
+        x[m][f] = __uint_as_float(mag | ((tot ^ sg[m]) & 0x80000000u));
+      }
+    }
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+      // leaf_bit on masks: where the message agrees with the LLR's sign the
+      // decision is that sign, unless both are zero; otherwise the larger one
+      // decides, a tie 0
+      const float S1 = S[NM + l], A1 = A[NM + l];
+      const uint64_t mt = __ballot((int32_t)tot < 0), ml = __ballot((int32_t)sg[NM + l] < 0);
+      const uint64_t lt = __ballot(S1 < A1), gt = __ballot(S1 > A1), inf = __ballot(A1 == __builtin_huge_valf());
+      const uint64_t bits = (~mt & ml & (lt | ~inf)) | (mt & ((lt & ~ml) | (gt & ml)));
+      dec[l] |= __builtin_amdgcn_inverse_ballot_w64(bits) ? 1u << f : 0u;
+      Sl[l][f] = __uint_as_float(__float_as_uint(S1) | ((tot ^ sg[NM + l]) & 0x80000000u));
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < NM; ++m) {
+    const uint32_t elem = (p0 + m * (uint32_t)c.n_checks) * W + wl * F;
+    if (!valid) continue;
+    if constexpr (!lut)
+      st_msgs<F, CT>(s.c2v, elem, x[m]);
+    else if constexpr (F == 4)
+      __builtin_amdgcn_raw_buffer_store_b32(code[m], s.c2v, elem, 0, 0);
+    else
+      __builtin_amdgcn_raw_buffer_store_b8((uint8_t)code[m], s.c2v, elem, 0, 0);
+  }
+  if (NL > 0 && ph.decide && valid) {
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+      const uint32_t own = (ph.act >> (wl * F)) & ((1u << F) - 1u);
+      __builtin_amdgcn_raw_buffer_store_b8((uint8_t)((old[l] & ~own) | (dec[l] & own)), s.B1,
+                                           b1_out + (l0 + l) * WPI + wl, 0, 0);
+      if (ph.post) {
+        float lr[F], p1[F];
+        const uint32_t off = ((l0 + l) * W + wl * F) * 4u;
+        ld_f32<F, kSc1>(s.Lraw(), off, lr);
+        ld_f32<F, kSc1>(s.P1(ph.it), off, p1);
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+          if ((own >> f) & 1u) p1[f] = lr[f] + 1.0f * copysignf(phi(fabsf(Sl[l][f])), Sl[l][f]);
+        st_f32<F>(s.P1(ph.it), off, p1);
+      }
+    }
+  }
+}
+
+// Run-time degrees, frame by frame.  The suffix sums of a check are kept in
+// private memory and its inputs formed twice: few checks take this path, and
+// arrays of the largest degree in registers would set the whole kernel's
+// register count.
+template <int W, typename CT>
+__device__ __forceinline__ void check_tile_generic(const GroupState &s, const TeamJob &job, const TeamClass &c,
+                                                   uint32_t tile, const Phase &ph, const Tables &tab,
+                                                   uint32_t &unsat) {
+  constexpr int F = kFramesPerLane<W>, LPI = W / F;
+  const uint32_t lane = threadIdx.x & 63, wl = lane % LPI;
+  const uint32_t i = tile * (64 / LPI) + lane / LPI;
+  const bool valid = i < (uint32_t)c.n_checks;
+  const uint32_t chk = (uint32_t)c.first_check + (valid ? i : 0u);
+  const uint32_t m0 = (uint32_t)job.chk_msg_ptr[chk], l0 = (uint32_t)job.chk_leaf_ptr[chk];
+  const int nm = (int)((uint32_t)job.chk_msg_ptr[chk + 1] - m0);
+  const int n = nm + (int)((uint32_t)job.chk_leaf_ptr[chk + 1] - l0);
+  const uint32_t b1_in = ((ph.it - 1) & 1) ? s.b1_half : 0u, b1_out = (ph.it & 1) ? s.b1_half : 0u;
+  const uint32_t sb = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(s.syn, chk * LPI + wl, 0, kSc1);
+  uint32_t word = 0;
+#pragma unroll 1
+  for (int f = 0; f < F; ++f) {
+    const uint32_t w = wl * F + f;
+    const bool on = (ph.act >> w) & 1u;
+    // phi-domain input k with its sign; *decided: the parity of its decision
+    auto input = [&](int k, uint32_t *decided) {
+      if (k < nm) {
+        float pv[1], cv[1] = {0.0f};
+        ld_f32<1, kSc1>(ph.first ? s.L2 : s.P, ((uint32_t)job.edge_msgvn[m0 + k] * W + w) * 4u, pv);
+        if (!ph.first) ld_msgs<1, CT, 0>(s.c2v, (m0 + k) * W + w, tab, cv);
+        *decided ^= (uint32_t)(pv[0] < 0.0f);
+        const float x = clamp_llr(pv[0] - cv[0]);
+        return copysignf(phi(fabsf(x)), x);
+      }
+      const uint32_t le = l0 + (k - nm);
+      float lf[1];
+      ld_f32<1, kSc1>(s.Lphi, (le * W + w) * 4u, lf);
+      if (ph.test)
+        *decided ^= ((uint8_t)__builtin_amdgcn_raw_buffer_load_b8(s.B1, b1_in + le * LPI + wl, 0, kSc1) >> f) & 1u;
+      return lf[0];
+    };
+    float suf[MET_MAX_CHECK_DEGREE];
+    float run = 0.0f;
+    uint32_t parity = (sb >> f) & 1u, tot = parity, unused = 0;
+#pragma unroll 1
+    for (int k = n - 1; k >= 0; --k) {
+      const float a = input(k, &parity);
+      suf[k] = run;
+      run = run + fabsf(a);
+      tot ^= sign_bit(a);
+    }
+    if (ph.test && valid) word |= (parity & 1u) << w;
+    run = 0.0f;
+#pragma unroll 1
+    for (int k = 0; k < n; ++k) {
+      const float a = input(k, &unused);
+      const float S = run + suf[k];
+      run = run + fabsf(a);
+      const uint32_t neg = sign_bit(a), neg_c = (tot ^ neg) & 1u;
+      const float mag = phi(S);
+      if (k < nm) {
+        const float out[1] = {neg_c ? -mag : mag};
+        if (valid) st_msgs<1, CT>(s.c2v, (m0 + k) * W + w, out);
+      } else if (ph.decide && valid && on) {
+        const uint32_t le = l0 + (k - nm), at = b1_out + le * LPI + wl;
+        const uint32_t bit = leaf_bit(neg, neg_c, S, fabsf(a));
+        // this thread's own byte: the decisions of its F frames, one by one
+        const uint32_t was = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(s.B1, at, 0, kSc1);
+        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)((was & ~(1u << f)) | (bit << f)), s.B1, at, 0, 0);
+        if (ph.post) {
+          float lr[1];
+          const uint32_t off = (le * W + w) * 4u;
+          ld_f32<1, kSc1>(s.Lraw(), off, lr);
+          const float p1[1] = {lr[0] + 1.0f * (neg_c ? -mag : mag)};
+          st_f32<1>(s.P1(ph.it), off, p1);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int w = 0; w < W; ++w) unsat |= __ballot((word >> w) & 1u) ? 1u << w : 0u;
+}
+
+// Variable update of 64 / (W K) nodes: K lanes share a node's edges, each with U
+// gathers in flight; the sum runs through the K lanes in list order (a chain of
+// shuffles), so it is the sequential sum of variable_body.
+template <int W, int K, int U, typename CT>
+__device__ __forceinline__ void variable_tile(const GroupState &s, const int32_t *vn_ptr, const int32_t *vn_edges,
+                                              uint32_t n2, uint32_t tile, uint32_t act, const Tables &tab) {
+  const uint32_t lane = threadIdx.x & 63, w = lane % W, sub = (lane / W) % K;
+  const uint32_t v = tile * (64 / (W * K)) + lane / (W * K);
+  const bool on = v < n2 && ((act >> w) & 1u);
+  const uint32_t vv = v < n2 ? v : 0u;
+  uint32_t e = (uint32_t)vn_ptr[vv];
+  const uint32_t e1 = on ? (uint32_t)vn_ptr[vv + 1] : 0u;
+  float acc[1];
+  ld_f32<1, kSc1>(s.L2, (vv * W + w) * 4u, acc);
+  while (__any(e < e1)) {
+    float a[U][1];
+    uint32_t at[U];
+    const uint32_t first = e + sub * U;
+    int cnt = e1 > first ? (int)min(e1 - first, (uint32_t)U) : 0;  // this lane's edges
+#pragma unroll
+    for (int u = 0; u < U; ++u) at[u] = u < cnt ? (uint32_t)vn_edges[first + u] * W + w : kNowhere / 4u;
+#pragma unroll
+    for (int u = 0; u < U; ++u) ld_msgs<1, CT, kSc1>(s.c2v, at[u], tab, a[u]);
+    asm volatile("" : "+v"(cnt));  // compared again below: keeping U masks spills scalar registers
+    float in = acc[0];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      float x = in;
+#pragma unroll
+      for (int u = 0; u < U; ++u) x = u < cnt ? x + a[u][0] : x;
+      // the partial sum of lane k goes to all lanes of the node
+      in = K > 1 ? __shfl(x, (int)((lane & ~(uint32_t)(W * K - 1)) + k * W + w)) : x;
+    }
+    acc[0] = in;
+    e += K * U;
+  }
+  if (on && sub == 0) st_f32<1>(s.P, (vv * W + w) * 4u, acc);
+}
+
+// ---- The team -----------------------------------------------------------------
+
+struct TeamShared {
+  uint32_t rank, n, slot, err;
+  uint32_t word;    // OR of the waves' payloads
+  uint32_t result;  // OR of the members' payloads
+  int32_t stop[16]; // iteration at which each frame of the group stopped
+};
+
+__device__ __forceinline__ uint32_t xcc_id() {
+  uint32_t v;
+  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(v));
+  return v & (kXccIds - 1);
+}
+
+// Registers the workgroup with its XCD's team; false if it has no part in it.
+__device__ bool join_team(TeamControl *ctl, uint32_t xcc, uint32_t expected, uint32_t n_slots, TeamShared &sh) {
+  if (threadIdx.x == 0) {
+    auto &r = ctl->reg[xcc];
+    sh.err = 0;
+    sh.word = 0;
+    const uint32_t rank = __hip_atomic_fetch_add(&r.count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t pub = 0;
+    if (rank & kClosed) {
+      pub = 1;  // too late: no slot
+    } else if (rank == 0) {
+      const uint64_t t0 = wall_clock64();
+      while (__hip_atomic_load(&r.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < expected &&
+             wall_clock64() - t0 < kFormTicks) {
+      }
+      const uint32_t slot = __hip_atomic_fetch_add(&ctl->next_slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint32_t n = __hip_atomic_fetch_or(&r.count, kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      pub = min(n, (uint32_t)kMaxTeam) | (slot < n_slots ? (slot + 1) << 8 : 0u);
+      __hip_atomic_store(&r.pub, pub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      for (uint32_t i = 0; i < kPollLimit; ++i) {
+        pub = __hip_atomic_load(&r.pub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (pub) break;
+        __builtin_amdgcn_s_sleep(1);
+      }
+    }
+    sh.rank = rank;
+    sh.n = pub & 255u;
+    sh.slot = pub >> 8;  // slot + 1, 0: nothing to do
+  }
+  __syncthreads();
+  return sh.slot != 0 && sh.rank < sh.n;
+}
+
+// Barrier of the team's workgroups; returns the OR of everything the members
+// put into sh.word before it.  sh.err is set if a member never came (it cannot:
+// every member is running), and the caller leaves.
+struct TeamBarrier {
+  TeamControl *ctl;
+  uint32_t xcc, rank, n, epoch;
+  __device__ uint32_t operator()(TeamShared &sh) {
+    ++epoch;
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x < 64) {
+      uint64_t *fl = ctl->flag[xcc][epoch & 1];
+      if (threadIdx.x == 0) {
+        const uint64_t mine = ((uint64_t)sh.word << 32) | epoch;
+        sh.word = 0;
+        // stays in the XCD's L2, where the members' polls find it
+        __hip_atomic_store(fl + rank, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+      uint64_t v = 0;
+      uint32_t i = 0;
+      for (;; ++i) {
+        v = threadIdx.x < n ? __hip_atomic_load(fl + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : epoch;
+        if (__all((uint32_t)v == epoch)) break;
+        if (i == kPollLimit) break;
+      }
+      uint32_t w = (uint32_t)(v >> 32);
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) w |= __shfl_xor(w, d);
+      if (threadIdx.x == 0) {
+        sh.result = w;
+        if (i == kPollLimit) sh.err = 1;
+      }
+    }
+    __syncthreads();
+    return sh.result;
+  }
+};
+
+template <int W, typename CT>
+__device__ __forceinline__ void check_phase(const TeamJob &job, const GroupState &s, const Phase &ph,
+                                            uint32_t wave, uint32_t waves, const Tables &tab, TeamShared &sh) {
+  uint32_t unsat = 0;
+  int c = 0;
+  for (uint32_t t = wave; t < (uint32_t)job.check_tiles; t += waves) {
+    while (c + 1 < job.n_classes && t >= (uint32_t)job.cls[c + 1].tile0) ++c;
+    const TeamClass k = job.cls[c];
+    const uint32_t tile = t - (uint32_t)k.tile0;
+    switch (k.shape) {
+      case 0: check_tile<W, 3, 1, CT>(s, job.edge_msgvn, k, tile, ph, tab, unsat); break;
+      case 1: check_tile<W, 2, 1, CT>(s, job.edge_msgvn, k, tile, ph, tab, unsat); break;
+      case 2: check_tile<W, 12, 0, CT>(s, job.edge_msgvn, k, tile, ph, tab, unsat); break;
+      case 3: check_tile<W, 11, 0, CT>(s, job.edge_msgvn, k, tile, ph, tab, unsat); break;
+      case 4: check_tile<W, 6, 0, CT>(s, job.edge_msgvn, k, tile, ph, tab, unsat); break;
+      case 5: check_tile<W, 5, 0, CT>(s, job.edge_msgvn, k, tile, ph, tab, unsat); break;
+      case 6: check_tile<W, 4, 0, CT>(s, job.edge_msgvn, k, tile, ph, tab, unsat); break;
+      default: check_tile_generic<W, CT>(s, job, k, tile, ph, tab, unsat);
+    }
+  }
+  if (unsat && (threadIdx.x & 63) == 0) atomicOr(&sh.word, unsat);
+}
+
+// Parity of the final decisions (after the last iteration).
+template <int W>
+__device__ __forceinline__ void test_phase(const TeamJob &job, const GroupState &s, int it, uint32_t wave,
+                                           uint32_t waves, TeamShared &sh) {
+  constexpr int F = kFramesPerLane<W>, LPI = W / F;
+  const uint32_t lane = threadIdx.x & 63, wl = lane % LPI;
+  const uint32_t b1 = (it & 1) ? s.b1_half : 0u;
+  uint32_t word = 0;
+  for (uint32_t t = wave; t * (64 / LPI) < (uint32_t)job.M; t += waves) {
+    const uint32_t j = t * (64 / LPI) + lane / LPI;
+    if (j >= (uint32_t)job.M) continue;
+    uint32_t par = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(s.syn, j * LPI + wl, 0, kSc1);
+    for (int32_t e = job.chk_msg_ptr[j]; e < job.chk_msg_ptr[j + 1]; ++e) {
+      float pv[F];
+      ld_f32<F, kSc1>(s.P, ((uint32_t)job.edge_msgvn[e] * W + wl * F) * 4u, pv);
+#pragma unroll
+      for (int f = 0; f < F; ++f) par ^= (uint32_t)(pv[f] < 0.0f) << f;
+    }
+    for (int32_t e = job.chk_leaf_ptr[j]; e < job.chk_leaf_ptr[j + 1]; ++e)
+      par ^= (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(s.B1, b1 + (uint32_t)e * LPI + wl, 0, kSc1);
+    word |= (par & ((1u << F) - 1u)) << (wl * F);
+  }
+  if (word) atomicOr(&sh.word, word);
+}
+
+// A group's inputs into its state: channel LLRs of the message nodes, leaf
+// inputs in the phi domain, syndrome bits.
+template <int W>
+__device__ __forceinline__ void setup_phase(const TeamJob &job, const GroupState &s, uint32_t g, uint32_t wave,
+                                            uint32_t waves) {
+  constexpr int F = kFramesPerLane<W>, LPI = W / F;
+  const uint32_t lane = threadIdx.x & 63, wl = lane % LPI;
+  const uint32_t items = (uint32_t)(job.EL + job.N2);
+  for (uint32_t t = wave; t * (64 / LPI) < items; t += waves) {
+    const uint32_t i = t * (64 / LPI) + lane / LPI;
+    if (i >= items) continue;
+    const bool leaf = i < (uint32_t)job.EL;
+    const uint32_t k = leaf ? i : i - (uint32_t)job.EL;
+    const int64_t v = leaf ? job.leaf_vn[k] : job.msg_vn_user[k];
+    float l[F];
+#pragma unroll
+    for (int f = 0; f < F; ++f) {
+      const uint32_t frame = g * W + wl * F + f;
+      l[f] = frame < (uint32_t)job.B ? job.llr[(int64_t)frame * job.N + v] : 0.0f;
+    }
+    const uint32_t off = (k * W + wl * F) * 4u;
+    if (leaf) {
+      float ph[F];
+#pragma unroll
+      for (int f = 0; f < F; ++f) ph[f] = copysignf(phi(fabsf(clamp_llr(l[f]))), l[f]);
+      st_f32<F>(s.Lphi, off, ph);
+      if (job.posterior) st_f32<F>(s.Lraw(), off, l);
+    } else {
+      st_f32<F>(s.L2, off, l);
+    }
+  }
+  for (uint32_t t = wave; t * (64 / LPI) < (uint32_t)job.M; t += waves) {
+    const uint32_t j = t * (64 / LPI) + lane / LPI;
+    if (j >= (uint32_t)job.M) continue;
+    uint32_t b = 0;
+#pragma unroll
+    for (int f = 0; f < F; ++f) {
+      const uint32_t frame = g * W + wl * F + f;
+      if (frame < (uint32_t)job.B) b |= (uint32_t)(job.syn[(int64_t)frame * job.M + j] & 1u) << f;
+    }
+    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)b, s.syn, (uint32_t)job.chk_pos[j] * LPI + wl, 0, 0);
+  }
+}
+
+// Outputs in user order, 64 consecutive nodes per wave and store.
+template <int W>
+__device__ __forceinline__ void output_phase(const TeamJob &job, const GroupState &s, uint32_t g, uint32_t wave,
+                                             uint32_t waves, const TeamShared &sh) {
+  constexpr int F = kFramesPerLane<W>, LPI = W / F;
+  const uint32_t lane = threadIdx.x & 63;
+  for (uint32_t t = wave; t * 64 < (uint32_t)job.N; t += waves) {
+    const uint32_t v = t * 64 + lane;
+    if (v >= (uint32_t)job.N) continue;
+    const int32_t slot = job.vn_slot[v];
+    const uint32_t k = slot >= 0 ? (uint32_t)slot : (uint32_t)(-(slot + 1));
+#pragma unroll
+    for (int wl = 0; wl < LPI; ++wl) {
+      float post[F];
+      uint32_t b = 0;
+      const uint32_t off = (k * W + wl * F) * 4u;
+      if (slot >= 0) {
+        ld_f32<F, kSc1>(s.P, off, post);
+#pragma unroll
+        for (int f = 0; f < F; ++f) b |= (uint32_t)(post[f] < 0.0f) << f;
+      } else {
+        const uint32_t ba = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(s.B1, k * LPI + wl, 0, kSc1);
+        const uint32_t bb = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(s.B1, s.b1_half + k * LPI + wl, 0, kSc1);
+#pragma unroll
+        for (int f = 0; f < F; ++f) b |= ((sh.stop[wl * F + f] & 1) ? bb : ba) & (1u << f);
+        if (job.posterior) {
+          float pa[F], pb[F];
+          ld_f32<F, kSc1>(s.P1(0), off, pa);
+          ld_f32<F, kSc1>(s.P1(1), off, pb);
+#pragma unroll
+          for (int f = 0; f < F; ++f) post[f] = (sh.stop[wl * F + f] & 1) ? pb[f] : pa[f];
+        }
+      }
+#pragma unroll
+      for (int f = 0; f < F; ++f) {
+        const uint32_t frame = g * W + wl * F + f;
+        if (frame >= (uint32_t)job.B) continue;
+        job.bits[(int64_t)frame * job.N + v] = (uint8_t)((b >> f) & 1u);
+        if (job.posterior) job.posterior[(int64_t)frame * job.N + v] = post[f];
+      }
+    }
+  }
+}
+
+template <int W, typename CT>
+__device__ __forceinline__ void variable_phase(const TeamJob &job, const GroupState &s, uint32_t act, uint32_t wave,
+                                               uint32_t waves, const Tables &tab) {
+  const uint32_t n2 = (uint32_t)job.N2;
+  auto sweep = [&](auto kc, auto uc) {
+    constexpr int K = decltype(kc)::value, U = decltype(uc)::value;
+    if constexpr (W * K <= 64) {
+      constexpr uint32_t per = 64 / (W * K);
+      for (uint32_t t = wave; t * per < n2; t += waves)
+        variable_tile<W, K, U, CT>(s, job.vn_ptr, job.vn_edges, n2, t, act, tab);
+    }
+  };
+  switch (job.lanes_per_vn) {
+    case 16: sweep(std::integral_constant<int, 16>{}, std::integral_constant<int, 8>{}); break;
+    case 4: sweep(std::integral_constant<int, 4>{}, std::integral_constant<int, 16>{}); break;
+    default: sweep(std::integral_constant<int, 1>{}, std::integral_constant<int, 24>{});
+  }
+}
+
+template <int W, typename CT>
+__global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
+  __shared__ TeamShared sh;
+  __shared__ float s_q8[std::is_class<CT>::value ? 128 : 1];
+  __shared__ float s_phi[std::is_same<CT, q8lut_t>::value ? kLutSize : 1];
+  __shared__ uint8_t s_code[std::is_same<CT, q8lut_t>::value ? kLutSize : 1];
+  TeamControl *ctl = reinterpret_cast<TeamControl *>(job.ws);
+  const uint32_t xcc = xcc_id();
+  if (!join_team(ctl, xcc, (uint32_t)job.expected, (uint32_t)job.n_slots, sh)) return;
+  if constexpr (std::is_class<CT>::value)
+    for (int i = threadIdx.x; i < 128; i += kTeamBlock) s_q8[i] = kQ8Table.v[i];
+  if constexpr (std::is_same<CT, q8lut_t>::value)
+    for (int i = threadIdx.x; i < kLutSize; i += kTeamBlock) {
+      s_phi[i] = kPhiTables.a[i];
+      s_code[i] = kPhiTables.out[i];
+    }
+  __syncthreads();
+  const Tables tab{s_q8, s_phi, s_code};
+  const uint32_t rank = sh.rank, n = sh.n, slot = sh.slot - 1;
+  TeamBarrier barrier{ctl, xcc, rank, n, 0};
+  const uint32_t wave = rank + n * (uint32_t)wave_id(), waves = n * kTeamWaves;
+  char *base = job.ws + job.off_slots + (size_t)slot * job.slot_bytes;
+  auto buf = [&](uint32_t off, uint32_t end) { return buffer_of(base + off, end - off); };
+  GroupState s;
+  s.job = &job;
+  s.base = base;
+  s.c2v = buf(0, job.off_P);
+  s.P = buf(job.off_P, job.off_L2);
+  s.L2 = buf(job.off_L2, job.off_Lphi);
+  s.Lphi = buf(job.off_Lphi, job.off_Lraw);
+  s.syn = buf(job.off_syn, job.off_B1);
+  s.B1 = buf(job.off_B1, job.slot_bytes);
+  s.b1_half = (job.slot_bytes - job.off_B1) / 2;
+
+  uint32_t g = slot;
+  while (g < (uint32_t)job.G) {
+    const uint32_t frames = min((uint32_t)W, (uint32_t)job.B - g * W);
+    uint32_t act = (1u << frames) - 1u;
+    if (threadIdx.x < W) {
+      sh.stop[threadIdx.x] = job.max_iter;
+      if (rank == 0 && threadIdx.x < frames) {
+        job.iters[g * W + threadIdx.x] = 0;
+        job.converged[g * W + threadIdx.x] = 0;
+      }
+    }
+    setup_phase<W>(job, s, g, wave, waves);
+    barrier(sh);
+    int it = 1;
+    for (; it <= job.max_iter && !sh.err; ++it) {
+      Phase ph;
+      ph.first = it == 1;
+      ph.test = job.early && it >= 2;
+      ph.decide = job.early || it == job.max_iter;
+      ph.post = ph.decide && job.posterior;
+      ph.it = it;
+      ph.act = act;
+      check_phase<W, CT>(job, s, ph, wave, waves, tab, sh);
+      const uint32_t unsat = barrier(sh);
+      if (ph.test) {
+        const uint32_t done = act & ~unsat;
+        if (threadIdx.x < W && ((done >> threadIdx.x) & 1u)) {
+          sh.stop[threadIdx.x] = it - 1;
+          if (rank == 0) {
+            job.iters[g * W + threadIdx.x] = it - 1;
+            job.converged[g * W + threadIdx.x] = 1;
+          }
+        }
+        act &= unsat;
+        if (!act) break;
+      }
+      variable_phase<W, CT>(job, s, act, wave, waves, tab);
+      barrier(sh);
+    }
+    if (act && !sh.err) {  // frames that ran the whole budget
+      test_phase<W>(job, s, job.max_iter, wave, waves, sh);
+      const uint32_t unsat = barrier(sh);
+      if (rank == 0 && threadIdx.x < W && ((act >> threadIdx.x) & 1u)) {
+        job.iters[g * W + threadIdx.x] = job.max_iter;
+        job.converged[g * W + threadIdx.x] = (uint8_t)!((unsat >> threadIdx.x) & 1u);
+      }
+    }
+    __syncthreads();  // sh.stop
+    if (sh.err) return;
+    output_phase<W>(job, s, g, wave, waves, sh);
+    if (job.G <= job.n_slots) return;
+    if (rank == 0 && threadIdx.x == 0)
+      sh.word = (uint32_t)job.n_slots +
+                __hip_atomic_fetch_add(&ctl->next_group, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    g = barrier(sh);
+    if (sh.err) return;
+  }
+}
+
+template <int W, typename CT>
+void launch_team(const TeamJob &job, unsigned grid, hipStream_t st) {
+  hipLaunchKernelGGL((k_team<W, CT>), dim3(grid), dim3(kTeamBlock), 0, st, job);
+}
+
+template <typename CT>
+void launch_reduced(int W, const TeamJob &job, unsigned grid, hipStream_t st) {
+  W == 4   ? launch_team<4, CT>(job, grid, st)
+  : W == 8 ? launch_team<8, CT>(job, grid, st)
+           : launch_team<16, CT>(job, grid, st);
+}
+
+// Lanes per variable node: as many as still leave one tile per wave of a full
+// team (a second round of tiles costs more than shorter gather chains save),
+// as the node degrees can use, and as W allows.
+int lanes_per_vn(const met_code *c, int W) {
+  const int64_t lanes = 32 * (int64_t)kTeamBlock;
+  for (int k : {16, 4})
+    if (W * k <= 64 && c->N2 * W * k <= lanes && c->max_vn_deg > 8 * (k / 4)) return k;
+  return 1;
+}
+
+}  // namespace
+
+size_t team_control_bytes() { return align256(sizeof(TeamControl)); }
+
+size_t team_slot(const met_code *c, int W, bool post, size_t c2v_bytes, TeamJob *job) {
+  const int F = W < 4 ? W : 4, LPI = W / F;
+  size_t o = 0;
+  auto take = [&](size_t bytes) {
+    const size_t at = o;
+    o += align256(bytes);
+    return at;
+  };
+  const size_t e = (size_t)c->E12 * W, v = (size_t)c->N2 * W * 4, l = (size_t)c->EL * W * 4;
+  (void)take(e * c2v_bytes);
+  const size_t off[] = {take(v), take(v), take(l), take(post ? l : 0), take(post ? 2 * align256(l) : 0),
+                        take((size_t)c->M * LPI), take(2 * align256((size_t)c->EL * LPI))};
+  if (job) {
+    job->off_P = (uint32_t)off[0];
+    job->off_L2 = (uint32_t)off[1];
+    job->off_Lphi = (uint32_t)off[2];
+    job->off_Lraw = (uint32_t)off[3];
+    job->off_P1 = (uint32_t)off[4];
+    job->off_syn = (uint32_t)off[5];
+    job->off_B1 = (uint32_t)off[6];
+    job->slot_bytes = (uint32_t)o;
+  }
+  return o;
+}
+
+
+// The rule compares the measured time of an iteration on both paths (us; E:
+// message edges in millions; float messages, rates 0.1 to 0.02, N = 4096 to
+// 10^6, 1 to 256 frames):
+//   team:     4.5 + (32 + 17.5 W) E per round of eight groups.  N = 65536, rate 0.1:
+//             W = 1 15.2, 2 17.8, 4 23.4, 8 38.5, 16 67; 8-bit messages
+//             (20 + 16 W): W = 4 19, 8 32, 16 57; N = 16384: W = 1 7.4, 4 9.4, 8
+//             11, 16 18; 15 % more once a group's state is beyond 8 MB, twice
+//             the L2 (N = 262144: W = 1 64, 4 96)
+//   launches: 3.4 per launch + 2.6 F E, F = frames in whole groups (2.1 F E
+//             with 16- or 8-bit messages).  N = 65536, rate 0.1: 1 frame 21, 16
+//             25, 64 52, 256 142; N = 262144: 1 frame 25, 16 50, 64 138; the
+//             team takes 64, 94 (W = 4) and 193 (W = 4) there
+// With early exit the launches run until the slowest of all frames stops, a team
+// until the slowest of each of its groups: in units of the former, a group of W
+// out of B frames takes about m = (W / B)^(1/4) and the eight teams end after
+// max(1, m groups / 8) + m / 2 (1 where each has one group).  Measured (ms, launches / team, waterfall):
+// 64 frames of N = 65536 6.3 / 3.7 (W = 4; 2: 4.1, 8: 4.3), 250 of 16384 5.1 /
+// 3.0 (W = 8), 16 of 16001 at rate 0.02 4.5 / 1.5 (W = 1), 100 of 30000 6.0 / 4.8
+// (W = 4), 64 of 262144 with 8-bit messages 21.7 / 18.7.  Where every frame runs
+// its whole budget that advantage is gone, so a team may cost at most a fifth
+// more per iteration.  States that leave the Infinity Cache are not for teams:
+// 64 frames of N = 10^6 take 87 ms in groups of 8, 49 ms in launches.
+int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, bool early, size_t ws_bytes) {
+  const double E = 1e-6 * (double)c->E12;
+  const int plain_w = choose_interleave(B);
+  const double plain = 3.4 * (double)(c->classes.size() + 1) +
+                       (c2v_bytes == sizeof(float) ? 2.6 : 2.1) * E * ((B + plain_w - 1) / plain_w) * plain_w;
+  int best = 0;
+  double best_t = plain;
+  for (int W : {16, 8, 4, 2, 1}) {
+    if (c2v_bytes != sizeof(float) && W < 4) continue;
+    const int G = (B + W - 1) / W, rounds = (G + kTeamSlots - 1) / kTeamSlots;
+    const size_t slot = team_slot(c, W, post, c2v_bytes, nullptr), all = slot * std::min(G, kTeamSlots);
+    if (slot >= kMaxSlotBytes || team_control_bytes() + all > ws_bytes || all > kMaxTeamBytes) continue;
+    const double it = (4.5 + (c2v_bytes == 1 ? 20 + 16 * W : 32 + 17.5 * W) * E) * (slot > (8u << 20) ? 1.15 : 1.0);
+    if (rounds * it > 1.2 * plain) continue;
+    const double m = std::min(1.0, std::pow((double)W / B, 0.25));
+    const double t = early && rounds > 1 ? it * (std::max(1.0, m * G / kTeamSlots) + 0.5 * m) : rounds * it;
+    if (t < best_t) {
+      best = W;
+      best_t = t;
+    }
+  }
+  return best;
+}
+
+int team_decode(const met_code *c, const DeviceCode *d, int W, const float *llr, const uint8_t *syn, int B,
+                int max_iter, uint32_t flags, uint8_t *bits, int32_t *iters, uint8_t *conv, float *post,
+                char *ws, hipStream_t st) {
+  const size_t cb = (flags & MET_C2V_Q8) ? 1 : (flags & MET_C2V_FP16) ? 2 : 4;
+  TeamJob job{};
+  job.edge_msgvn = d->edge_msgvn;
+  job.vn_ptr = d->vn_ptr;
+  job.vn_edges = d->vn_edges_plane;
+  job.msg_vn_user = d->msg_vn_user;
+  job.leaf_vn = d->leaf_vn;
+  job.vn_slot = d->vn_slot;
+  job.chk_msg_ptr = d->chk_msg_ptr;
+  job.chk_leaf_ptr = d->chk_leaf_ptr;
+  job.chk_pos = d->chk_pos;
+  job.N = c->N;
+  job.M = (int32_t)c->M;
+  job.N2 = (int32_t)c->N2;
+  job.EL = (int32_t)c->EL;
+  job.llr = llr;
+  job.syn = syn;
+  job.bits = bits;
+  job.iters = iters;
+  job.converged = conv;
+  job.posterior = post;
+  job.ws = ws;
+  job.B = B;
+  job.G = (B + W - 1) / W;
+  job.max_iter = max_iter;
+  job.early = !(flags & MET_FIXED_ITERS);
+  job.n_slots = std::min(job.G, kTeamSlots);
+  job.off_slots = team_control_bytes();
+  job.lanes_per_vn = lanes_per_vn(c, W);
+  team_slot(c, W, post != nullptr, cb, &job);
+  int32_t tiles = 0;
+  for (const CheckClass &k : c->classes) {
+    TeamClass &t = job.cls[job.n_classes++];
+    t.shape = k.shape;
+    t.tile0 = tiles;
+    t.first_check = (int32_t)k.first_check;
+    t.n_checks = (int32_t)k.n_checks;
+    t.first_msg = (int32_t)k.first_msg;
+    t.first_leaf = (int32_t)k.first_leaf;
+    const bool wide = k.shape != kShapeGeneric && kShapeMsg[k.shape] > 4;
+    const int per = 64 / (wide ? W : W / std::min(W, 4));  // checks per wave, as check_tile
+    tiles += (int32_t)((k.n_checks + per - 1) / per);
+  }
+  job.check_tiles = tiles;
+  int dev = 0, cus = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  job.expected = std::max(1, std::min(cus / kXcds, kMaxTeam));
+  hipLaunchKernelGGL(k_team_clear, dim3(1), dim3(kBlock), 0, st, reinterpret_cast<uint32_t *>(ws));
+  {
+    ScopedTimer t(st, "k_team");
+    const unsigned grid = (unsigned)cus;
+    if (flags & MET_C2V_FP16) {
+      launch_reduced<half_t>(W, job, grid, st);
+    } else if (flags & MET_CHECK_LUT) {
+      launch_reduced<q8lut_t>(W, job, grid, st);
+    } else if (flags & MET_C2V_Q8) {
+      launch_reduced<q8_t>(W, job, grid, st);
+    } else {
+      switch (W) {
+        case 1: launch_team<1, float>(job, grid, st); break;
+        case 2: launch_team<2, float>(job, grid, st); break;
+        case 4: launch_team<4, float>(job, grid, st); break;
+        case 8: launch_team<8, float>(job, grid, st); break;
+        default: launch_team<16, float>(job, grid, st);
+      }
+    }
+  }
+  HIP_TRY(hipGetLastError());
+  return MET_OK;
+}
+
+}  // namespace met
