@@ -210,6 +210,15 @@ void met_code_free(met_code *c);
  * Errors: MET_EINVAL (NULL pointer, B < 1), MET_EHIP. */
 int met_syndrome(const met_code *c, const uint8_t *bits, int32_t B, uint8_t *syn, void *stream);
 
+/* The same with room for the frames' bits packed into words (workspace: dev,
+ * 8-byte aligned, at least met_syndrome_workspace_bytes(), contents need not be
+ * initialised), which gathers every edge once for up to 64 frames; a NULL
+ * workspace gives met_syndrome.  The results are the same.
+ * Errors: MET_EINVAL, MET_EHIP. */
+int met_syndrome_workspace_bytes(const met_code *c, int32_t B, size_t *bytes);
+int met_syndrome_ex(const met_code *c, const uint8_t *bits, int32_t B, uint8_t *syn, void *workspace, size_t ws_bytes,
+                    void *stream);
+
 /* ---- Multidimensional reconciliation (the decoder's front end) ----------
  * Results, "Information reconciliation for CV-QKD system", and Methods Step 1:
  * the correlated Gaussian raw keys of Alice (x) and Bob (y = x + z, noise

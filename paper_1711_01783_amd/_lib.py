@@ -114,6 +114,8 @@ def _load():
         "met_code_classes": (ctypes.c_int, [P, ctypes.POINTER(met_check_class), i32, ctypes.POINTER(i32)]),
         "met_code_free": (None, [P]),
         "met_syndrome": (ctypes.c_int, [P, P, i32, P, P]),
+        "met_syndrome_workspace_bytes": (ctypes.c_int, [P, i32, ctypes.POINTER(sz)]),
+        "met_syndrome_ex": (ctypes.c_int, [P, P, i32, P, P, sz, P]),
         "met_decode_workspace_bytes": (ctypes.c_int, [P, i32, u32, i32, ctypes.POINTER(sz)]),
         "met_decode": (ctypes.c_int, [P, P, P, i32, i32, u32, P, P, P, P, P, sz, P]),
         "met_mdr_bob": (ctypes.c_int, [P, P, i64, i64, i32, P, P, P]),

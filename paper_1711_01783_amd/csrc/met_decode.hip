@@ -520,20 +520,6 @@ extern "C" void met_code_free(met_code *c) {
   delete c;
 }
 
-extern "C" int met_syndrome(const met_code *c, const uint8_t *bits, int32_t B, uint8_t *syn, void *stream) { return met::guarded("met_syndrome", [&]() -> int {
-  met::clear_error();
-  if (!c || !bits || !syn) return fail(MET_EINVAL, "met_syndrome: NULL argument");
-  if (B < 1 || B > 65535) return fail(MET_EINVAL, "met_syndrome: B = %d outside 1..65535", B);
-  const met::DeviceCode *d = nullptr;
-  int rc = met::device_code(c, &d);
-  if (rc) return rc;
-  hipLaunchKernelGGL(met::k_syndrome, dim3((unsigned)((c->M + met::kBlock - 1) / met::kBlock), B),
-                     dim3(met::kBlock), 0, (hipStream_t)stream, d->all_vn, d->all_ptr, c->N, c->M, bits, syn);
-  HIP_TRY(hipGetLastError());
-  return MET_OK;
-  });
-}
-
 static int validate_decode(const met_code *c, int32_t B, uint32_t flags) {
   if (!c) return fail(MET_EINVAL, "NULL code");
   if (B < 1 || B > 65535) return fail(MET_EINVAL, "B = %d outside 1..65535", B);

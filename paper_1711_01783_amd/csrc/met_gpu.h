@@ -1005,16 +1005,6 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const FinalParams p) {
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_syndrome(const int32_t *all_vn, const int32_t *all_ptr, int64_t N,
-                                                     int64_t M, const uint8_t *bits, uint8_t *syn) {
-  const int f = blockIdx.y;
-  const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (j >= M) return;
-  uint32_t s = 0;
-  for (int32_t e = all_ptr[j]; e < all_ptr[j + 1]; ++e) s ^= bits[(int64_t)f * N + all_vn[e]] & 1u;
-  syn[(int64_t)f * M + j] = (uint8_t)s;
-}
-
 // ----------------------------------------------------------------------------
 // Host launch helpers
 
