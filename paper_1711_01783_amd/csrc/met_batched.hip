@@ -196,7 +196,7 @@ __device__ __forceinline__ void check_tile(CJob *jobs, int j, int l, int64_t t) 
   uint64_t *B1 = jobs[j].B1, *unsat = jobs[j].unsat;
   const int32_t G = jobs[j].G;
   p.it = l;
-  p.flags = jobs[j].early && l >= 2 ? F_TEST : 0;
+  p.flags = (jobs[j].early && l >= 2 ? F_TEST : 0) | (jobs[j].early || l == jobs[j].max_iter ? F_DECIDE : 0);
   p.Pin = l == 1 ? jobs[j].L2 : jobs[j].P;
   p.B1in = B1 + (size_t)((l - 1) & 1) * lw;
   p.B1out = B1 + (size_t)(l & 1) * lw;
@@ -942,7 +942,7 @@ struct Batched {
     const int l = (ph - b.offset) / 2 + 1;
     CheckParams p = b.cp;
     p.it = l;
-    p.flags = b.early && l >= 2 ? F_TEST : 0;
+    p.flags = (b.early && l >= 2 ? F_TEST : 0) | (b.early || l == b.max_iter ? F_DECIDE : 0);
     p.Pin = l == 1 ? b.L2 : b.P;
     p.B1in = b.B1 + (size_t)((l - 1) & 1) * b.leaf_words;
     p.B1out = b.B1 + (size_t)(l & 1) * b.leaf_words;

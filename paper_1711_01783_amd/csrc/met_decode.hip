@@ -323,7 +323,7 @@ struct Decoder {
     fp.posterior = post;
     fp.slot_frame = slot_frame;
     fp.G = G;
-    const int base_flags = (post ? F_POST : 0) | (weights ? F_WEIGHTED : 0);
+    const int base_flags = weights ? F_WEIGHTED : 0;
     // Early stop of the launch sequence: in early-exit mode the host reads
     // whether any frame still runs after iterations 4, 8, 16, ... (a stream
     // synchronisation each, so a doubling schedule); once none does, the
@@ -341,13 +341,15 @@ struct Decoder {
 
     for (int it = 1; it <= max_iter; ++it) {
       cp.it = it;
-      cp.flags = base_flags | (it == 1 ? F_FIRST : 0) | (early && it >= 2 ? F_TEST : 0);
+      const bool decide = early || it == max_iter;
+      cp.flags = base_flags | (it == 1 ? F_FIRST : 0) | (early && it >= 2 ? F_TEST : 0) | (decide ? F_DECIDE : 0) |
+                 (decide && post ? F_POST : 0);
       cp.Pin = it == 1 ? L2 : P;
       cp.B1in = B1 + (size_t)((it - 1) & 1) * leaf_words;
       cp.B1out = B1 + (size_t)(it & 1) * leaf_words;
       cp.P1 = P1 ? P1 + (size_t)(it & 1) * leaf_floats : nullptr;
       cp.unsat = unsat + (size_t)((it - 1) & 1) * G;
-      const int mode = special ? M_SPECIAL : (it == 1 ? M_FIRST : M_MAIN);
+      const int mode = (weights || (cp.flags & F_POST)) ? M_SPECIAL : (it == 1 ? M_FIRST : M_MAIN);
       for (size_t k = 0; k < classes.size(); ++k) {
         cp.unsat_clear = k == 0 ? unsat + (size_t)(it & 1) * G : nullptr;
         ScopedTimer t(st, kCheckKernelName[classes[k].shape]);

@@ -270,6 +270,7 @@ enum : int32_t {
   F_TEST = 2,      // evaluate the syndrome test of the previous iteration
   F_POST = 4,      // store leaf posteriors
   F_WEIGHTED = 8,  // scale c2v by a per-(edge type, iteration) weight
+  F_DECIDE = 16,   // store leaf decisions (tested by the next iteration, or final)
 };
 
 // Compile-time modes of the fixed-shape check kernel.
@@ -507,6 +508,7 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
   const bool test = MODE != M_FIRST && (p.flags & F_TEST);
   const bool post = MODE == M_SPECIAL && (p.flags & F_POST);
   const bool weighted = MODE == M_SPECIAL && (p.flags & F_WEIGHTED);
+  const bool decide = p.flags & F_DECIDE;
   const int64_t base = (bx * kWavesPerBlock + wv) * IPW * IPWAVE;
   if (W == 64 && base >= c.n_checks) return;
 
@@ -591,6 +593,9 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
         if (store) st_c2v<W, CT>(p.c2v, ((int64_t)g * p.E12 + m0 + m) * W + w, out);
       }
     }
+    // Leaf decisions (and posteriors) only where somebody reads them: every
+    // iteration with early exit, the last one otherwise.
+    if (!decide) continue;
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
       const int64_t le = l0 + l;
@@ -692,7 +697,7 @@ __device__ __forceinline__ void check_generic_body(const CheckParams &p, const C
   }
   // Leaf decisions: ballots must be executed by every lane of the wave, so the
   // loop runs to the wave-wide maximum leaf count.
-  int nl_max = valid ? nl : 0;
+  int nl_max = valid && (p.flags & F_DECIDE) ? nl : 0;
   for (int off = 32; off >= 1; off >>= 1) nl_max = max(nl_max, __shfl_xor(nl_max, off));
   for (int k = 0; k < nl_max; ++k) {
     const bool has = valid && k < nl;

@@ -467,7 +467,7 @@ struct Wbp {
     cp.weights = weights;
     cp.wstride = pl.L;
     cp.it = l;
-    cp.flags = F_WEIGHTED | (l == 1 ? F_FIRST : 0) | (post ? F_POST : 0);
+    cp.flags = F_WEIGHTED | (l == 1 ? F_FIRST : 0) | (post ? F_POST | F_DECIDE : 0);
     cp.G = b.G;
     const std::vector<ClassArgs> classes = class_args(c);
     for (const ClassArgs &a : classes) {
