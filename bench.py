@@ -561,6 +561,10 @@ def run_single(args, cpu) -> dict:
     dom = max(classes, key=lambda c: c["n_checks"] * (c["n_msg"] + c["n_leaf"]))
     kname = "k_check<%d,%d>" % (dom["n_msg"], dom["n_leaf"])
     wl = "%s N=%d B=%d snr=%g max_iter=%d %s" % (prof, n, B, snr, max_iter, "early-exit" if early else "fixed")
+    kbytes = cls[kname]
+    if kname not in kt:  # one launch for all check classes, or for the whole decode
+        kname = "k_team" if "k_team" in kt else "k_check_set"
+        kbytes = sum(cls.values()) + (var if kname == "k_team" else 0.0)
     kl, kms = kt.get(kname, (0, 0.0))
     rec = {
         "value": round(value, 3),
@@ -573,7 +577,7 @@ def run_single(args, cpu) -> dict:
             "profile": prof, "N": n, "frames": B, "snr": snr, "max_iter": max_iter, "mode": "plain",
             "interleave": W, "code_seed": CODE_SEED[prof], "frame_seed": FRAME_SEED,
         },
-        "roofline": roofline(kname, cls[kname] * args.steps, kl, kms, measured_traffic(kname, wl)),
+        "roofline": roofline(kname, kbytes * args.steps, kl, kms, measured_traffic(kname, wl)),
         "kernels_us": {k: {"launches": v[0], "avg_us": round(1e3 * v[1] / max(1, v[0]), 2)} for k, v in kt.items()},
     }
     rec.update(fer_summary(out, bits))

@@ -350,11 +350,8 @@ struct Decoder {
       cp.P1 = P1 ? P1 + (size_t)(it & 1) * leaf_floats : nullptr;
       cp.unsat = unsat + (size_t)((it - 1) & 1) * G;
       const int mode = (weights || (cp.flags & F_POST)) ? M_SPECIAL : (it == 1 ? M_FIRST : M_MAIN);
-      for (size_t k = 0; k < classes.size(); ++k) {
-        cp.unsat_clear = k == 0 ? unsat + (size_t)(it & 1) * G : nullptr;
-        ScopedTimer t(st, kCheckKernelName[classes[k].shape]);
-        launch_check<W, CT>(cp, classes[k], mode, cn_ipw, G, st);
-      }
+      cp.unsat_clear = unsat + (size_t)(it & 1) * G;
+      launch_checks<W, CT>(cp, classes, mode, cn_ipw, G, st);
       vp.it = it;
       vp.retire = early && it >= 2;
       vp.unsat = unsat + (size_t)((it - 1) & 1) * G;

@@ -317,9 +317,10 @@ struct GridTile {
   int64_t bx;
   int g;
 };
-__device__ __forceinline__ GridTile xcd_grid_tile() {
-  const int64_t nx = gridDim.x, bx = blockIdx.x;
-  const int s = (int)(((int64_t)blockIdx.y * nx) % kXcds);  // XCD of the group's first block
+__device__ __forceinline__ GridTile xcd_grid_tile(int64_t skip = 0) {
+  // (the tiles after the first `skip` blocks of a group)
+  const int64_t nx = gridDim.x - skip, bx = blockIdx.x - skip;
+  const int s = (int)(((int64_t)blockIdx.y * gridDim.x + skip) % kXcds);  // XCD of the group's first tile
   const int x = (int)((s + bx) % kXcds);
   int64_t first = 0;  // tiles of the XCDs before x
   for (int y = 0; y < x; ++y) {
@@ -744,6 +745,42 @@ __global__ __launch_bounds__(kBlock) void k_check_generic(const CheckParams p, c
   check_generic_body<W, false, CT>(p, c, t.bx, t.g);
 }
 
+// All check classes of a compiled shape in one launch.  Classes with few checks
+// last as long as one tile's chain of loads and phis however few they are
+// (N = 65536, 64 frames: 2 checks of degree 11 8.3 us, 1311 of degree 12 11.4 us,
+// 25 of (2,1) 4.6 us, next to 28.4 us for the (3,1) class), so one after the
+// other they cost as much as the main class; here their blocks come first and
+// the main class (the last one) fills the machine around them.
+struct ClassSet {
+  int32_t n, lead_block;  // classes; first block of the last class, a multiple of 8
+  int32_t block0[kMaxClasses];
+  ClassArgs c[kMaxClasses];
+};
+
+template <int W, int MODE, int IPW, typename CT = float>
+__global__ __launch_bounds__(kBlock) void k_check_set(const CheckParams p, const ClassSet set) {
+  if ((int)blockIdx.x >= set.lead_block) {
+    const GridTile t = MODE == M_SPECIAL ? GridTile{(int64_t)blockIdx.x - set.lead_block, (int)blockIdx.y}
+                                         : xcd_grid_tile(set.lead_block);
+    check_fixed_body<W, 3, 1, MODE, IPW, false, CT>(p, set.c[set.n - 1], t.bx, t.g);
+    return;
+  }
+  int k = 0;
+  while (k + 2 < set.n && (int)blockIdx.x >= set.block0[k + 1]) ++k;
+  const ClassArgs &c = set.c[k];
+  const int64_t bx = (int64_t)blockIdx.x - set.block0[k];
+  const int g = (int)blockIdx.y;
+  switch (c.shape) {
+    case 0: check_fixed_body<W, 3, 1, MODE, 1, false, CT>(p, c, bx, g); break;
+    case 1: check_fixed_body<W, 2, 1, MODE, 1, false, CT>(p, c, bx, g); break;
+    case 2: check_fixed_body<W, 12, 0, MODE, 1, false, CT>(p, c, bx, g); break;
+    case 3: check_fixed_body<W, 11, 0, MODE, 1, false, CT>(p, c, bx, g); break;
+    case 4: check_fixed_body<W, 6, 0, MODE, 1, false, CT>(p, c, bx, g); break;
+    case 5: check_fixed_body<W, 5, 0, MODE, 1, false, CT>(p, c, bx, g); break;
+    default: check_fixed_body<W, 4, 0, MODE, 1, false, CT>(p, c, bx, g); break;
+  }
+}
+
 // Syndrome test only (after the last iteration): parity of the hard decisions
 // of P^l (message VNs) and of the stored leaf decisions against s.
 struct TestParams {
@@ -1131,6 +1168,12 @@ void launch_check(const CheckParams &p, const ClassArgs &a, int mode, int cn_ipw
     launch_fixed_ipw<W, M_MAIN>(ipw, a.shape, blocks, G, st, p, a);
 }
 
+// One check update of every class: the compiled shapes in one launch when the
+// largest of them is a (3,1) class, else a launch per class.
+template <int W, typename CT = float>
+void launch_checks(const CheckParams &p, const std::vector<ClassArgs> &classes, int mode, int cn_ipw, int G,
+                   hipStream_t st, const char *name = nullptr);
+
 inline std::vector<ClassArgs> class_args(const met_code *c) {
   std::vector<ClassArgs> out;
   for (const CheckClass &cc : c->classes) {
@@ -1151,6 +1194,65 @@ inline std::vector<ClassArgs> class_args(const met_code *c) {
 const char *const kCheckKernelName[kNumFixedShapes + 1] = {
     "k_check<3,1>", "k_check<2,1>", "k_check<12,0>", "k_check<11,0>", "k_check<6,0>", "k_check<5,0>",
     "k_check<4,0>", "k_check_generic"};
+template <int W, typename CT>
+void launch_checks(const CheckParams &p, const std::vector<ClassArgs> &classes, int mode, int cn_ipw, int G,
+                   hipStream_t st, const char *name) {
+  constexpr bool half = !std::is_same<CT, float>::value;
+  const int ipw = W == 64 ? (half ? 4 : cn_ipw) : 1;
+  const ClassArgs *lead = nullptr;
+  int n_fixed = 0;
+  for (const ClassArgs &a : classes)
+    if (a.shape != kShapeGeneric) {
+      ++n_fixed;
+      if (!lead || a.n_checks > lead->n_checks) lead = &a;
+    }
+  // Where the main class alone fills the GPU for much longer than the small ones
+  // last, the launches of their own are as fast or faster (their blocks keep
+  // their own register budget): 64 frames of N = 10^6 48.3 ms against 49.3
+  // merged, 128 of 2^18 28.3 against 28.2; below, merging gains: 64 frames of
+  // 2^18, 12 iterations 1.99 to 1.75 ms, 16 of 2^18 5.97 to 5.29, the training
+  // step at 32 of 2^18 17.4 to 16.2, at 64 of 100001 2.76 to 2.45.  Not with 1
+  // or 4 frames per item (1 of N = 10^6: 0.80 against 0.98 ms merged) nor with
+  // 8-bit messages (64 of 400001: 20.8 against 21.1).
+  const bool merged = n_fixed > 1 && lead->shape == 0 && W >= 16 && !std::is_class<CT>::value &&
+                      lead->n_checks * W * G <= 25000000;
+  CheckParams q = p;
+  if constexpr (W >= 16 && !std::is_class<CT>::value) if (merged) {
+    ClassSet set{};
+    int64_t blocks = 0;
+    for (const ClassArgs &a : classes) {
+      if (a.shape == kShapeGeneric || &a == lead) continue;
+      set.block0[set.n] = (int32_t)blocks;
+      set.c[set.n++] = a;
+      const int64_t per = kWavesPerBlock * (64 / W);
+      blocks += (a.n_checks + per - 1) / per;
+    }
+    blocks = (blocks + kXcds - 1) / kXcds * kXcds;
+    set.lead_block = (int32_t)blocks;
+    set.block0[set.n] = (int32_t)blocks;
+    set.c[set.n++] = *lead;
+    const int64_t per = (int64_t)kWavesPerBlock * ipw * (64 / W);
+    const unsigned nb = (unsigned)(blocks + (lead->n_checks + per - 1) / per);
+    ScopedTimer t(st, name ? name : "k_check_set");
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(nb, G), dim3(kBlock), 0, st, q, set); };
+    constexpr int i4 = W == 64 ? 4 : 1, i2 = W == 64 && !half ? 2 : i4, i1 = half ? i4 : 1;
+    // (reduced storage is compiled with 4 steps per wave only)
+    if (mode == M_SPECIAL)
+      ipw == 4 ? go(k_check_set<W, M_SPECIAL, i4, CT>) : ipw == 2 ? go(k_check_set<W, M_SPECIAL, i2, CT>) : go(k_check_set<W, M_SPECIAL, i1, CT>);
+    else if (mode == M_FIRST)
+      ipw == 4 ? go(k_check_set<W, M_FIRST, i4, CT>) : ipw == 2 ? go(k_check_set<W, M_FIRST, i2, CT>) : go(k_check_set<W, M_FIRST, i1, CT>);
+    else
+      ipw == 4 ? go(k_check_set<W, M_MAIN, i4, CT>) : ipw == 2 ? go(k_check_set<W, M_MAIN, i2, CT>) : go(k_check_set<W, M_MAIN, i1, CT>);
+    q.unsat_clear = nullptr;  // cleared by the set's first blocks
+  }
+  for (const ClassArgs &a : classes) {
+    if (merged && a.shape != kShapeGeneric) continue;
+    ScopedTimer t(st, name ? name : kCheckKernelName[a.shape]);
+    launch_check<W, CT>(q, a, mode, cn_ipw, G, st);
+    q.unsat_clear = nullptr;
+  }
+}
+
 static_assert(kShapeMsg[0] == 3 && kShapeLeaf[0] == 1 && kShapeMsg[2] == 12 && kShapeMsg[5] == 5 &&
                   kShapeMsg[6] == 4 && kNumFixedShapes == 7,
               "timer names and kernel switches follow the shape table");

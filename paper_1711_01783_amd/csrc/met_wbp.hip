@@ -470,10 +470,7 @@ struct Wbp {
     cp.flags = F_WEIGHTED | (l == 1 ? F_FIRST : 0) | (post ? F_POST | F_DECIDE : 0);
     cp.G = b.G;
     const std::vector<ClassArgs> classes = class_args(c);
-    for (const ClassArgs &a : classes) {
-      ScopedTimer t(st, "k_check_weighted");
-      launch_check<W>(cp, a, M_SPECIAL, 4, b.G, st);
-    }
+    launch_checks<W>(cp, classes, M_SPECIAL, 4, b.G, st, "k_check_weighted");
     VarParams vp{};
     vp.vn_ptr = d->vn_ptr;
     vp.vn_edges = d->vn_edges;

@@ -157,3 +157,29 @@ def test_large_decodes_keep_the_launches():
     bits, llr = make_frames(300000, 64, 0.3, 9)
     syn = met.syndrome(code, torch.from_numpy(bits).to(DEV))
     _compare(code, torch.from_numpy(llr).to(DEV), syn, 12, team=False)
+
+
+@pytest.mark.parametrize("n,b,kw", [(200003, 16, dict()), (150001, 32, dict(posterior=True, fixed_iters=True)),
+                                    (140003, 65, dict()), (150001, 64, dict(c2v_fp16=True, fixed_iters=True))])
+def test_all_classes_in_one_launch(n, b, kw):
+    """Four check classes (degrees 11, 12, 2+1 and 3+1) in one launch against the
+    same classes in the batched decoder's launches, or, where that has no such
+    option, against the class kernels' other step counts: equal bit for bit."""
+    code = met.Code.build(PROFILES["r0.05"], n, 21)
+    assert len(code.classes()) >= 3
+    bits, llr = make_frames(n, b, 0.115, 40)
+    d_llr, syn = torch.from_numpy(llr).to(DEV), met.syndrome(code, torch.from_numpy(bits).to(DEV))
+    print("check set", n, b, kw, flush=True)
+    got, used = _kernels(lambda: met.decode(code, d_llr, syn, 14, compact=False, **kw))
+    assert "k_check_set" in used and "k_check<3,1>" not in used
+    if kw.get("c2v_fp16"):  # the same frames with 25 others: past the size of one launch per update
+        more_bits, more = make_frames(n, 192, 0.115, 41)
+        more[:b] = llr
+        syn2 = torch.cat([syn, met.syndrome(code, torch.from_numpy(more_bits[b:]).to(DEV))])
+        ref, sep = _kernels(lambda: met.decode(code, torch.from_numpy(more).to(DEV), syn2, 14, compact=False, **kw))
+        assert "k_check<3,1>" in sep
+        assert torch.equal(ref.bits[:b], got.bits) and torch.equal(ref.converged[:b], got.converged)
+        return
+    ref = met.BatchedDecoder(phase_launches=True, stagger=False)([met.Job(code, d_llr, syn, 14, kw.get("fixed_iters", False))])[0]
+    for k in ("bits", "iterations", "converged"):
+        assert torch.equal(getattr(ref, k), getattr(got, k)), k
