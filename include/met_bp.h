@@ -59,7 +59,10 @@ extern "C" {
                                few groups as hold them, when that frees at least
                                a quarter of the occupied groups; results are
                                identical either way; no compaction when
-                               posteriors are requested) */
+                               posteriors are requested), and without squeezing
+                               (by default, once no group holds more than 32
+                               or 16 running frames they move to the lowest
+                               lanes of their groups) */
 #define MET_C2V_FP16 8u     /* check-to-variable messages stored as IEEE half
                                (rounded to nearest; all arithmetic in float):
                                half the message bytes.  Groups of 64 frames

@@ -200,8 +200,8 @@ __device__ __forceinline__ void check_tile(CJob *jobs, int j, int l, int64_t t) 
   p.Pin = l == 1 ? jobs[j].L2 : jobs[j].P;
   p.B1in = B1 + (size_t)((l - 1) & 1) * lw;
   p.B1out = B1 + (size_t)(l & 1) * lw;
-  p.unsat = unsat + (size_t)((l - 1) & 1) * G;
-  p.unsat_clear = c == 0 ? unsat + (size_t)(l & 1) * G : nullptr;
+  p.unsat = unsat + (size_t)((l - 1) & 1) * G * kUnsatWords;
+  p.unsat_clear = c == 0 ? unsat + (size_t)(l & 1) * G * kUnsatWords : nullptr;
   const ClassArgs a = jobs[j].cls[c];
   constexpr int I2 = 1;  // degree-11/12 checks: one step (keeps the union of the shapes' registers small)
   const int gi = (int)g;
@@ -227,7 +227,7 @@ __device__ __forceinline__ void variable_tile(CJob *jobs, int j, int l, int64_t 
   const int32_t vb = jobs[j].vn_blocks;
   vp.it = l;
   vp.retire = jobs[j].early && l >= 2;
-  vp.unsat = jobs[j].unsat + (size_t)((l - 1) & 1) * jobs[j].G;
+  vp.unsat = jobs[j].unsat + (size_t)((l - 1) & 1) * jobs[j].G * kUnsatWords;
   int64_t g = 0, r = 0;
   split_tile(t, vb, jobs[j].G, &g, &r);
   variable_body<W, 16, PERSIST>(vp, r, (int)g);
@@ -877,7 +877,7 @@ struct Batched {
       tp.synw = reinterpret_cast<uint64_t *>(base + pl.off_synw);
       tp.B1 = B1 + (size_t)(jb.max_iter & 1) * leaf_words;
       tp.active = reinterpret_cast<uint64_t *>(base + pl.off_active);
-      tp.unsat = unsat + (size_t)(jb.max_iter & 1) * G;
+      tp.unsat = unsat + (size_t)(jb.max_iter & 1) * G * kUnsatWords;
       const int64_t per = (int64_t)kWavesPerBlock * (64 / kBatchW);
       hipLaunchKernelGGL(k_test<kBatchW>, dim3((unsigned)((c->M + per - 1) / per), G), dim3(kBlock), 0, st, tp);
       FinalParams fp{};
@@ -946,10 +946,10 @@ struct Batched {
     p.Pin = l == 1 ? b.L2 : b.P;
     p.B1in = b.B1 + (size_t)((l - 1) & 1) * b.leaf_words;
     p.B1out = b.B1 + (size_t)(l & 1) * b.leaf_words;
-    p.unsat = b.unsat + (size_t)((l - 1) & 1) * b.G;
+    p.unsat = b.unsat + (size_t)((l - 1) & 1) * b.G * kUnsatWords;
     for (int c = 0; c < b.n_classes; ++c) {
       if (b.cls_wide[c]) continue;
-      p.unsat_clear = c == 0 ? b.unsat + (size_t)(l & 1) * b.G : nullptr;
+      p.unsat_clear = c == 0 ? b.unsat + (size_t)(l & 1) * b.G * kUnsatWords : nullptr;
       ScopedTimer t(hs, phase_timer_name(1));
       launch_check<kBatchW, float>(p, b.cls[c], M_MAIN, ipw_narrow, b.G, hs);
     }

@@ -35,6 +35,10 @@
 // frame).  Per-item bit words (syndrome, leaf decisions, flags) hold the W
 // frames of a group in one uint64.
 //
+// Squeezing (early exit, groups of 64 frames, not while captured): once no group
+// holds more than 32 (16) running frames they move to the lowest lanes of their
+// rows, and the launches read half (a quarter) of each row from then on.
+//
 // Compaction (early exit, groups of 64 frames): every few iterations, frames
 // that stopped have their outputs written and their lanes freed; when the
 // frames still running would fill markedly fewer groups than they occupy, they
@@ -55,12 +59,66 @@ constexpr int kCompactEvery = 4;    // iterations between compaction points
 constexpr int kCompactMinLeft = 4;  // no compaction this close to the budget
 constexpr int kMaxGroups = 1024;    // 65535 frames in groups of 64
 
-// flag = 1 if any frame of any group still runs (one block).
-__global__ __launch_bounds__(kBlock) void k_any_active(const uint64_t *active, int G, uint32_t *flag) {
-  uint64_t any = 0;
-  for (int g = threadIdx.x; g < G; g += kBlock) any |= active[g];
-  const int r = __syncthreads_or(any != 0ull);
-  if (threadIdx.x == 0) *flag = (uint32_t)r;
+// flag = the largest number of frames of one group that still run (one block).
+__global__ __launch_bounds__(kBlock) void k_most_active(const uint64_t *active, int G, uint32_t *flag) {
+  __shared__ uint32_t most;
+  if (threadIdx.x == 0) most = 0;
+  __syncthreads();
+  uint32_t n = 0;
+  for (int g = threadIdx.x; g < G; g += kBlock) n = max(n, (uint32_t)__popcll(active[g]));
+  if (n) atomicMax(&most, n);
+  __syncthreads();
+  if (threadIdx.x == 0) *flag = most;
+}
+
+// Squeezing: once no group of 64 holds more than 32 (or 16) running frames,
+// they move to the lowest lanes of their rows, and later launches read and
+// compute those lanes only: two or four items per wave, half or a quarter of
+// each row's bytes (a row keeps its place, so that it is moved in place by the
+// wave that reads it).  src[g 64 + k]: the lane whose frame goes to lane k, -1
+// none.
+__global__ __launch_bounds__(kBlock) void k_squeeze_plan(uint64_t *active, int32_t *slot_frame, int32_t *src, int G) {
+  for (int g = blockIdx.x * kBlock + threadIdx.x; g < G; g += gridDim.x * kBlock) {
+    uint64_t a = active[g];
+    int n = 0;
+    for (; a; a &= a - 1) {
+      const int w = __ffsll((unsigned long long)a) - 1;  // ascending, so n <= w
+      src[g * 64 + n] = w;
+      slot_frame[g * 64 + n] = slot_frame[g * 64 + w];
+      ++n;
+    }
+    active[g] = n == 64 ? ~0ull : (1ull << n) - 1ull;
+    for (; n < 64; ++n) {
+      src[g * 64 + n] = -1;
+      slot_frame[g * 64 + n] = -1;
+    }
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_squeeze_rows(const int32_t *src, T *arr, int64_t items) {
+  const int g = blockIdx.y, lane = threadIdx.x & 63;
+  const int from = src[g * 64 + lane];
+  if (!__syncthreads_or(from >= 0)) return;
+  for (int64_t i = (int64_t)blockIdx.x * kWavesPerBlock + wave_id(); i < items;
+       i += (int64_t)gridDim.x * kWavesPerBlock) {
+    T *row = arr + ((int64_t)g * items + i) * 64;
+    if (from >= 0) {
+      const T v = row[from];
+      row[lane] = v;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kBlock) void k_squeeze_bits(const int32_t *src, uint64_t *arr, int64_t items) {
+  const int g = blockIdx.y;
+  if (src[g * 64] < 0) return;
+  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < items; i += (int64_t)gridDim.x * kBlock) {
+    const uint64_t word = arr[(int64_t)g * items + i];
+    uint64_t out = 0;
+    for (int k = 0; k < 32 && src[g * 64 + k] >= 0; ++k) out |= ((word >> src[g * 64 + k]) & 1ull) << k;
+    arr[(int64_t)g * items + i] = out;
+  }
 }
 
 struct CompactView {
@@ -207,6 +265,45 @@ struct Decoder {
   template <typename T>
   T *at(size_t off) const { return reinterpret_cast<T *>(ws + off); }
 
+  // One iteration: check update of every class, variable update.
+  template <int W, int RS, typename CT>
+  void step(const CheckParams &cp, const VarParams &vp, const std::vector<ClassArgs> &classes, int mode) {
+    launch_checks<W, CT, RS>(cp, classes, mode, cn_ipw, pl.G, st);
+    const int64_t per = (int64_t)kWavesPerBlock * (64 / W);
+    if (c->N2 == 0) return;
+    ScopedTimer t(st, "k_variable");
+    const dim3 grid((unsigned)((c->N2 + per - 1) / per), pl.G);
+    if (RS != W || vn_chunk == 16)
+      hipLaunchKernelGGL((k_variable<W, 16, CT, RS>), grid, dim3(kBlock), 0, st, vp);
+    else if (vn_chunk == 32)
+      hipLaunchKernelGGL((k_variable<W, (RS == W ? 32 : 16), CT, RS>), grid, dim3(kBlock), 0, st, vp);
+    else
+      hipLaunchKernelGGL((k_variable<W, (RS == W ? 8 : 16), CT, RS>), grid, dim3(kBlock), 0, st, vp);
+  }
+
+  void finalize(const FinalParams &fp, int width, int G) {
+    const dim3 grid((unsigned)((c->N + 63) / 64), G);
+    if (width == 64)
+      hipLaunchKernelGGL((k_finalize<64, 64>), grid, dim3(kBlock), 0, st, fp);
+    else if (width == 32)
+      hipLaunchKernelGGL((k_finalize<32, 64>), grid, dim3(kBlock), 0, st, fp);
+    else
+      hipLaunchKernelGGL((k_finalize<16, 64>), grid, dim3(kBlock), 0, st, fp);
+  }
+
+  // Final test, outcomes and outputs.
+  template <int W, int RS>
+  void finish(const TestParams &tp, const FinalParams &fp, int G) {
+    const int64_t per = (int64_t)kWavesPerBlock * (64 / W);
+    {
+      ScopedTimer t(st, "k_test");
+      hipLaunchKernelGGL((k_test<W, RS>), dim3((unsigned)((c->M + per - 1) / per), G), dim3(kBlock), 0, st, tp);
+    }
+    ScopedTimer t(st, "k_finalize");
+    hipLaunchKernelGGL((k_final_status<W, RS>), dim3((B + kBlock - 1) / kBlock), dim3(kBlock), 0, st, fp);
+    hipLaunchKernelGGL((k_finalize<W, RS>), dim3((unsigned)((c->N + 63) / 64), G), dim3(kBlock), 0, st, fp);
+  }
+
   // CT: storage type of the check-to-variable messages (float, or half_t for
   // MET_C2V_FP16; the arithmetic is float either way).
   template <int W, typename CT = float>
@@ -291,17 +388,23 @@ struct Decoder {
     vp.iters = iters;
     vp.converged = conv;
     vp.G = G;
-    const int64_t vn_per_block = (int64_t)kWavesPerBlock * (64 / W);
-    const unsigned vn_blocks = (unsigned)((c->N2 + vn_per_block - 1) / vn_per_block);
     const bool early = !(flags & MET_FIXED_ITERS);
     const bool special = post || weights;
     // (compaction moves float message rows: not with half-precision storage)
     const bool compact = W == 64 && G > 1 && early && !special && !(flags & MET_NO_COMPACT) &&
                          std::is_same<CT, float>::value;
-    int32_t *slot_frame = compact ? at<int32_t>(pl.off_slot) : nullptr;
+    // squeezing needs the host to see how many frames run
+    bool squeeze = false;
+    if constexpr (W == 64) {
+      hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+      if (early && !special && !(flags & MET_NO_COMPACT)) HIP_TRY(hipStreamIsCapturing(st, &cs));
+      squeeze = early && !special && !(flags & MET_NO_COMPACT) && cs == hipStreamCaptureStatusNone;
+    }
+    int width = W;  // lanes in use: 64, or 32 or 16 after squeezing
+    int32_t *slot_frame = compact || squeeze ? at<int32_t>(pl.off_slot) : nullptr;
     int32_t *ctab = at<int32_t>(pl.off_ctab);
     vp.slot_frame = slot_frame;
-    if (compact)
+    if (slot_frame)
       hipLaunchKernelGGL(k_init_slots, dim3((unsigned)((G * W + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
                          slot_frame, B, G * W);
     FinalParams fp{};
@@ -325,8 +428,8 @@ struct Decoder {
     fp.G = G;
     const int base_flags = weights ? F_WEIGHTED : 0;
     // Early stop of the launch sequence: in early-exit mode the host reads
-    // whether any frame still runs after iterations 4, 8, 16, ... (a stream
-    // synchronisation each, so a doubling schedule); once none does, the
+    // how many frames still run after iterations 4, 8, 12, 16, 20, 25, 31, ... (a
+    // stream synchronisation each, so a growing interval); once none does, the
     // remaining iterations would launch kernels with nothing to do, and the
     // final test and outputs follow at once.  Not while the stream is being
     // captured into a graph (no synchronisation is possible there).
@@ -348,24 +451,19 @@ struct Decoder {
       cp.B1in = B1 + (size_t)((it - 1) & 1) * leaf_words;
       cp.B1out = B1 + (size_t)(it & 1) * leaf_words;
       cp.P1 = P1 ? P1 + (size_t)(it & 1) * leaf_floats : nullptr;
-      cp.unsat = unsat + (size_t)((it - 1) & 1) * G;
+      cp.unsat = unsat + (size_t)((it - 1) & 1) * G * kUnsatWords;
       const int mode = (weights || (cp.flags & F_POST)) ? M_SPECIAL : (it == 1 ? M_FIRST : M_MAIN);
-      cp.unsat_clear = unsat + (size_t)(it & 1) * G;
-      launch_checks<W, CT>(cp, classes, mode, cn_ipw, G, st);
+      cp.unsat_clear = unsat + (size_t)(it & 1) * G * kUnsatWords;
       vp.it = it;
       vp.retire = early && it >= 2;
-      vp.unsat = unsat + (size_t)((it - 1) & 1) * G;
-      if (vn_blocks > 0) {
-        ScopedTimer t(st, "k_variable");
-        const dim3 grid(vn_blocks, G);
-        if (vn_chunk == 32)
-          hipLaunchKernelGGL((k_variable<W, 32, CT>), grid, dim3(kBlock), 0, st, vp);
-        else if (vn_chunk == 16)
-          hipLaunchKernelGGL((k_variable<W, 16, CT>), grid, dim3(kBlock), 0, st, vp);
-        else
-          hipLaunchKernelGGL((k_variable<W, 8, CT>), grid, dim3(kBlock), 0, st, vp);
-      }
-      if (compact && it % kCompactEvery == 0 && max_iter - it >= kCompactMinLeft) {
+      vp.unsat = unsat + (size_t)((it - 1) & 1) * G * kUnsatWords;
+      if (W == 64 && width == 32)
+        step<32, (W == 64 ? 64 : 32), CT>(cp, vp, classes, mode);
+      else if (W == 64 && width == 16)
+        step<16, (W == 64 ? 64 : 16), CT>(cp, vp, classes, mode);
+      else
+        step<W, W, CT>(cp, vp, classes, mode);
+      if (compact && width == W && it % kCompactEvery == 0 && max_iter - it >= kCompactMinLeft) {
         ScopedTimer t(st, "k_compact");
         // outputs of frames that stopped, then the plan, then the state the
         // next check update reads: P, c2v, L, leaf inputs, syndrome, and the
@@ -392,12 +490,45 @@ struct Decoder {
         move_bits(B1 + (size_t)(it & 1) * leaf_words, c->EL);
       }
       if (can_stop && it == next_check && it < max_iter) {
-        next_check *= 2;
-        hipLaunchKernelGGL(k_any_active, dim3(1), dim3(kBlock), 0, st, active, G, flag);
-        uint32_t any = 1;
-        HIP_TRY(hipMemcpyAsync(&any, flag, sizeof any, hipMemcpyDeviceToHost, st));
+        next_check = std::max(it + 4, it + it / 4);
+        hipLaunchKernelGGL(k_most_active, dim3(1), dim3(kBlock), 0, st, active, G, flag);
+        uint32_t most = 0;
+        HIP_TRY(hipMemcpyAsync(&most, flag, sizeof most, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
-        if (!any) break;  // every frame has stopped
+        if (!most) break;  // every frame has stopped
+        const int fit = most <= 16 ? 16 : most <= 32 ? 32 : 64;
+        if constexpr (W == 64) {
+          if (squeeze && fit < width && max_iter - it >= kCompactMinLeft) {
+            ScopedTimer t(st, "k_squeeze");
+            // outputs of frames that stopped, then the state the next check
+            // update reads, as in a compaction
+            FinalParams ff = fp;
+            ff.flush = 1;
+            finalize(ff, width, G);
+            hipLaunchKernelGGL(k_squeeze_plan, dim3((unsigned)((G + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, active,
+                               slot_frame, ctab, G);
+            auto rows = [&](auto *a, int64_t items) {
+              if (items > 0)
+                hipLaunchKernelGGL(k_squeeze_rows, dim3((unsigned)std::min<int64_t>(8192, (items + 3) / 4), G),
+                                   dim3(kBlock), 0, st, ctab, a, items);
+            };
+            auto words = [&](uint64_t *a, int64_t items) {
+              if (items > 0)
+                hipLaunchKernelGGL(k_squeeze_bits, dim3((unsigned)std::min<int64_t>(4096, (items + 255) / 256), G),
+                                   dim3(kBlock), 0, st, ctab, a, items);
+            };
+            if constexpr (std::is_class<CT>::value)
+              rows(reinterpret_cast<uint8_t *>(c2v), c->E12);
+            else
+              rows(reinterpret_cast<CT *>(c2v), c->E12);
+            rows(P, c->N2);
+            rows(L2, c->N2);
+            rows(Lphi, c->EL);
+            words(synw, c->M);
+            words(B1 + (size_t)(it & 1) * leaf_words, c->EL);
+            width = fit;
+          }
+        }
       }
     }
     TestParams tp{};
@@ -412,18 +543,14 @@ struct Decoder {
     tp.synw = synw;
     tp.B1 = B1 + (size_t)(max_iter & 1) * leaf_words;
     tp.active = active;
-    tp.unsat = unsat + (size_t)(max_iter & 1) * G;
-    {
-      const int64_t per = (int64_t)kWavesPerBlock * (64 / W);
-      ScopedTimer t(st, "k_test");
-      hipLaunchKernelGGL(k_test<W>, dim3((unsigned)((c->M + per - 1) / per), G), dim3(kBlock), 0, st, tp);
-    }
-    fp.unsat_last = unsat + (size_t)(max_iter & 1) * G;
-    {
-      ScopedTimer t(st, "k_finalize");
-      hipLaunchKernelGGL(k_final_status<W>, dim3((B + kBlock - 1) / kBlock), dim3(kBlock), 0, st, fp);
-      hipLaunchKernelGGL(k_finalize<W>, dim3((unsigned)((c->N + 63) / 64), G), dim3(kBlock), 0, st, fp);
-    }
+    tp.unsat = unsat + (size_t)(max_iter & 1) * G * kUnsatWords;
+    fp.unsat_last = unsat + (size_t)(max_iter & 1) * G * kUnsatWords;
+    if (W == 64 && width == 32)
+      finish<32, (W == 64 ? 64 : 32)>(tp, fp, G);
+    else if (W == 64 && width == 16)
+      finish<16, (W == 64 ? 64 : 16)>(tp, fp, G);
+    else
+      finish<W, W>(tp, fp, G);
     HIP_TRY(hipGetLastError());
     return MET_OK;
   }
@@ -599,7 +726,8 @@ static int decode_checked(const met_code *c, const float *llr, const uint8_t *sy
   // launches it asks for.
   const bool shaped = tuning && (tuning->check_steps_per_wave || tuning->variable_chunk);
   if (!shaped && !(flags & (MET_NO_COMPACT | MET_NO_DEG1_SKIP))) {
-    const int tw = met::team_width(c, B, posterior != nullptr, c2v_bytes(flags), !(flags & MET_FIXED_ITERS), ws_bytes);
+    const int tw = met::team_width(c, B, posterior != nullptr, c2v_bytes(flags), max_iter,
+                                   !(flags & MET_FIXED_ITERS), ws_bytes);
     if (tw)
       return met::team_decode(c, d, tw, llr, syn, B, max_iter, flags, bits, iters, converged, posterior,
                               static_cast<char *>(workspace), (hipStream_t)stream);

@@ -390,21 +390,30 @@ __device__ __forceinline__ uint64_t wmask() {
   return W == 64 ? ~0ull : ((1ull << W) - 1ull);
 }
 
-// OR of the W-bit chunks of a wave ballot (lane = item * W + frame).
-template <int W>
-__device__ __forceinline__ uint64_t fold(uint64_t b) {
-  uint64_t r = 0;
-#pragma unroll
-  for (int q = 0; q < 64 / W; ++q) r |= (b >> (q * W)) & wmask<W>();
-  return r;
+// Frames of a group with an unsatisfied check: one byte per frame and accelerator
+// die (XCD); a wave stores 1 for the frames its checks leave unsatisfied, and a
+// reader takes a frame's eight bytes as one word.  Stores need no look first, no
+// wait and no atomic.  (An atomic OR per wave into one word per group, with a look
+// first, queued the waves of an update on that word: 64 frames of N = 65536
+// 35.5 us with the test against 20 without; one word per die 29.7 us; the look
+// moved ahead of the arithmetic 73 us, since every resident wave then issues its
+// atomic; bytes 26.8 us, and with 32 lanes in use 19 us instead of 49.)
+constexpr int kUnsatDies = 8, kUnsatWords = 64;  // uint64 per group: one per frame
+
+__device__ __forceinline__ uint32_t xcc_id() {
+  uint32_t v;
+  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(v));
+  return v & 15u;
 }
 
-// Records frames with an unsatisfied check; one atomic per wave at most, and
-// none once the group's flags already hold these bits.
-__device__ __forceinline__ void flag_unsat(uint64_t *dst, uint64_t f) {
-  if (!f) return;
-  const uint64_t seen = __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (f & ~seen) __hip_atomic_fetch_or(dst, f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void flag_unsat(uint64_t *unsat, int g, int w, bool bad) {
+  uint8_t *bytes = reinterpret_cast<uint8_t *>(unsat + (int64_t)g * kUnsatWords);
+  if (bad) bytes[w * kUnsatDies + (xcc_id() & (kUnsatDies - 1))] = 1;
+}
+
+// Whether frame w of group g has an unsatisfied check.
+__device__ __forceinline__ bool unsat_frame(const uint64_t *unsat, int g, int w) {
+  return unsat[(int64_t)g * kUnsatWords + w] != 0ull;
 }
 
 struct ClassArgs {
@@ -428,8 +437,8 @@ struct CheckParams {
   const uint64_t *synw;  // [G][M]
   const uint64_t *B1in;  // [G][EL] leaf decisions of iteration l-1 (F_TEST)
   uint64_t *B1out;       // [G][EL] leaf decisions of iteration l
-  uint64_t *unsat;       // [G] frames with an unsatisfied check (F_TEST)
-  uint64_t *unsat_clear; // [G] buffer to zero for iteration l+1's test, or NULL
+  uint64_t *unsat;       // [G][kUnsatWords] frames with an unsatisfied check (F_TEST)
+  uint64_t *unsat_clear; // [G][kUnsatWords] buffer to zero for iteration l+1's test, or NULL
   const uint64_t *active;
   const float *weights;  // [T][wstride]
   int32_t wstride, it, flags, G;
@@ -455,7 +464,7 @@ __device__ __forceinline__ void store_leaf_word(uint64_t *dst, uint64_t ball, in
 
 __device__ __forceinline__ void clear_next_unsat(const CheckParams &p, int64_t bx, int g) {
   if (p.unsat_clear && bx == 0 && g == 0)
-    for (int gg = threadIdx.x; gg < p.G; gg += kBlock) p.unsat_clear[gg] = 0ull;
+    for (int k = threadIdx.x; k < p.G * kUnsatWords; k += kBlock) p.unsat_clear[k] = 0ull;
 }
 
 // Loads of words that an earlier phase of the same persistent launch may have
@@ -481,7 +490,7 @@ __device__ __forceinline__ uint64_t ld_racy(const uint64_t *p, int64_t i) {
 // Check update of one class of checks with a compile-time shape (NM message
 // edges, NL leaf edges per check).  Each wave takes IPW consecutive steps of
 // 64/W checks; all loads of its checks are issued before any arithmetic.
-template <int W, int NM, int NL, int MODE, int IPW, bool PERSIST, typename CT = float>
+template <int W, int NM, int NL, int MODE, int IPW, bool PERSIST, typename CT = float, int RS = W>
 __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const ClassArgs &c, int64_t bx, int g) {
   constexpr int D = NM + NL;
   constexpr int IPWAVE = 64 / W;
@@ -531,12 +540,12 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
       const int32_t vi = ldro(p.edge_msgvn, m0 + m);
-      pv[k][m] = p.Pin[((int64_t)g * p.N2 + vi) * W + w];
-      cv[k][m] = first ? 0.0f : ld_c2v<W, CT>(p.c2v_in, ((int64_t)g * p.E12 + m0 + m) * W + w);
+      pv[k][m] = p.Pin[((int64_t)g * p.N2 + vi) * RS + w];
+      cv[k][m] = first ? 0.0f : ld_c2v<W, CT>(p.c2v_in, ((int64_t)g * p.E12 + m0 + m) * RS + w);
     }
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
-      lf[k][l] = ld_stream<W>(&p.Lphi[((int64_t)g * p.EL + l0 + l) * W + w]);
+      lf[k][l] = ld_stream<W>(&p.Lphi[((int64_t)g * p.EL + l0 + l) * RS + w]);
       b1[k][l] = test ? ld_word<PERSIST>(p.B1in, (int64_t)g * p.EL + l0 + l) : 0ull;
     }
   }
@@ -584,14 +593,14 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
       if constexpr (lut) {
         const uint32_t code = tab_out[lut_index(S[m])] | (((tot ^ (neg >> m)) & 1u) << 7);
         if (store)
-          st_stream<W>((uint8_t)code, reinterpret_cast<uint8_t *>(p.c2v) + ((int64_t)g * p.E12 + m0 + m) * W + w);
+          st_stream<W>((uint8_t)code, reinterpret_cast<uint8_t *>(p.c2v) + ((int64_t)g * p.E12 + m0 + m) * RS + w);
       } else {
         const float mag = phi(S[m]);
         float out = ((tot ^ (neg >> m)) & 1u) ? -mag : mag;
         if (weighted)
           out *= edge_scale<W>(p.weights, p.wstride, p.it - 1, p.edge_type, c.first_msg, NM, m, base + k * IPWAVE,
                                c.n_checks, q, m0 + m);
-        if (store) st_c2v<W, CT>(p.c2v, ((int64_t)g * p.E12 + m0 + m) * W + w, out);
+        if (store) st_c2v<W, CT>(p.c2v, ((int64_t)g * p.E12 + m0 + m) * RS + w, out);
       }
     }
     // Leaf decisions (and posteriors) only where somebody reads them: every
@@ -610,34 +619,31 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
       if (wt == 1.0f) {
         bit = leaf_bit(neg_l, neg_c, S[NM + l], A[NM + l]);
       } else {
-        const float lr = p.Lraw[((int64_t)g * p.EL + le) * W + w];
+        const float lr = p.Lraw[((int64_t)g * p.EL + le) * RS + w];
         const float mag = phi(S[NM + l]);
         bit = (uint32_t)(lr + wt * (neg_c ? -mag : mag) < 0.0f);
       }
       if (post && store && lane_act) {
-        const float lr = p.Lraw[((int64_t)g * p.EL + le) * W + w];
+        const float lr = p.Lraw[((int64_t)g * p.EL + le) * RS + w];
         const float mag = phi(S[NM + l]);
-        p.P1[((int64_t)g * p.EL + le) * W + w] = lr + wt * (neg_c ? -mag : mag);
+        p.P1[((int64_t)g * p.EL + le) * RS + w] = lr + wt * (neg_c ? -mag : mag);
       }
       const uint64_t ball = __ballot((int)(bit & (uint32_t)valid[k]));
       if (w == 0 && valid[k]) store_leaf_word<W>(p.B1out + (int64_t)g * p.EL + le, ball, q, act);
     }
   }
-  if (test) {
-    const uint64_t f = fold<W>(__ballot((int)bad));
-    if (lane == 0) flag_unsat(p.unsat + g, f);
-  }
+  if (test) flag_unsat(p.unsat, g, w, bad);
 }
 
-template <int W, int NM, int NL, int MODE, int IPW, typename CT = float>
+template <int W, int NM, int NL, int MODE, int IPW, typename CT = float, int RS = W>
 __global__ __launch_bounds__(kBlock) void k_check_fixed(const CheckParams p, const ClassArgs c) {
   const GridTile t = MODE == M_SPECIAL ? GridTile{blockIdx.x, (int)blockIdx.y} : xcd_grid_tile();
-  check_fixed_body<W, NM, NL, MODE, IPW, false, CT>(p, c, t.bx, t.g);
+  check_fixed_body<W, NM, NL, MODE, IPW, false, CT, RS>(p, c, t.bx, t.g);
 }
 
 // Check update with run-time degrees (total degree <= MET_MAX_CHECK_DEGREE),
 // for classes without a compiled shape.  One check per lane group.
-template <int W, bool PERSIST, typename CT = float>
+template <int W, bool PERSIST, typename CT = float, int RS = W>
 __device__ __forceinline__ void check_generic_body(const CheckParams &p, const ClassArgs &c, int64_t bx, int g) {
   constexpr int D = MET_MAX_CHECK_DEGREE;
   clear_next_unsat(p, bx, g);
@@ -663,15 +669,15 @@ __device__ __forceinline__ void check_generic_body(const CheckParams &p, const C
     A[k] = 0.0f;  // phi-domain identity: an absent input adds nothing
     if (k < nm) {
       const int64_t e = m0 + k;
-      const float pv = p.Pin[((int64_t)g * p.N2 + p.edge_msgvn[e]) * W + w];
-      const float cv = first ? 0.0f : ld_c2v<W, CT>(p.c2v_in, ((int64_t)g * p.E12 + e) * W + w);
+      const float pv = p.Pin[((int64_t)g * p.N2 + p.edge_msgvn[e]) * RS + w];
+      const float cv = first ? 0.0f : ld_c2v<W, CT>(p.c2v_in, ((int64_t)g * p.E12 + e) * RS + w);
       parity ^= (uint32_t)(pv < 0.0f);
       const float x = clamp_llr(pv - cv);
       A[k] = phi(fabsf(x));
       neg |= sign_bit(x) << k;
     } else if (k < nm + nl) {
       const int64_t le = l0 + (k - nm);
-      const float f = p.Lphi[((int64_t)g * p.EL + le) * W + w];
+      const float f = p.Lphi[((int64_t)g * p.EL + le) * RS + w];
       A[k] = fabsf(f);
       neg |= sign_bit(f) << k;
       if (test) parity ^= (uint32_t)(ld_word<PERSIST>(p.B1in, (int64_t)g * p.EL + le) >> w) & 1u;
@@ -693,7 +699,7 @@ __device__ __forceinline__ void check_generic_body(const CheckParams &p, const C
       const float mag = phi(pre[k] + suf[k]);
       float out = ((tot ^ (neg >> k)) & 1u) ? -mag : mag;
       if (weighted) out *= p.weights[(int64_t)p.edge_type[m0 + k] * p.wstride + (p.it - 1)];
-      if (store) st_c2v<W, CT>(p.c2v, ((int64_t)g * p.E12 + m0 + k) * W + w, out);
+      if (store) st_c2v<W, CT>(p.c2v, ((int64_t)g * p.E12 + m0 + k) * RS + w, out);
     }
   }
   // Leaf decisions: ballots must be executed by every lane of the wave, so the
@@ -720,29 +726,26 @@ __device__ __forceinline__ void check_generic_body(const CheckParams &p, const C
       if (wt == 1.0f) {
         bit = leaf_bit(neg_l, neg_c, S, Aleaf);
       } else {
-        const float lr = p.Lraw[((int64_t)g * p.EL + le) * W + w];
+        const float lr = p.Lraw[((int64_t)g * p.EL + le) * RS + w];
         const float mag = phi(S);
         bit = (uint32_t)(lr + wt * (neg_c ? -mag : mag) < 0.0f);
       }
       if ((p.flags & F_POST) && store && lane_act) {
-        const float lr = p.Lraw[((int64_t)g * p.EL + le) * W + w];
+        const float lr = p.Lraw[((int64_t)g * p.EL + le) * RS + w];
         const float mag = phi(S);
-        p.P1[((int64_t)g * p.EL + le) * W + w] = lr + wt * (neg_c ? -mag : mag);
+        p.P1[((int64_t)g * p.EL + le) * RS + w] = lr + wt * (neg_c ? -mag : mag);
       }
     }
     const uint64_t ball = __ballot((int)bit);
     if (w == 0 && has) store_leaf_word<W>(p.B1out + (int64_t)g * p.EL + le, ball, q, act);
   }
-  if (test) {
-    const uint64_t f = fold<W>(__ballot((int)bad));
-    if (lane == 0) flag_unsat(p.unsat + g, f);
-  }
+  if (test) flag_unsat(p.unsat, g, w, bad);
 }
 
-template <int W, typename CT = float>
+template <int W, typename CT = float, int RS = W>
 __global__ __launch_bounds__(kBlock) void k_check_generic(const CheckParams p, const ClassArgs c) {
   const GridTile t = xcd_grid_tile();
-  check_generic_body<W, false, CT>(p, c, t.bx, t.g);
+  check_generic_body<W, false, CT, RS>(p, c, t.bx, t.g);
 }
 
 // All check classes of a compiled shape in one launch.  Classes with few checks
@@ -757,12 +760,12 @@ struct ClassSet {
   ClassArgs c[kMaxClasses];
 };
 
-template <int W, int MODE, int IPW, typename CT = float>
+template <int W, int MODE, int IPW, typename CT = float, int RS = W>
 __global__ __launch_bounds__(kBlock) void k_check_set(const CheckParams p, const ClassSet set) {
   if ((int)blockIdx.x >= set.lead_block) {
     const GridTile t = MODE == M_SPECIAL ? GridTile{(int64_t)blockIdx.x - set.lead_block, (int)blockIdx.y}
                                          : xcd_grid_tile(set.lead_block);
-    check_fixed_body<W, 3, 1, MODE, IPW, false, CT>(p, set.c[set.n - 1], t.bx, t.g);
+    check_fixed_body<W, 3, 1, MODE, IPW, false, CT, RS>(p, set.c[set.n - 1], t.bx, t.g);
     return;
   }
   int k = 0;
@@ -771,13 +774,13 @@ __global__ __launch_bounds__(kBlock) void k_check_set(const CheckParams p, const
   const int64_t bx = (int64_t)blockIdx.x - set.block0[k];
   const int g = (int)blockIdx.y;
   switch (c.shape) {
-    case 0: check_fixed_body<W, 3, 1, MODE, 1, false, CT>(p, c, bx, g); break;
-    case 1: check_fixed_body<W, 2, 1, MODE, 1, false, CT>(p, c, bx, g); break;
-    case 2: check_fixed_body<W, 12, 0, MODE, 1, false, CT>(p, c, bx, g); break;
-    case 3: check_fixed_body<W, 11, 0, MODE, 1, false, CT>(p, c, bx, g); break;
-    case 4: check_fixed_body<W, 6, 0, MODE, 1, false, CT>(p, c, bx, g); break;
-    case 5: check_fixed_body<W, 5, 0, MODE, 1, false, CT>(p, c, bx, g); break;
-    default: check_fixed_body<W, 4, 0, MODE, 1, false, CT>(p, c, bx, g); break;
+    case 0: check_fixed_body<W, 3, 1, MODE, 1, false, CT, RS>(p, c, bx, g); break;
+    case 1: check_fixed_body<W, 2, 1, MODE, 1, false, CT, RS>(p, c, bx, g); break;
+    case 2: check_fixed_body<W, 12, 0, MODE, 1, false, CT, RS>(p, c, bx, g); break;
+    case 3: check_fixed_body<W, 11, 0, MODE, 1, false, CT, RS>(p, c, bx, g); break;
+    case 4: check_fixed_body<W, 6, 0, MODE, 1, false, CT, RS>(p, c, bx, g); break;
+    case 5: check_fixed_body<W, 5, 0, MODE, 1, false, CT, RS>(p, c, bx, g); break;
+    default: check_fixed_body<W, 4, 0, MODE, 1, false, CT, RS>(p, c, bx, g); break;
   }
 }
 
@@ -791,7 +794,7 @@ struct TestParams {
   uint64_t *unsat;
 };
 
-template <int W>
+template <int W, int RS = W>
 __global__ __launch_bounds__(kBlock) void k_test(const TestParams p) {
   const int g = blockIdx.y;
   const uint64_t act = p.active[g];
@@ -802,13 +805,12 @@ __global__ __launch_bounds__(kBlock) void k_test(const TestParams p) {
   if (j < p.M) {
     uint32_t parity = (uint32_t)(p.synw[(int64_t)g * p.M + j] >> w) & 1u;
     for (int32_t e = p.chk_msg_ptr[j]; e < p.chk_msg_ptr[j + 1]; ++e)
-      parity ^= (uint32_t)(p.P[((int64_t)g * p.N2 + p.edge_msgvn[e]) * W + w] < 0.0f);
+      parity ^= (uint32_t)(p.P[((int64_t)g * p.N2 + p.edge_msgvn[e]) * RS + w] < 0.0f);
     for (int32_t e = p.chk_leaf_ptr[j]; e < p.chk_leaf_ptr[j + 1]; ++e)
       parity ^= (uint32_t)(p.B1[(int64_t)g * p.EL + e] >> w) & 1u;
     bad = parity & (uint32_t)((act >> w) & 1ull);
   }
-  const uint64_t f = fold<W>(__ballot((int)bad));
-  if (lane == 0) flag_unsat(p.unsat + g, f);
+  flag_unsat(p.unsat, g, w, bad);
 }
 
 struct VarParams {
@@ -818,7 +820,7 @@ struct VarParams {
   const float *c2v;      // [G][E12][W]
   float *P;              // [G][N2][W]
   uint64_t *active;      // [G]
-  const uint64_t *unsat; // [G] test result of iteration it-1 (retire mode)
+  const uint64_t *unsat; // [G][kUnsatWords] test result of iteration it-1 (retire mode)
   int32_t *iters;
   uint8_t *converged;
   const int32_t *slot_frame;  // [G*W] frame held by each lane, -1 none (NULL: lane s holds frame s)
@@ -826,14 +828,14 @@ struct VarParams {
 };
 
 // Frame held by lane w of group g.
-template <int W>
+template <int RS>
 __device__ __forceinline__ int lane_frame(const int32_t *slot_frame, int g, int w) {
-  return slot_frame ? slot_frame[g * W + w] : g * W + w;
+  return slot_frame ? slot_frame[g * RS + w] : g * RS + w;
 }
 
 // Variable update: P_v = L_v + sum of c2v over v's message edges (gathered U
 // at a time, summed in list order).
-template <int W, int U, bool PERSIST, typename CT = float>
+template <int W, int U, bool PERSIST, typename CT = float, int RS = W>
 __device__ __forceinline__ void variable_body(const VarParams &p, int64_t bx, int g) {
   uint64_t act = ld_racy<PERSIST>(p.active, g);
   if (p.retire) {
@@ -842,12 +844,13 @@ __device__ __forceinline__ void variable_body(const VarParams &p, int64_t bx, in
     if (bx == 0 && g == 0) {
       for (int gg = threadIdx.x; gg < p.G; gg += kBlock) {
         const uint64_t a = p.active[gg];  // only this block writes the mask
-        const uint64_t u = p.unsat[gg];
+        uint64_t u = 0;
+        for (int w = 0; w < W; ++w) u |= (uint64_t)unsat_frame(p.unsat, gg, w) << w;
         const uint64_t done = a & ~u;
         if (done) {
           for (int w = 0; w < W; ++w)
             if ((done >> w) & 1ull) {
-              const int f = lane_frame<W>(p.slot_frame, gg, w);
+              const int f = lane_frame<RS>(p.slot_frame, gg, w);
               p.iters[f] = p.it - 1;
               p.converged[f] = 1;
             }
@@ -855,7 +858,7 @@ __device__ __forceinline__ void variable_body(const VarParams &p, int64_t bx, in
         }
       }
     }
-    act &= p.unsat[g];
+    act &= __ballot(unsat_frame(p.unsat, g, (int)(threadIdx.x & 63) % W));  // bits past W: not in act
   }
   if (act == 0ull) return;
   const int lane = threadIdx.x & 63, wv = wave_id(), w = lane % W, q = lane / W;
@@ -863,13 +866,13 @@ __device__ __forceinline__ void variable_body(const VarParams &p, int64_t bx, in
   const int64_t i = (bx * kWavesPerBlock + wv) * (64 / W) + q;
   if (i >= p.N2) return;
   const int32_t e0 = ldro(p.vn_ptr, i), e1 = ldro(p.vn_ptr, i + 1);
-  float P = p.L2[((int64_t)g * p.N2 + i) * W + w];
-  const CT *c2v = reinterpret_cast<const CT *>(p.c2v) + (int64_t)g * p.E12 * W + w;
+  float P = p.L2[((int64_t)g * p.N2 + i) * RS + w];
+  const CT *c2v = reinterpret_cast<const CT *>(p.c2v) + (int64_t)g * p.E12 * RS + w;
   int32_t e = e0;
   for (; e + U <= e1; e += U) {
     float a[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) a[u] = ld_msg<W, CT>(c2v + (int64_t)ldro(p.vn_edges, e + u) * W);
+    for (int u = 0; u < U; ++u) a[u] = ld_msg<W, CT>(c2v + (int64_t)ldro(p.vn_edges, e + u) * RS);
 #pragma unroll
     for (int u = 0; u < U; ++u) P += a[u];
   }
@@ -877,18 +880,18 @@ __device__ __forceinline__ void variable_body(const VarParams &p, int64_t bx, in
     for (; e + 8 <= e1; e += 8) {
       float a[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) a[u] = ld_msg<W, CT>(c2v + (int64_t)ldro(p.vn_edges, e + u) * W);
+      for (int u = 0; u < 8; ++u) a[u] = ld_msg<W, CT>(c2v + (int64_t)ldro(p.vn_edges, e + u) * RS);
 #pragma unroll
       for (int u = 0; u < 8; ++u) P += a[u];
     }
-  for (; e < e1; ++e) P += ld_msg<W, CT>(c2v + (int64_t)ldro(p.vn_edges, e) * W);
-  if (lane_act) p.P[((int64_t)g * p.N2 + i) * W + w] = P;
+  for (; e < e1; ++e) P += ld_msg<W, CT>(c2v + (int64_t)ldro(p.vn_edges, e) * RS);
+  if (lane_act) p.P[((int64_t)g * p.N2 + i) * RS + w] = P;
 }
 
-template <int W, int U, typename CT = float>
+template <int W, int U, typename CT = float, int RS = W>
 __global__ __launch_bounds__(kBlock) void k_variable(const VarParams p) {
   const GridTile t = xcd_grid_tile();
-  variable_body<W, U, false, CT>(p, t.bx, t.g);
+  variable_body<W, U, false, CT, RS>(p, t.bx, t.g);
 }
 
 // ----------------------------------------------------------------------------
@@ -958,11 +961,12 @@ __global__ __launch_bounds__(kBlock) void k_pack_syndrome(const InitParams p) {
     }
     p.synw[(int64_t)g * p.M + p.chk_pos[j]] = word;
   }
+  if (blockIdx.x == 0)
+    for (int k = threadIdx.x; k < 2 * kUnsatWords; k += kBlock)
+      p.unsat[((int64_t)(k / kUnsatWords) * p.G + g) * kUnsatWords + k % kUnsatWords] = 0ull;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     const int valid = min(W, p.B - g * W);
     p.active[g] = valid >= 64 ? ~0ull : ((1ull << valid) - 1ull);
-    p.unsat[g] = 0ull;
-    p.unsat[p.G + g] = 0ull;
     for (int w = 0; w < valid; ++w) {
       p.iters[g * W + w] = 0;
       p.converged[g * W + w] = 0;
@@ -988,21 +992,21 @@ struct FinalParams {
 };
 
 // Outcome of frames still running after the last iteration.
-template <int W>
+template <int W, int RS = W>
 __global__ void k_final_status(const FinalParams p) {
   for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < p.G * W; s += gridDim.x * blockDim.x) {
     const int g = s / W, w = s % W;
-    const int f = lane_frame<W>(p.slot_frame, g, w);
+    const int f = lane_frame<RS>(p.slot_frame, g, w);
     if (f >= 0 && f < p.B && ((p.active[g] >> w) & 1ull)) {
       p.iters[f] = p.max_iter;
-      p.converged[f] = (uint8_t)!((p.unsat_last[g] >> w) & 1ull);
+      p.converged[f] = (uint8_t)!unsat_frame(p.unsat_last, g, w);
     }
   }
 }
 
 // Outputs in user order through an LDS tile of 64 VNs x W frames: reads are
 // item rows of W frames, writes are runs of 64 consecutive VNs per frame.
-template <int W>
+template <int W, int RS = W>
 __global__ __launch_bounds__(kBlock) void k_finalize(const FinalParams p) {
   __shared__ float val[64][W + 1];
   __shared__ uint8_t bit[64][W + 1];
@@ -1012,7 +1016,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const FinalParams p) {
   const int64_t v0 = (int64_t)blockIdx.x * 64;
   bool any = false;
   if (threadIdx.x < W) {
-    int f = lane_frame<W>(p.slot_frame, g, threadIdx.x);
+    int f = lane_frame<RS>(p.slot_frame, g, threadIdx.x);
     if (f >= p.B || (p.flush && ((p.active[g] >> threadIdx.x) & 1ull))) f = -1;
     frame[threadIdx.x] = f;
     odd[threadIdx.x] = f >= 0 ? (uint8_t)(p.iters[f] & 1) : 0;
@@ -1026,12 +1030,12 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const FinalParams p) {
     if (v0 + v < p.N) {
       const int32_t slot = p.vn_slot[v0 + v];
       if (slot >= 0) {
-        post = p.P[((int64_t)g * p.N2 + slot) * W + w];
+        post = p.P[((int64_t)g * p.N2 + slot) * RS + w];
         b = post < 0.0f;
       } else {
         const int64_t le = -(int64_t)slot - 1;
         b = (uint8_t)(((odd[w] ? p.B1b : p.B1a)[(int64_t)g * p.EL + le] >> w) & 1ull);
-        if (p.posterior) post = (odd[w] ? p.P1b : p.P1a)[((int64_t)g * p.EL + le) * W + w];
+        if (p.posterior) post = (odd[w] ? p.P1b : p.P1a)[((int64_t)g * p.EL + le) * RS + w];
       }
     }
     val[v][w] = post;
@@ -1049,6 +1053,11 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const FinalParams p) {
 
 // ----------------------------------------------------------------------------
 // Host launch helpers
+
+// Check steps per wave after squeezing (32 or 16 lanes in use): 64 frames of
+// N = 10^6 at 32 lanes 194 us a (3,1) update against 246 with one step and 215 with
+// four, of N = 65536 16.7 against 19.0.
+constexpr int kSqueezeSteps = 2;
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -1097,7 +1106,7 @@ Plan make_plan(const met_code *c, int B, bool post, bool weighted, int W, size_t
   pl.off_P1 = pl.p1 ? take(2 * GW * c->EL * sizeof(float)) : 0;
   pl.off_synw = take((size_t)pl.G * c->M * sizeof(uint64_t));
   pl.off_B1 = take(2 * (size_t)pl.G * c->EL * sizeof(uint64_t));
-  pl.off_unsat = take(2 * (size_t)pl.G * sizeof(uint64_t));
+  pl.off_unsat = take(2 * (size_t)pl.G * kUnsatWords * sizeof(uint64_t));
   pl.off_active = take((size_t)pl.G * sizeof(uint64_t));
   pl.off_slot = take(GW * sizeof(int32_t));
   pl.off_ctab = take(compact_table_bytes(pl.G));
@@ -1116,17 +1125,17 @@ Plan make_plan(const met_code *c, int B, bool post, bool weighted, int W, size_t
     if (e_ != hipSuccess) return fail(MET_EHIP, "%s: %s", #expr, hipGetErrorString(e_)); \
   } while (0)
 
-template <int W, int MODE, int IPW, typename CT = float>
+template <int W, int MODE, int IPW, typename CT = float, int RS = W>
 void launch_fixed(int shape, unsigned blocks, int G, hipStream_t st, const CheckParams &p, const ClassArgs &c) {
   const dim3 grid(blocks, G), block(kBlock);
   switch (shape) {
-    case 0: hipLaunchKernelGGL((k_check_fixed<W, 3, 1, MODE, IPW, CT>), grid, block, 0, st, p, c); break;
-    case 1: hipLaunchKernelGGL((k_check_fixed<W, 2, 1, MODE, IPW, CT>), grid, block, 0, st, p, c); break;
-    case 2: hipLaunchKernelGGL((k_check_fixed<W, 12, 0, MODE, IPW, CT>), grid, block, 0, st, p, c); break;
-    case 3: hipLaunchKernelGGL((k_check_fixed<W, 11, 0, MODE, IPW, CT>), grid, block, 0, st, p, c); break;
-    case 4: hipLaunchKernelGGL((k_check_fixed<W, 6, 0, MODE, IPW, CT>), grid, block, 0, st, p, c); break;
-    case 5: hipLaunchKernelGGL((k_check_fixed<W, 5, 0, MODE, IPW, CT>), grid, block, 0, st, p, c); break;
-    default: hipLaunchKernelGGL((k_check_fixed<W, 4, 0, MODE, IPW, CT>), grid, block, 0, st, p, c); break;
+    case 0: hipLaunchKernelGGL((k_check_fixed<W, 3, 1, MODE, IPW, CT, RS>), grid, block, 0, st, p, c); break;
+    case 1: hipLaunchKernelGGL((k_check_fixed<W, 2, 1, MODE, IPW, CT, RS>), grid, block, 0, st, p, c); break;
+    case 2: hipLaunchKernelGGL((k_check_fixed<W, 12, 0, MODE, IPW, CT, RS>), grid, block, 0, st, p, c); break;
+    case 3: hipLaunchKernelGGL((k_check_fixed<W, 11, 0, MODE, IPW, CT, RS>), grid, block, 0, st, p, c); break;
+    case 4: hipLaunchKernelGGL((k_check_fixed<W, 6, 0, MODE, IPW, CT, RS>), grid, block, 0, st, p, c); break;
+    case 5: hipLaunchKernelGGL((k_check_fixed<W, 5, 0, MODE, IPW, CT, RS>), grid, block, 0, st, p, c); break;
+    default: hipLaunchKernelGGL((k_check_fixed<W, 4, 0, MODE, IPW, CT, RS>), grid, block, 0, st, p, c); break;
   }
 }
 
@@ -1144,23 +1153,26 @@ void launch_fixed_ipw(int ipw, int shape, unsigned blocks, int G, hipStream_t st
 // One check-kernel launch over a class: compiled shape (mode, steps per wave)
 // or the run-time-degree kernel.  Half-precision and 8-bit message storage are
 // compiled for groups of 64 frames with 4 check steps per wave only.
-template <int W, typename CT = float>
+template <int W, typename CT = float, int RS = W>
 void launch_check(const CheckParams &p, const ClassArgs &a, int mode, int cn_ipw, int G, hipStream_t st) {
   constexpr bool half = !std::is_same<CT, float>::value;  // half or 8-bit storage
-  static_assert(!half || W == 64, "reduced message storage needs groups of 64 frames");
+  static_assert(!half || RS == 64, "reduced message storage needs groups of 64 frames");
   const bool gen = a.shape == kShapeGeneric;
-  const int ipw = (W == 64 && !gen) ? (half ? 4 : cn_ipw) : 1;
+  const int ipw = gen ? 1 : RS != W ? kSqueezeSteps : W == 64 ? (half ? 4 : cn_ipw) : 1;
   const int64_t per_block = (int64_t)kWavesPerBlock * ipw * (64 / W);
   const unsigned blocks = (unsigned)((a.n_checks + per_block - 1) / per_block);
   if (gen)
-    hipLaunchKernelGGL((k_check_generic<W, CT>), dim3(blocks, G), dim3(kBlock), 0, st, p, a);
-  else if (half && mode == M_SPECIAL)
-    launch_fixed<W, M_SPECIAL, 4, CT>(a.shape, blocks, G, st, p, a);
-  else if (half && mode == M_FIRST)
-    launch_fixed<W, M_FIRST, 4, CT>(a.shape, blocks, G, st, p, a);
-  else if (half)
-    launch_fixed<W, M_MAIN, 4, CT>(a.shape, blocks, G, st, p, a);
-  else if (mode == M_SPECIAL)
+    hipLaunchKernelGGL((k_check_generic<W, CT, RS>), dim3(blocks, G), dim3(kBlock), 0, st, p, a);
+  else if constexpr (RS != W)
+    launch_fixed<W, M_MAIN, kSqueezeSteps, CT, RS>(a.shape, blocks, G, st, p, a);
+  else if constexpr (half) {
+    if (mode == M_SPECIAL)
+      launch_fixed<W, M_SPECIAL, 4, CT>(a.shape, blocks, G, st, p, a);
+    else if (mode == M_FIRST)
+      launch_fixed<W, M_FIRST, 4, CT>(a.shape, blocks, G, st, p, a);
+    else
+      launch_fixed<W, M_MAIN, 4, CT>(a.shape, blocks, G, st, p, a);
+  } else if (mode == M_SPECIAL)
     launch_fixed_ipw<W, M_SPECIAL>(ipw, a.shape, blocks, G, st, p, a);
   else if (mode == M_FIRST)
     launch_fixed_ipw<W, M_FIRST>(ipw, a.shape, blocks, G, st, p, a);
@@ -1169,8 +1181,9 @@ void launch_check(const CheckParams &p, const ClassArgs &a, int mode, int cn_ipw
 }
 
 // One check update of every class: the compiled shapes in one launch when the
-// largest of them is a (3,1) class, else a launch per class.
-template <int W, typename CT = float>
+// largest of them is a (3,1) class, else a launch per class.  RS != W: groups of
+// 64 frames of which the lower W lanes are in use (main mode only).
+template <int W, typename CT = float, int RS = W>
 void launch_checks(const CheckParams &p, const std::vector<ClassArgs> &classes, int mode, int cn_ipw, int G,
                    hipStream_t st, const char *name = nullptr);
 
@@ -1194,11 +1207,11 @@ inline std::vector<ClassArgs> class_args(const met_code *c) {
 const char *const kCheckKernelName[kNumFixedShapes + 1] = {
     "k_check<3,1>", "k_check<2,1>", "k_check<12,0>", "k_check<11,0>", "k_check<6,0>", "k_check<5,0>",
     "k_check<4,0>", "k_check_generic"};
-template <int W, typename CT>
+template <int W, typename CT, int RS>
 void launch_checks(const CheckParams &p, const std::vector<ClassArgs> &classes, int mode, int cn_ipw, int G,
                    hipStream_t st, const char *name) {
   constexpr bool half = !std::is_same<CT, float>::value;
-  const int ipw = W == 64 ? (half ? 4 : cn_ipw) : 1;
+  const int ipw = RS != W ? kSqueezeSteps : W == 64 ? (half ? 4 : cn_ipw) : 1;
   const ClassArgs *lead = nullptr;
   int n_fixed = 0;
   for (const ClassArgs &a : classes)
@@ -1235,20 +1248,24 @@ void launch_checks(const CheckParams &p, const std::vector<ClassArgs> &classes, 
     const unsigned nb = (unsigned)(blocks + (lead->n_checks + per - 1) / per);
     ScopedTimer t(st, name ? name : "k_check_set");
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(nb, G), dim3(kBlock), 0, st, q, set); };
-    constexpr int i4 = W == 64 ? 4 : 1, i2 = W == 64 && !half ? 2 : i4, i1 = half ? i4 : 1;
-    // (reduced storage is compiled with 4 steps per wave only)
-    if (mode == M_SPECIAL)
-      ipw == 4 ? go(k_check_set<W, M_SPECIAL, i4, CT>) : ipw == 2 ? go(k_check_set<W, M_SPECIAL, i2, CT>) : go(k_check_set<W, M_SPECIAL, i1, CT>);
-    else if (mode == M_FIRST)
-      ipw == 4 ? go(k_check_set<W, M_FIRST, i4, CT>) : ipw == 2 ? go(k_check_set<W, M_FIRST, i2, CT>) : go(k_check_set<W, M_FIRST, i1, CT>);
-    else
-      ipw == 4 ? go(k_check_set<W, M_MAIN, i4, CT>) : ipw == 2 ? go(k_check_set<W, M_MAIN, i2, CT>) : go(k_check_set<W, M_MAIN, i1, CT>);
+    if constexpr (RS != W) {
+      go(k_check_set<W, M_MAIN, kSqueezeSteps, CT, RS>);
+    } else {
+      // (reduced storage is compiled with 4 steps per wave only)
+      constexpr int i4 = W == 64 ? 4 : 1, i2 = W == 64 && !half ? 2 : i4, i1 = half ? i4 : 1;
+      if (mode == M_SPECIAL)
+        ipw == 4 ? go(k_check_set<W, M_SPECIAL, i4, CT>) : ipw == 2 ? go(k_check_set<W, M_SPECIAL, i2, CT>) : go(k_check_set<W, M_SPECIAL, i1, CT>);
+      else if (mode == M_FIRST)
+        ipw == 4 ? go(k_check_set<W, M_FIRST, i4, CT>) : ipw == 2 ? go(k_check_set<W, M_FIRST, i2, CT>) : go(k_check_set<W, M_FIRST, i1, CT>);
+      else
+        ipw == 4 ? go(k_check_set<W, M_MAIN, i4, CT>) : ipw == 2 ? go(k_check_set<W, M_MAIN, i2, CT>) : go(k_check_set<W, M_MAIN, i1, CT>);
+    }
     q.unsat_clear = nullptr;  // cleared by the set's first blocks
   }
   for (const ClassArgs &a : classes) {
     if (merged && a.shape != kShapeGeneric) continue;
     ScopedTimer t(st, name ? name : kCheckKernelName[a.shape]);
-    launch_check<W, CT>(q, a, mode, cn_ipw, G, st);
+    launch_check<W, CT, RS>(q, a, mode, cn_ipw, G, st);
     q.unsat_clear = nullptr;
   }
 }

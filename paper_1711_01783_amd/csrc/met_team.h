@@ -43,7 +43,7 @@ size_t team_control_bytes();
 
 // Frames per group with which the team decoder takes this decode, or 0 where
 // the per-phase launches are the better path or the workspace is too small.
-int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, bool early, size_t ws_bytes);
+int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, int max_iter, bool early, size_t ws_bytes);
 
 int team_decode(const met_code *c, const DeviceCode *d, int W, const float *llr, const uint8_t *syn, int B,
                 int max_iter, uint32_t flags, uint8_t *bits, int32_t *iters, uint8_t *conv, float *post,

@@ -512,12 +512,6 @@ struct TeamShared {
   int32_t stop[16]; // iteration at which each frame of the group stopped
 };
 
-__device__ __forceinline__ uint32_t xcc_id() {
-  uint32_t v;
-  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(v));
-  return v & (kXccIds - 1);
-}
-
 // Registers the workgroup with its XCD's team; false if it has no part in it.
 __device__ bool join_team(TeamControl *ctl, uint32_t xcc, uint32_t expected, uint32_t n_slots, TeamShared &sh) {
   if (threadIdx.x == 0) {
@@ -890,44 +884,46 @@ size_t team_slot(const met_code *c, int W, bool post, size_t c2v_bytes, TeamJob 
 }
 
 
-// The rule compares the measured time of an iteration on both paths (us; E:
-// message edges in millions; float messages, rates 0.1 to 0.02, N = 4096 to
-// 10^6, 1 to 256 frames):
+// The rule compares the estimated time of an iteration on both paths (us; E:
+// message edges in millions, F: frames in whole groups of the launches; measured
+// with float messages, rates 0.1 to 0.02, N = 4096 to 10^6, 1 to 256 frames):
 //   team:     4.5 + (32 + 17.5 W) E per round of eight groups.  N = 65536, rate 0.1:
 //             W = 1 15.2, 2 17.8, 4 23.4, 8 38.5, 16 67; 8-bit messages
 //             (20 + 16 W): W = 4 19, 8 32, 16 57; N = 16384: W = 1 7.4, 4 9.4, 8
 //             11, 16 18; 15 % more once a group's state is beyond 8 MB, twice
 //             the L2 (N = 262144: W = 1 64, 4 96)
-//   launches: 3.4 per launch + 2.6 F E, F = frames in whole groups (2.1 F E
-//             with 16- or 8-bit messages).  N = 65536, rate 0.1: 1 frame 21, 16
-//             25, 64 52, 256 142; N = 262144: 1 frame 25, 16 50, 64 138; the
-//             team takes 64, 94 (W = 4) and 193 (W = 4) there
-// With early exit the launches run until the slowest of all frames stops, a team
-// until the slowest of each of its groups: in units of the former, a group of W
-// out of B frames takes about m = (W / B)^(1/4) and the eight teams end after
-// max(1, m groups / 8) + m / 2 (1 where each has one group).  Measured (ms, launches / team, waterfall):
-// 64 frames of N = 65536 6.3 / 3.7 (W = 4; 2: 4.1, 8: 4.3), 250 of 16384 5.1 /
-// 3.0 (W = 8), 16 of 16001 at rate 0.02 4.5 / 1.5 (W = 1), 100 of 30000 6.0 / 4.8
-// (W = 4), 64 of 262144 with 8-bit messages 21.7 / 18.7.  Where every frame runs
-// its whole budget that advantage is gone, so a team may cost at most a fifth
-// more per iteration.  States that leave the Infinity Cache are not for teams:
-// 64 frames of N = 10^6 take 87 ms in groups of 8, 49 ms in launches.
-int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, bool early, size_t ws_bytes) {
+//   launches: 3.2 per launch + 2.5 F E (2.0 with 16- or 8-bit messages), 9 more for
+//             the host's reads with early exit, and 60 more per decode of set-up
+//             and output launches.  N = 65536, rate 0.1: 1 frame 21, 16 18, 64 32,
+//             256 119; N = 262144: 1 frame 26, 16 40, 64 122
+// With early exit the launches run until the slowest of all frames stops, on
+// squeezed groups for about half of the time if there were 64 frames to begin
+// with; a team runs until the slowest of each of its groups.  In units of the
+// former a group of W out of B frames takes about m = (W / B)^(1/5), and the
+// eight teams end after max(1, m groups / 8) + m (1 where each has one group).
+// Measured (ms, launches / team, waterfall): 1 frame of 4096 0.41 / 0.09, 64 1.6 /
+// 0.8, 256 2.1 / 1.8; N = 16384: 64 frames 1.9 / 1.3, 128 2.3 / 2.4, 256 3.1 / 4.1;
+// N = 65536: 1 frame 1.1 / 0.5, 16 2.4 / 1.8, 32 3.0 / 1.8, 64 3.1 / 3.6.  A team that
+// would be slower if every frame ran its whole budget is not taken, nor one whose
+// states leave the Infinity Cache (64 frames of N = 10^6 in groups of 8: 87 ms).
+int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, int max_iter, bool early, size_t ws_bytes) {
   const double E = 1e-6 * (double)c->E12;
   const int plain_w = choose_interleave(B);
-  const double plain = 3.4 * (double)(c->classes.size() + 1) +
-                       (c2v_bytes == sizeof(float) ? 2.6 : 2.1) * E * ((B + plain_w - 1) / plain_w) * plain_w;
+  const double FE = E * ((B + plain_w - 1) / plain_w) * plain_w * (c2v_bytes == sizeof(float) ? 2.5 : 2.0);
+  const double launches = plain_w >= 16 && c2v_bytes != 1 ? 2.0 : (double)(c->classes.size() + 1);
+  const double fixed = 3.2 * launches + (early ? 9.0 : 0.0) + 60.0 / (early ? 0.5 * max_iter + 0.5 : max_iter);
+  const double whole = fixed + FE;  // every frame to the end of the budget
   int best = 0;
-  double best_t = plain;
+  double best_t = early && plain_w == 64 ? fixed + 0.5 * FE : whole;
   for (int W : {16, 8, 4, 2, 1}) {
     if (c2v_bytes != sizeof(float) && W < 4) continue;
     const int G = (B + W - 1) / W, rounds = (G + kTeamSlots - 1) / kTeamSlots;
     const size_t slot = team_slot(c, W, post, c2v_bytes, nullptr), all = slot * std::min(G, kTeamSlots);
     if (slot >= kMaxSlotBytes || team_control_bytes() + all > ws_bytes || all > kMaxTeamBytes) continue;
     const double it = (4.5 + (c2v_bytes == 1 ? 20 + 16 * W : 32 + 17.5 * W) * E) * (slot > (8u << 20) ? 1.15 : 1.0);
-    if (rounds * it > 1.2 * plain) continue;
-    const double m = std::min(1.0, std::pow((double)W / B, 0.25));
-    const double t = early && rounds > 1 ? it * (std::max(1.0, m * G / kTeamSlots) + 0.5 * m) : rounds * it;
+    if (rounds * it > whole) continue;
+    const double m = std::min(1.0, std::pow((double)W / B, 0.2));
+    const double t = early && rounds > 1 ? it * (std::max(1.0, m * G / kTeamSlots) + m) : rounds * it;
     if (t < best_t) {
       best = W;
       best_t = t;

@@ -521,7 +521,7 @@ struct Wbp {
     tp.synw = at<uint64_t>(b.off_synw);
     tp.B1 = at<uint64_t>(b.off_B1) + (size_t)(pl.L & 1) * leaf_words;
     tp.active = at<uint64_t>(b.off_active);
-    tp.unsat = at<uint64_t>(b.off_unsat) + (size_t)(pl.L & 1) * b.G;
+    tp.unsat = at<uint64_t>(b.off_unsat) + (size_t)(pl.L & 1) * b.G * kUnsatWords;
     const int64_t per = (int64_t)kWavesPerBlock * (64 / W);
     hipLaunchKernelGGL(k_test<W>, dim3((unsigned)((c->M + per - 1) / per), b.G), dim3(kBlock), 0, st, tp);
     FinalParams fp{};
