@@ -96,6 +96,17 @@ struct PairCounts {
 
 // Derived structures for the decoder: message/leaf split, VN edge lists,
 // check classes.
+static int32_t class_types(const met_code *c, const CheckClass &k) {
+  if (k.n_msg == 0) return -1;
+  const int8_t *m = c->edge_type_msg.data() + k.first_msg, *l = c->leaf_type.data() + k.first_leaf;
+  const int64_t nm = k.n_checks * k.n_msg, nl = k.n_checks * k.n_leaf;
+  for (int64_t i = 0; i < nm; ++i)
+    if (m[i] != m[0]) return -1;
+  for (int64_t i = 0; i < nl; ++i)
+    if (l[i] != l[0] || l[i] == m[0]) return -1;
+  return m[0] | (nl ? l[0] << 8 : 0);
+}
+
 int finalize_code(met_code *c, bool skip_deg1) {
   const int64_t N = c->N, M = c->M, E = c->E;
   std::vector<int32_t> deg(N, 0);
@@ -228,6 +239,7 @@ int finalize_code(met_code *c, bool skip_deg1) {
       k.n_checks = r.count;
       k.first_msg = c->chk_msg_ptr[r.first];
       k.first_leaf = c->chk_leaf_ptr[r.first];
+      k.types = s == kShapeGeneric ? -1 : class_types(c, k);
       out.push_back(k);
     }
     return out;

@@ -417,7 +417,7 @@ __device__ __forceinline__ bool unsat_frame(const uint64_t *unsat, int g, int w)
 }
 
 struct ClassArgs {
-  int32_t shape, n_msg, n_leaf, pad;
+  int32_t shape, n_msg, n_leaf, types;  // types: as in CheckClass
   int64_t first_check, n_checks, first_msg, first_leaf;
 };
 
@@ -519,6 +519,13 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
   const bool post = MODE == M_SPECIAL && (p.flags & F_POST);
   const bool weighted = MODE == M_SPECIAL && (p.flags & F_WEIGHTED);
   const bool decide = p.flags & F_DECIDE;
+  // one scale for all message edges and one for all leaf edges, where the
+  // class has one type of each: two scalar loads for the whole wave
+  float scale_m = 1.0f, scale_l = 1.0f;
+  if (weighted && c.types >= 0) {
+    scale_m = ldro(p.weights, (int64_t)(c.types & 255) * p.wstride + (p.it - 1));
+    if (NL > 0 && decide) scale_l = ldro(p.weights, (int64_t)(c.types >> 8) * p.wstride + (p.it - 1));
+  }
   const int64_t base = (bx * kWavesPerBlock + wv) * IPW * IPWAVE;
   if (W == 64 && base >= c.n_checks) return;
 
@@ -597,9 +604,13 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
       } else {
         const float mag = phi(S[m]);
         float out = ((tot ^ (neg >> m)) & 1u) ? -mag : mag;
-        if (weighted)
-          out *= edge_scale<W>(p.weights, p.wstride, p.it - 1, p.edge_type, c.first_msg, NM, m, base + k * IPWAVE,
-                               c.n_checks, q, m0 + m);
+        if (weighted) {
+          float scale = scale_m;
+          if (c.types < 0)
+            scale = edge_scale<W>(p.weights, p.wstride, p.it - 1, p.edge_type, c.first_msg, NM, m, base + k * IPWAVE,
+                                  c.n_checks, q, m0 + m);
+          out *= scale;
+        }
         if (store) st_c2v<W, CT>(p.c2v, ((int64_t)g * p.E12 + m0 + m) * RS + w, out);
       }
     }
@@ -611,8 +622,8 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
       const int64_t le = l0 + l;
       const uint32_t neg_l = (neg >> (NM + l)) & 1u;
       const uint32_t neg_c = (tot ^ neg_l) & 1u;
-      float wt = 1.0f;
-      if (weighted)
+      float wt = scale_l;
+      if (weighted && c.types < 0)
         wt = edge_scale<W>(p.weights, p.wstride, p.it - 1, p.leaf_type, c.first_leaf, NL, l, base + k * IPWAVE,
                            c.n_checks, q, le);
       uint32_t bit;
@@ -1194,6 +1205,7 @@ inline std::vector<ClassArgs> class_args(const met_code *c) {
     a.shape = cc.shape;
     a.n_msg = cc.n_msg;
     a.n_leaf = cc.n_leaf;
+    a.types = cc.types;
     a.first_check = cc.first_check;
     a.n_checks = cc.n_checks;
     a.first_msg = cc.first_msg;

@@ -51,6 +51,9 @@ struct CheckClass {
   int32_t n_msg, n_leaf;   // per check (fixed shapes); 0 for generic
   int64_t first_check, n_checks;
   int64_t first_msg, first_leaf;  // first message / leaf edge of the run
+  // Edge types where all message edges of the run have one type and all leaf
+  // edges another (or there are none): message type | leaf type << 8, else -1.
+  int32_t types;
 };
 
 // Device copy of the adjacency (one allocation, typed views).

@@ -75,7 +75,13 @@ __device__ __forceinline__ float expm1_nonpos(float y) {
 // inputs) when NM > 0, run-time degrees (up to MET_MAX_CHECK_DEGREE) otherwise.
 constexpr int kMaxAdjDegree = 16;  // run-time-degree checks in weighted BP
 
-template <int W, int NM, int NL>
+//
+// UNI: the class has one type of message edges and another of leaf edges (every
+// class of the built profiles; ClassArgs.types), so a lane sums two values
+// instead of eight selected ones and the scales are two scalar loads.  The
+// update is bound by its arithmetic (32 frames of N = 262144: 240 MB of rows
+// are 48 us): (3,1) class 106 to 95 us, forward update 73 to 69.
+template <int W, int NM, int NL, bool UNI>
 __global__ __launch_bounds__(kBlock) void k_check_adj(const AdjParams p, const ClassArgs c) {
   constexpr bool GEN = NM == 0;
   constexpr int D = GEN ? kMaxAdjDegree : NM + NL;
@@ -102,13 +108,18 @@ __global__ __launch_bounds__(kBlock) void k_check_adj(const AdjParams p, const C
   }
   const uint32_t s = (uint32_t)(p.synw[(int64_t)g * p.M + j] >> w) & 1u;
   float A[D], gsum[D];
-  int8_t ty[D];
+  int8_t ty[UNI ? 1 : D];
+  float scale_m = 0.0f, scale_l = 0.0f;
+  if constexpr (UNI) {
+    scale_m = ldro(p.weights, (int64_t)(c.types & 255) * p.wstride + (p.it - 1));
+    if (NL > 0) scale_l = ldro(p.weights, (int64_t)(c.types >> 8) * p.wstride + (p.it - 1));
+  }
   uint32_t neg = 0, inrange = 0;
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     A[k] = 0.0f;  // absent input: no contribution to any sum
     gsum[k] = 0.0f;
-    ty[k] = 0;
+    if constexpr (!UNI) ty[k] = 0;
     if (k < nm) {
       const int64_t e = m0 + k;
       const int32_t vi = p.edge_msgvn[e];
@@ -121,14 +132,14 @@ __global__ __launch_bounds__(kBlock) void k_check_adj(const AdjParams p, const C
       neg |= sign_bit(x) << k;
       gsum[k] = p.Pbar[((int64_t)g * p.N2 + vi) * W + w] +
                 ld_stream<W>(&p.Cbar[((int64_t)g * p.E12 + e) * W + w]);
-      ty[k] = (int8_t)edge_type_of<W>(p.edge_type, e);
+      if constexpr (!UNI) ty[k] = (int8_t)edge_type_of<W>(p.edge_type, e);
     } else if (k < nm + nl) {
       const int64_t le = l0 + (k - nm);
       const float f = p.Lphi[((int64_t)g * p.EL + le) * W + w];
       A[k] = fabsf(f);
       neg |= sign_bit(f) << k;
       gsum[k] = p.gleaf ? p.gleaf[((int64_t)g * p.EL + le) * W + w] : 0.0f;
-      ty[k] = (int8_t)edge_type_of<W>(p.leaf_type, le);
+      if constexpr (!UNI) ty[k] = (int8_t)edge_type_of<W>(p.leaf_type, le);
     }
     if (!valid) gsum[k] = 0.0f;
   }
@@ -140,9 +151,10 @@ __global__ __launch_bounds__(kBlock) void k_check_adj(const AdjParams p, const C
   suf[D - 1] = 0.0f;
 #pragma unroll
   for (int k = D - 2; k >= 0; --k) suf[k] = suf[k + 1] + A[k + 1];
-  float acc[kMaxT];
+  constexpr int NACC = UNI ? 2 : kMaxT;  // sums of the message and leaf edges, or of each type
+  float acc[NACC];
 #pragma unroll
-  for (int t = 0; t < kMaxT; ++t) acc[t] = 0.0f;
+  for (int t = 0; t < NACC; ++t) acc[t] = 0.0f;
   float Q[D];  // Rbar_e * sgn(R_e)
 #pragma unroll
   for (int k = 0; k < D; ++k) {
@@ -151,9 +163,15 @@ __global__ __launch_bounds__(kBlock) void k_check_adj(const AdjParams p, const C
       const float R = phi(pre[k] + suf[k]);
       const bool rneg = (tot ^ (neg >> k)) & 1u;
       const float contrib = gsum[k] * (rneg ? -R : R);
+      float wt;
+      if constexpr (UNI) {
+        acc[k < NM ? 0 : 1] += contrib;
+        wt = k < NM ? scale_m : scale_l;
+      } else {
 #pragma unroll
-      for (int t = 0; t < kMaxT; ++t) acc[t] += (ty[k] == t) ? contrib : 0.0f;
-      const float wt = p.weights[(int64_t)ty[k] * p.wstride + (p.it - 1)];
+        for (int t = 0; t < kMaxT; ++t) acc[t] += (ty[k] == t) ? contrib : 0.0f;
+        wt = p.weights[(int64_t)ty[k] * p.wstride + (p.it - 1)];
+      }
       const float rbar = gsum[k] * wt;
       Q[k] = rneg ? -rbar : rbar;
     }
@@ -199,7 +217,17 @@ __global__ __launch_bounds__(kBlock) void k_check_adj(const AdjParams p, const C
   // its sum (10 exchanges instead of 6 per type).
   static_assert(kMaxT == 8, "exchange pattern assumes 8 types over 64 lanes");
   __shared__ float red[kWavesPerBlock][kMaxT];
-  {
+  if constexpr (UNI) {
+    // the same sums: the halves of the wave take one of the two values each
+    const bool h32 = lane & 32;
+    float v = NL == 0 ? acc[0] + __shfl_xor(acc[0], 32)
+                      : (h32 ? acc[1] : acc[0]) + __shfl_xor(h32 ? acc[0] : acc[1], 32);
+#pragma unroll
+    for (int off = 16; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+    const float vm = __shfl(v, 0), vl = __shfl(v, 32);
+    if (lane < kMaxT)
+      red[threadIdx.x >> 6][lane] = lane == (c.types & 255) ? vm : NL > 0 && lane == (c.types >> 8) ? vl : 0.0f;
+  } else {
     float v4[4], v2[2];
     const bool h32 = lane & 32, h16 = lane & 16, h8 = lane & 8;
 #pragma unroll
@@ -288,7 +316,17 @@ __global__ __launch_bounds__(kBlock) void k_reduce_wgrad(const float *partial, i
                                                          int32_t ntypes, int32_t wstride, int32_t it) {
   const int t = threadIdx.x >> 5, lane = threadIdx.x & 31;
   float v = 0.0f;
-  for (int64_t r = lane; r < rows; r += 32) v += partial[r * kMaxT + t];
+  int64_t r = lane;
+  // one block, bound by the loads' latency: eight under way at a time, added in
+  // row order
+  for (; r + 7 * 32 < rows; r += 8 * 32) {
+    float a[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) a[u] = partial[(r + u * 32) * kMaxT + t];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v += a[u];
+  }
+  for (; r < rows; r += 32) v += partial[r * kMaxT + t];
   for (int off = 16; off >= 1; off >>= 1) v += __shfl_xor(v, off, 32);
   if (lane == 0 && t < ntypes) grad[(int64_t)t * wstride + (it - 1)] = v;
 }
@@ -552,15 +590,18 @@ struct Wbp {
   template <int W>
   void launch_adj(const AdjParams &p, const ClassArgs &a, unsigned blocks) {
     const dim3 grid(blocks, pl.base.G), block(kBlock);
+    auto go = [&](auto uniform, auto mixed) {
+      hipLaunchKernelGGL(a.types >= 0 ? uniform : mixed, grid, block, 0, st, p, a);
+    };
     switch (a.shape) {
-      case 0: hipLaunchKernelGGL((k_check_adj<W, 3, 1>), grid, block, 0, st, p, a); break;
-      case 1: hipLaunchKernelGGL((k_check_adj<W, 2, 1>), grid, block, 0, st, p, a); break;
-      case 2: hipLaunchKernelGGL((k_check_adj<W, 12, 0>), grid, block, 0, st, p, a); break;
-      case 3: hipLaunchKernelGGL((k_check_adj<W, 11, 0>), grid, block, 0, st, p, a); break;
-      case 4: hipLaunchKernelGGL((k_check_adj<W, 6, 0>), grid, block, 0, st, p, a); break;
-      case 5: hipLaunchKernelGGL((k_check_adj<W, 5, 0>), grid, block, 0, st, p, a); break;
-      case 6: hipLaunchKernelGGL((k_check_adj<W, 4, 0>), grid, block, 0, st, p, a); break;
-      default: hipLaunchKernelGGL((k_check_adj<W, 0, 0>), grid, block, 0, st, p, a); break;
+      case 0: go(k_check_adj<W, 3, 1, true>, k_check_adj<W, 3, 1, false>); break;
+      case 1: go(k_check_adj<W, 2, 1, true>, k_check_adj<W, 2, 1, false>); break;
+      case 2: go(k_check_adj<W, 12, 0, true>, k_check_adj<W, 12, 0, false>); break;
+      case 3: go(k_check_adj<W, 11, 0, true>, k_check_adj<W, 11, 0, false>); break;
+      case 4: go(k_check_adj<W, 6, 0, true>, k_check_adj<W, 6, 0, false>); break;
+      case 5: go(k_check_adj<W, 5, 0, true>, k_check_adj<W, 5, 0, false>); break;
+      case 6: go(k_check_adj<W, 4, 0, true>, k_check_adj<W, 4, 0, false>); break;
+      default: hipLaunchKernelGGL((k_check_adj<W, 0, 0, false>), grid, block, 0, st, p, a); break;
     }
   }
 
