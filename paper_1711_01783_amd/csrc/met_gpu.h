@@ -256,13 +256,25 @@ __device__ __forceinline__ float ld_c2v(const float *base, int64_t i) {
   return ld_msg<W, CT>(reinterpret_cast<const CT *>(base) + i);
 }
 template <int W, typename CT>
-__device__ __forceinline__ void st_c2v(float *base, int64_t i, float v) {
+__device__ __forceinline__ void st_msg(CT *p, float v) {
   if constexpr (std::is_class<CT>::value) {
     const CT q(v);
-    st_stream<W>(q.c, reinterpret_cast<uint8_t *>(base) + i);
+    st_stream<W>(q.c, reinterpret_cast<uint8_t *>(p));
   } else {
-    st_stream<W>((CT)v, reinterpret_cast<CT *>(base) + i);
+    st_stream<W>((CT)v, p);
   }
+}
+template <int W, typename CT>
+__device__ __forceinline__ void st_c2v(float *base, int64_t i, float v) {
+  st_msg<W, CT>(reinterpret_cast<CT *>(base) + i, v);
+}
+
+// p moved by a 32-bit number of bytes: with a scalar p the offset goes into the
+// load or store itself.
+template <typename T>
+__device__ __forceinline__ T *at_bytes(T *p, uint32_t bytes) {
+  using byte = std::conditional_t<std::is_const_v<T>, const char, char>;
+  return reinterpret_cast<T *>(reinterpret_cast<byte *>(p) + bytes);
 }
 
 enum : int32_t {
@@ -290,12 +302,18 @@ constexpr float kLn2 = 0.69314718055994531f;
 constexpr float kLog2e = 1.4426950408889634f;
 
 __device__ __forceinline__ float phi(float x) {
+  // the leading coefficients in registers of their own: an fma has room for one
+  // literal, so the compiler would move one of them in for each phi
+  float p3 = kP3, q3 = 2.0f * kQ3;
+  asm("" : "+v"(p3));
+  asm("" : "+v"(q3));
   const float z = x * x;
-  const float ps = z * fmaf(z, fmaf(z, fmaf(z, kP3, kP2), kP1), kP0);
+  const float ps = z * fmaf(z, fmaf(z, fmaf(z, p3, kP2), kP1), kP0);
   const float lo = fmaf(-kLn2, __builtin_amdgcn_logf(x), kLn2) + ps;
   const float u = __builtin_amdgcn_exp2f(-x * kLog2e);
   const float v = u * u;
-  const float hi = 2.0f * u * fmaf(v, fmaf(v, fmaf(v, fmaf(v, kQ3, kQ2), kQ1), kQ0), 1.0f);
+  // (twice the polynomial, exactly: its coefficients doubled)
+  const float hi = u * fmaf(v, fmaf(v, fmaf(v, fmaf(v, q3, 2.0f * kQ2), 2.0f * kQ1), 2.0f * kQ0), 2.0f);
   return x < 1.0f ? lo : hi;
 }
 
@@ -454,6 +472,27 @@ __device__ __forceinline__ uint32_t leaf_bit(uint32_t neg_l, uint32_t neg_c, flo
   return 0u;
 }
 
+// The same with the signs as conditions, which are scalar lane masks.
+__device__ __forceinline__ bool leaf_cond(bool neg_l, bool neg_c, float S, float A) {
+  const bool decided = !(isinf(A) & isinf(S));
+  return (neg_l & neg_c & decided) | ((neg_l != neg_c) & (((S < A) & neg_c) | ((S > A) & neg_l)));
+}
+
+// A word that every lane of the wave holds, in scalar registers.
+__device__ __forceinline__ uint64_t wave_word(uint64_t x) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+  return (uint64_t)hi << 32 | lo;
+}
+
+// Bit w of a word of one bit per frame, as a sign bit.  A word of 64 frames is
+// the same for the whole wave, so it serves as the lanes' condition itself.
+template <int W>
+__device__ __forceinline__ uint32_t frame_sign(uint64_t word, int w) {
+  if constexpr (W == 64) return __builtin_amdgcn_inverse_ballot_w64(word) ? 0x80000000u : 0u;
+  return (uint32_t)word << (31 - w);
+}
+
 // Writes the W leaf decisions of one item, keeping the stored bits of frames
 // that are no longer active.
 template <int W>
@@ -509,7 +548,7 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
     tab_a = s_a;
     tab_out = s_out;
   }
-  const uint64_t act = p.active[g];  // not written during check updates
+  const uint64_t act = ld_word<PERSIST>(p.active, g);  // not written during check updates
   if (act == 0ull) return;
   const int lane = threadIdx.x & 63, wv = wave_id();
   const int w = lane % W, q = lane / W;
@@ -529,58 +568,120 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
   const int64_t base = (bx * kWavesPerBlock + wv) * IPW * IPWAVE;
   if (W == 64 && base >= c.n_checks) return;
 
-  int64_t item[IPW];
+  // Rows are addressed by scalar pointers to the wave's first check of a step
+  // plus 32-bit byte offsets of the lane's own (lane group q has the q-th).
+  int64_t first_item[IPW];
+  uint32_t own[IPW];
   bool valid[IPW];
   float pv[IPW][NM > 0 ? NM : 1], cv[IPW][NM > 0 ? NM : 1], lf[IPW][NL > 0 ? NL : 1];
   uint64_t sw[IPW], b1[IPW][NL > 0 ? NL : 1];
 #pragma unroll
   for (int k = 0; k < IPW; ++k) {
-    const int64_t i = base + k * IPWAVE + q;
-    valid[k] = i < c.n_checks;
-    item[k] = valid[k] ? i : 0;
+    const int64_t left = c.n_checks - (base + k * IPWAVE);  // lanes past the last check read a valid one
+    first_item[k] = left > 0 ? base + k * IPWAVE : 0;
+    valid[k] = W == 64 ? left > 0 : q < (int)(left < IPWAVE ? left : IPWAVE);
+    own[k] = W < 64 && valid[k] ? (uint32_t)q : 0u;
   }
-  // loads: P gathers, c2v rows, leaf inputs, syndrome and previous decisions
+  const float *Pg = p.Pin + (int64_t)g * p.N2 * RS;
+  // All loads before any arithmetic, and those that wait for nothing first: the
+  // gathers of P wait for their indices, and a branch in between (on the
+  // iteration, on the test) would make them wait for every row before it.
+  // Iteration 1 of the special mode reads rows whose values it drops.  32 frames
+  // per row, N = 262144: decode 58.9 to 50.2 us a launch, weighted 69.4 to 61.7;
+  // half-used rows of N = 10^6 199 to 181.  (With a wave per check the indices
+  // are scalar and the order does not matter; 8-bit messages with the lookup
+  // table take 2 % more.)
+  const CT *c_in = reinterpret_cast<const CT *>(MODE == M_SPECIAL && first ? p.c2v : p.c2v_in);
+  int32_t vi[IPW][NM > 0 ? NM : 1];
+  auto gather = [&](int k, int m) {
+    pv[k][m] = at_bytes(Pg, w * (uint32_t)sizeof(float))[(uint64_t)(uint32_t)vi[k][m] * RS];
+  };
 #pragma unroll
   for (int k = 0; k < IPW; ++k) {
-    const int64_t m0 = c.first_msg + item[k] * NM, l0 = c.first_leaf + item[k] * NL;
-    sw[k] = ldro(p.synw, (int64_t)g * p.M + c.first_check + item[k]);
+    const int64_t m0 = c.first_msg + first_item[k] * NM, l0 = c.first_leaf + first_item[k] * NL;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) vi[k][m] = ldro(p.edge_msgvn + m0, own[k] * NM + m);
+    sw[k] = ldro(p.synw + ((int64_t)g * p.M + c.first_check + first_item[k]), own[k]);
+    const CT *c_rows = c_in + ((int64_t)g * p.E12 + m0) * RS;
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
-      const int32_t vi = ldro(p.edge_msgvn, m0 + m);
-      pv[k][m] = p.Pin[((int64_t)g * p.N2 + vi) * RS + w];
-      cv[k][m] = first ? 0.0f : ld_c2v<W, CT>(p.c2v_in, ((int64_t)g * p.E12 + m0 + m) * RS + w);
+      if constexpr (W == 64) gather(k, m);  // (scalar indices)
+      cv[k][m] = 0.0f;
+      if constexpr (MODE != M_FIRST)
+        cv[k][m] = ld_msg<W, CT>(at_bytes(c_rows + m * RS, (own[k] * (NM * RS) + w) * (uint32_t)sizeof(CT)));
     }
+    const float *l_rows = p.Lphi + ((int64_t)g * p.EL + l0) * RS;
+#pragma unroll
+    for (int l = 0; l < NL; ++l)
+      lf[k][l] = ld_stream<W>(at_bytes(l_rows + l * RS, (own[k] * (NL * RS) + w) * (uint32_t)sizeof(float)));
+  }
+  if constexpr (W < 64)
+#pragma unroll
+    for (int k = 0; k < IPW; ++k)
+#pragma unroll
+      for (int m = 0; m < NM; ++m) gather(k, m);
+#pragma unroll
+  for (int k = 0; k < IPW; ++k) {
+    const int64_t l0 = c.first_leaf + first_item[k] * NL;
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
-      lf[k][l] = ld_stream<W>(&p.Lphi[((int64_t)g * p.EL + l0 + l) * RS + w]);
-      b1[k][l] = test ? ld_word<PERSIST>(p.B1in, (int64_t)g * p.EL + l0 + l) : 0ull;
+      b1[k][l] = 0ull;
+      if (test) b1[k][l] = ld_word<PERSIST>(p.B1in + ((int64_t)g * p.EL + l0), own[k] * NL + l);
+      if constexpr (PERSIST && W == 64) b1[k][l] = wave_word(b1[k][l]);
     }
   }
+  if (MODE == M_SPECIAL && first)
+#pragma unroll
+    for (int k = 0; k < IPW; ++k)
+#pragma unroll
+      for (int m = 0; m < NM; ++m) cv[k][m] = 0.0f;
+  // The update is bound by its arithmetic (6 phis of 19 instructions for a
+  // (3,1) check), so the rest is kept short: signs stay in the top bits of the
+  // inputs, and with a wave per check the parities of a test are words of lane
+  // bits on the scalar unit.
+  uint64_t bad_word = 0;
   uint32_t bad = 0;
 #pragma unroll
   for (int k = 0; k < IPW; ++k) {
-    const int64_t m0 = c.first_msg + item[k] * NM, l0 = c.first_leaf + item[k] * NL;
-    const uint32_t s = (uint32_t)(sw[k] >> w) & 1u;
+    const int64_t m0 = c.first_msg + first_item[k] * NM, l0 = c.first_leaf + first_item[k] * NL;
+    CT *c_rows = reinterpret_cast<CT *>(p.c2v) + ((int64_t)g * p.E12 + m0) * RS;
+    const uint32_t c_own = (own[k] * (NM * RS) + w) * (uint32_t)sizeof(CT);
     float A[D];
-    uint32_t neg = 0, parity = s;
+    uint32_t sgn[D], tot = frame_sign<W>(sw[k], w);  // top bits
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
-      parity ^= (uint32_t)(pv[k][m] < 0.0f);
       const float x = clamp_llr(pv[k][m] - cv[k][m]);
       if constexpr (lut)
         A[m] = tab_a[lut_index(fabsf(x))];
       else
         A[m] = phi(fabsf(x));
-      neg |= sign_bit(x) << m;
+      sgn[m] = __float_as_uint(x);
+      tot ^= sgn[m];
     }
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
       A[NM + l] = fabsf(lf[k][l]);
-      neg |= sign_bit(lf[k][l]) << (NM + l);
-      parity ^= (uint32_t)(b1[k][l] >> w) & 1u;
+      sgn[NM + l] = __float_as_uint(lf[k][l]);
+      tot ^= sgn[NM + l];
     }
-    if (test) bad |= parity & (uint32_t)(valid[k] && lane_act);
-    const uint32_t tot = (__popc(neg) & 1u) ^ s;
+    if (test) {
+      if constexpr (W == 64) {
+        uint64_t parity = sw[k];
+#pragma unroll
+        for (int m = 0; m < NM; ++m) parity ^= __ballot(pv[k][m] < 0.0f);
+#pragma unroll
+        for (int l = 0; l < NL; ++l) parity ^= b1[k][l];
+        if (valid[k]) bad_word |= parity;
+      } else {
+        uint64_t word = sw[k];
+#pragma unroll
+        for (int l = 0; l < NL; ++l) word ^= b1[k][l];
+        uint32_t parity = (uint32_t)word >> w;
+#pragma unroll
+        for (int m = 0; m < NM; ++m) parity ^= (uint32_t)(pv[k][m] < 0.0f);
+        bad |= valid[k] ? parity : 0u;
+      }
+    }
     // leave-one-out sums S[m] = sum of A over the other inputs, from prefix
     // and suffix sums (no subtraction; no additions of zero)
     float pre[D], suf[D], S[D];
@@ -598,20 +699,20 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
       if constexpr (lut) {
-        const uint32_t code = tab_out[lut_index(S[m])] | (((tot ^ (neg >> m)) & 1u) << 7);
+        const uint32_t code = tab_out[lut_index(S[m])] | (((tot ^ sgn[m]) >> 24) & 0x80u);
         if (store)
-          st_stream<W>((uint8_t)code, reinterpret_cast<uint8_t *>(p.c2v) + ((int64_t)g * p.E12 + m0 + m) * RS + w);
+          st_stream<W>((uint8_t)code, at_bytes(reinterpret_cast<uint8_t *>(c_rows + m * RS), c_own));
       } else {
         const float mag = phi(S[m]);
-        float out = ((tot ^ (neg >> m)) & 1u) ? -mag : mag;
+        float out = __uint_as_float(__float_as_uint(mag) | ((tot ^ sgn[m]) & 0x80000000u));
         if (weighted) {
           float scale = scale_m;
           if (c.types < 0)
             scale = edge_scale<W>(p.weights, p.wstride, p.it - 1, p.edge_type, c.first_msg, NM, m, base + k * IPWAVE,
-                                  c.n_checks, q, m0 + m);
+                                  c.n_checks, q, m0 + own[k] * NM + m);
           out *= scale;
         }
-        if (store) st_c2v<W, CT>(p.c2v, ((int64_t)g * p.E12 + m0 + m) * RS + w, out);
+        if (store) st_msg<W, CT>(at_bytes(c_rows + m * RS, c_own), out);
       }
     }
     // Leaf decisions (and posteriors) only where somebody reads them: every
@@ -619,31 +720,32 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
     if (!decide) continue;
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
-      const int64_t le = l0 + l;
-      const uint32_t neg_l = (neg >> (NM + l)) & 1u;
-      const uint32_t neg_c = (tot ^ neg_l) & 1u;
+      const int64_t le = l0 + own[k] * NL + l;
+      const bool neg_l = (int32_t)sgn[NM + l] < 0;
+      const bool neg_c = (int32_t)(tot ^ sgn[NM + l]) < 0;
       float wt = scale_l;
       if (weighted && c.types < 0)
         wt = edge_scale<W>(p.weights, p.wstride, p.it - 1, p.leaf_type, c.first_leaf, NL, l, base + k * IPWAVE,
                            c.n_checks, q, le);
-      uint32_t bit;
+      bool bit;
       if (wt == 1.0f) {
-        bit = leaf_bit(neg_l, neg_c, S[NM + l], A[NM + l]);
+        bit = leaf_cond(neg_l, neg_c, S[NM + l], A[NM + l]);
       } else {
         const float lr = p.Lraw[((int64_t)g * p.EL + le) * RS + w];
         const float mag = phi(S[NM + l]);
-        bit = (uint32_t)(lr + wt * (neg_c ? -mag : mag) < 0.0f);
+        bit = lr + wt * (neg_c ? -mag : mag) < 0.0f;
       }
       if (post && store && lane_act) {
         const float lr = p.Lraw[((int64_t)g * p.EL + le) * RS + w];
         const float mag = phi(S[NM + l]);
         p.P1[((int64_t)g * p.EL + le) * RS + w] = lr + wt * (neg_c ? -mag : mag);
       }
-      const uint64_t ball = __ballot((int)(bit & (uint32_t)valid[k]));
+      const uint64_t ball = __ballot(bit && valid[k]);
       if (w == 0 && valid[k]) store_leaf_word<W>(p.B1out + (int64_t)g * p.EL + le, ball, q, act);
     }
   }
-  if (test) flag_unsat(p.unsat, g, w, bad);
+  if constexpr (W == 64) bad = (uint32_t)__builtin_amdgcn_inverse_ballot_w64(bad_word);
+  if (test) flag_unsat(p.unsat, g, w, lane_act ? bad & 1u : 0u);
 }
 
 template <int W, int NM, int NL, int MODE, int IPW, typename CT = float, int RS = W>
@@ -769,6 +871,7 @@ struct ClassSet {
   int32_t n, lead_block;  // classes; first block of the last class, a multiple of 8
   int32_t block0[kMaxClasses];
   ClassArgs c[kMaxClasses];
+  ClassArgs lead;  // the last class
 };
 
 template <int W, int MODE, int IPW, typename CT = float, int RS = W>
@@ -776,7 +879,7 @@ __global__ __launch_bounds__(kBlock) void k_check_set(const CheckParams p, const
   if ((int)blockIdx.x >= set.lead_block) {
     const GridTile t = MODE == M_SPECIAL ? GridTile{(int64_t)blockIdx.x - set.lead_block, (int)blockIdx.y}
                                          : xcd_grid_tile(set.lead_block);
-    check_fixed_body<W, 3, 1, MODE, IPW, false, CT, RS>(p, set.c[set.n - 1], t.bx, t.g);
+    check_fixed_body<W, 3, 1, MODE, IPW, false, CT, RS>(p, set.lead, t.bx, t.g);
     return;
   }
   int k = 0;
@@ -1158,7 +1261,7 @@ void launch_fixed_ipw(int ipw, int shape, unsigned blocks, int G, hipStream_t st
   else if (W == 64 && ipw == 2)
     launch_fixed<W, MODE, (W == 64 ? 2 : 1)>(shape, blocks, G, st, p, c);
   else
-    launch_fixed<W, MODE, 1>(shape, blocks, G, st, p, c);
+    launch_fixed<W, MODE, (W == 32 ? 2 : 1)>(shape, blocks, G, st, p, c);
 }
 
 // One check-kernel launch over a class: compiled shape (mode, steps per wave)
@@ -1169,7 +1272,8 @@ void launch_check(const CheckParams &p, const ClassArgs &a, int mode, int cn_ipw
   constexpr bool half = !std::is_same<CT, float>::value;  // half or 8-bit storage
   static_assert(!half || RS == 64, "reduced message storage needs groups of 64 frames");
   const bool gen = a.shape == kShapeGeneric;
-  const int ipw = gen ? 1 : RS != W ? kSqueezeSteps : W == 64 ? (half ? 4 : cn_ipw) : 1;
+  // (32 frames per row: two steps share a wave's chain of scalar loads)
+  const int ipw = gen ? 1 : RS != W ? kSqueezeSteps : W == 64 ? (half ? 4 : cn_ipw) : W == 32 ? 2 : 1;
   const int64_t per_block = (int64_t)kWavesPerBlock * ipw * (64 / W);
   const unsigned blocks = (unsigned)((a.n_checks + per_block - 1) / per_block);
   if (gen)
@@ -1223,7 +1327,7 @@ template <int W, typename CT, int RS>
 void launch_checks(const CheckParams &p, const std::vector<ClassArgs> &classes, int mode, int cn_ipw, int G,
                    hipStream_t st, const char *name) {
   constexpr bool half = !std::is_same<CT, float>::value;
-  const int ipw = RS != W ? kSqueezeSteps : W == 64 ? (half ? 4 : cn_ipw) : 1;
+  const int ipw = RS != W ? kSqueezeSteps : W == 64 ? (half ? 4 : cn_ipw) : W == 32 ? 2 : 1;
   const ClassArgs *lead = nullptr;
   int n_fixed = 0;
   for (const ClassArgs &a : classes)
@@ -1255,7 +1359,8 @@ void launch_checks(const CheckParams &p, const std::vector<ClassArgs> &classes, 
     blocks = (blocks + kXcds - 1) / kXcds * kXcds;
     set.lead_block = (int32_t)blocks;
     set.block0[set.n] = (int32_t)blocks;
-    set.c[set.n++] = *lead;
+    ++set.n;
+    set.lead = *lead;
     const int64_t per = (int64_t)kWavesPerBlock * ipw * (64 / W);
     const unsigned nb = (unsigned)(blocks + (lead->n_checks + per - 1) / per);
     ScopedTimer t(st, name ? name : "k_check_set");
@@ -1264,7 +1369,7 @@ void launch_checks(const CheckParams &p, const std::vector<ClassArgs> &classes, 
       go(k_check_set<W, M_MAIN, kSqueezeSteps, CT, RS>);
     } else {
       // (reduced storage is compiled with 4 steps per wave only)
-      constexpr int i4 = W == 64 ? 4 : 1, i2 = W == 64 && !half ? 2 : i4, i1 = half ? i4 : 1;
+      constexpr int i4 = W == 64 ? 4 : W == 32 ? 2 : 1, i2 = W == 64 && !half ? 2 : i4, i1 = half || W == 32 ? i4 : 1;
       if (mode == M_SPECIAL)
         ipw == 4 ? go(k_check_set<W, M_SPECIAL, i4, CT>) : ipw == 2 ? go(k_check_set<W, M_SPECIAL, i2, CT>) : go(k_check_set<W, M_SPECIAL, i1, CT>);
       else if (mode == M_FIRST)

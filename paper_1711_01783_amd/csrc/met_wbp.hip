@@ -80,7 +80,8 @@ constexpr int kMaxAdjDegree = 16;  // run-time-degree checks in weighted BP
 // class of the built profiles; ClassArgs.types), so a lane sums two values
 // instead of eight selected ones and the scales are two scalar loads.  The
 // update is bound by its arithmetic (32 frames of N = 262144: 240 MB of rows
-// are 48 us): (3,1) class 106 to 95 us, forward update 73 to 69.
+// are 48 us): (3,1) class 106 to 95 us, forward update 73 to 69; then 95 to 84
+// with all loads ahead of the first use and no branch between them.
 template <int W, int NM, int NL, bool UNI>
 __global__ __launch_bounds__(kBlock) void k_check_adj(const AdjParams p, const ClassArgs c) {
   constexpr bool GEN = NM == 0;
@@ -115,6 +116,36 @@ __global__ __launch_bounds__(kBlock) void k_check_adj(const AdjParams p, const C
     if (NL > 0) scale_l = ldro(p.weights, (int64_t)(c.types >> 8) * p.wstride + (p.it - 1));
   }
   uint32_t neg = 0, inrange = 0;
+  // Compiled shapes: all loads first, without branches, those that wait for no
+  // index ahead of the gathers (iteration 1 and all but the last read rows
+  // whose values they drop: the adjoint's own, the leaf inputs).
+  float pv_[D], cv_[D], cb_[D], pb_[D], lf_[D], gl_[D];
+  if constexpr (!GEN) {
+    const float *c_in = p.first ? p.Cbar : p.c2v_in, *gl_in = p.gleaf ? p.gleaf : p.Lphi;
+    int32_t vi[NM];
+#pragma unroll
+    for (int k = 0; k < NM; ++k) vi[k] = ldro(p.edge_msgvn, m0 + k);
+#pragma unroll
+    for (int k = 0; k < NM; ++k) {
+      cv_[k] = ld_stream<W>(&c_in[((int64_t)g * p.E12 + m0 + k) * W + w]);
+      cb_[k] = ld_stream<W>(&p.Cbar[((int64_t)g * p.E12 + m0 + k) * W + w]);
+    }
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+      lf_[NM + l] = p.Lphi[((int64_t)g * p.EL + l0 + l) * W + w];
+      gl_[NM + l] = gl_in[((int64_t)g * p.EL + l0 + l) * W + w];
+    }
+#pragma unroll
+    for (int k = 0; k < NM; ++k) {
+      const uint64_t row = ((uint64_t)((int64_t)g * p.N2) + (uint32_t)vi[k]) * W + w;
+      pv_[k] = p.Pin[row];
+      pb_[k] = p.Pbar[row];
+    }
+#pragma unroll
+    for (int k = 0; k < NM; ++k) cv_[k] = p.first ? 0.0f : cv_[k];
+#pragma unroll
+    for (int l = 0; l < NL; ++l) gl_[NM + l] = p.gleaf ? gl_[NM + l] : 0.0f;
+  }
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     A[k] = 0.0f;  // absent input: no contribution to any sum
@@ -122,23 +153,36 @@ __global__ __launch_bounds__(kBlock) void k_check_adj(const AdjParams p, const C
     if constexpr (!UNI) ty[k] = 0;
     if (k < nm) {
       const int64_t e = m0 + k;
-      const int32_t vi = p.edge_msgvn[e];
-      const float pv = p.Pin[((int64_t)g * p.N2 + vi) * W + w];
-      const float cv = p.first ? 0.0f : ld_stream<W>(&p.c2v_in[((int64_t)g * p.E12 + e) * W + w]);
+      float pv, cv;
+      if constexpr (GEN) {
+        const int32_t vi = p.edge_msgvn[e];
+        pv = p.Pin[((int64_t)g * p.N2 + vi) * W + w];
+        cv = p.first ? 0.0f : ld_stream<W>(&p.c2v_in[((int64_t)g * p.E12 + e) * W + w]);
+        pb_[k] = p.Pbar[((int64_t)g * p.N2 + vi) * W + w];
+        cb_[k] = ld_stream<W>(&p.Cbar[((int64_t)g * p.E12 + e) * W + w]);
+      } else {
+        pv = pv_[k];
+        cv = cv_[k];
+      }
       const float v = pv - cv;
       inrange |= (uint32_t)(fabsf(v) < kLlrMax) << k;
       const float x = clamp_llr(v);
       A[k] = phi(fabsf(x));
       neg |= sign_bit(x) << k;
-      gsum[k] = p.Pbar[((int64_t)g * p.N2 + vi) * W + w] +
-                ld_stream<W>(&p.Cbar[((int64_t)g * p.E12 + e) * W + w]);
+      gsum[k] = pb_[k] + cb_[k];
       if constexpr (!UNI) ty[k] = (int8_t)edge_type_of<W>(p.edge_type, e);
     } else if (k < nm + nl) {
       const int64_t le = l0 + (k - nm);
-      const float f = p.Lphi[((int64_t)g * p.EL + le) * W + w];
+      float f;
+      if constexpr (GEN) {
+        f = p.Lphi[((int64_t)g * p.EL + le) * W + w];
+        gl_[k] = p.gleaf ? p.gleaf[((int64_t)g * p.EL + le) * W + w] : 0.0f;
+      } else {
+        f = lf_[k];
+      }
       A[k] = fabsf(f);
       neg |= sign_bit(f) << k;
-      gsum[k] = p.gleaf ? p.gleaf[((int64_t)g * p.EL + le) * W + w] : 0.0f;
+      gsum[k] = gl_[k];
       if constexpr (!UNI) ty[k] = (int8_t)edge_type_of<W>(p.leaf_type, le);
     }
     if (!valid) gsum[k] = 0.0f;
