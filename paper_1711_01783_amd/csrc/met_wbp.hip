@@ -83,14 +83,14 @@ constexpr int kMaxAdjDegree = 16;  // run-time-degree checks in weighted BP
 // are 48 us): (3,1) class 106 to 95 us, forward update 73 to 69; then 95 to 84
 // with all loads ahead of the first use and no branch between them.
 template <int W, int NM, int NL, bool UNI>
-__global__ __launch_bounds__(kBlock) void k_check_adj(const AdjParams p, const ClassArgs c) {
+__device__ __forceinline__ void check_adj_body(const AdjParams &p, const ClassArgs &c, int64_t bx, int64_t row) {
   constexpr bool GEN = NM == 0;
   constexpr int D = GEN ? kMaxAdjDegree : NM + NL;
   constexpr int UNR = GEN ? 1 : D;  // compiled shapes unroll fully
   const int g = blockIdx.y;
   const int lane = threadIdx.x & 63, wv = wave_id();
   const int w = lane % W, q = lane / W;
-  const int64_t i = ((int64_t)blockIdx.x * kWavesPerBlock + wv) * (64 / W) + q;
+  const int64_t i = (bx * kWavesPerBlock + wv) * (64 / W) + q;
   const bool valid = i < c.n_checks;
   const int64_t item = valid ? i : 0;
   const int64_t j = c.first_check + item;
@@ -290,7 +290,50 @@ __global__ __launch_bounds__(kBlock) void k_check_adj(const AdjParams p, const C
   if (threadIdx.x < kMaxT) {
     float v = 0.0f;
     for (int k = 0; k < kWavesPerBlock; ++k) v += red[k][threadIdx.x];
-    p.partial[(p.partial_base + (int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kMaxT + threadIdx.x] = v;
+    p.partial[row * kMaxT + threadIdx.x] = v;
+  }
+}
+
+template <int W, int NM, int NL, bool UNI>
+__global__ __launch_bounds__(kBlock) void k_check_adj(const AdjParams p, const ClassArgs c) {
+  check_adj_body<W, NM, NL, UNI>(p, c, blockIdx.x, p.partial_base + (int64_t)blockIdx.y * gridDim.x + blockIdx.x);
+}
+
+// The classes of compiled shapes but the largest in one launch: each lasts 5-14
+// us however few its checks are (32 frames of N = 262144: 14.2 + 6.6 + 4.8 us
+// apart, 14.8 together; training step 13.3 to 12.5 ms).  The largest keeps a launch of its own: beside the wide
+// bodies' 120 registers it would have half of its waves in flight.
+struct AdjSet {
+  int32_t n;
+  int32_t block0[kMaxClasses + 1];  // first block of each class, and the end
+  int64_t row[kMaxClasses];         // first partial row of each class
+  ClassArgs c[kMaxClasses];
+};
+
+template <int W>
+__global__ __launch_bounds__(kBlock) void k_check_adj_set(const AdjParams p, const AdjSet set) {
+  int k = 0;
+  while (k + 1 < set.n && (int)blockIdx.x >= set.block0[k + 1]) ++k;
+  const ClassArgs &c = set.c[k];
+  const int64_t bx = (int64_t)blockIdx.x - set.block0[k];
+  const int64_t row = set.row[k] + (int64_t)blockIdx.y * (set.block0[k + 1] - set.block0[k]) + bx;
+  auto go = [&](auto nm, auto nl) {
+    if (c.types >= 0)
+      check_adj_body<W, decltype(nm)::value, decltype(nl)::value, true>(p, c, bx, row);
+    else
+      check_adj_body<W, decltype(nm)::value, decltype(nl)::value, false>(p, c, bx, row);
+  };
+  using std::integral_constant;
+  constexpr integral_constant<int, 0> n0{};
+  constexpr integral_constant<int, 1> n1{};
+  switch (c.shape) {
+    case 0: go(integral_constant<int, 3>{}, n1); break;
+    case 1: go(integral_constant<int, 2>{}, n1); break;
+    case 2: go(integral_constant<int, 12>{}, n0); break;
+    case 3: go(integral_constant<int, 11>{}, n0); break;
+    case 4: go(integral_constant<int, 6>{}, n0); break;
+    case 5: go(integral_constant<int, 5>{}, n0); break;
+    default: go(integral_constant<int, 4>{}, n0); break;
   }
 }
 
@@ -699,6 +742,14 @@ struct Wbp {
     vp.Pbar = pbar;
     const std::vector<ClassArgs> classes = class_args(c);
     const int64_t per = (int64_t)kWavesPerBlock * (64 / W);
+    const ClassArgs *lead = nullptr;
+    int n_fixed = 0;
+    for (const ClassArgs &a : classes)
+      if (a.shape != kShapeGeneric) {
+        ++n_fixed;
+        if (!lead || a.n_checks > lead->n_checks) lead = &a;
+      }
+    const bool merged = n_fixed > 2;  // at least two classes beside the largest
     const int nsegs = (pl.L + pl.k - 1) / pl.k;
     for (int sg = nsegs - 1; sg >= 0; --sg) {
       const int a = sg * pl.k, bnd = std::min(a + pl.k, pl.L);
@@ -720,12 +771,21 @@ struct Wbp {
         int64_t row = 0;
         {
           ScopedTimer t(st, "k_check_adj");
+          AdjSet set{};
           for (const ClassArgs &cl : classes) {
             const unsigned blocks = (unsigned)((cl.n_checks + per - 1) / per);
             ap.partial_base = row;
-            launch_adj<W>(ap, cl, blocks);
+            if (merged && &cl != lead && cl.shape != kShapeGeneric) {
+              set.row[set.n] = row;
+              set.c[set.n++] = cl;
+              set.block0[set.n] = set.block0[set.n - 1] + (int32_t)blocks;
+            } else {
+              launch_adj<W>(ap, cl, blocks);
+            }
             row += (int64_t)blocks * G;
           }
+          if (merged)
+            hipLaunchKernelGGL(k_check_adj_set<W>, dim3((unsigned)set.block0[set.n], G), dim3(kBlock), 0, st, ap, set);
         }
         {
           // two levels: up to kReduceChunks blocks of fixed row ranges, then one block
