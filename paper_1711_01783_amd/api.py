@@ -1,6 +1,7 @@
 """Python-level API: code handles, syndrome and decode (argument marshalling)."""
 from __future__ import annotations
 
+import contextlib
 import ctypes
 from dataclasses import dataclass
 
@@ -129,6 +130,32 @@ def _stream_ptr(stream):
     return ctypes.c_void_p(s.cuda_stream)
 
 
+def _on(stream):
+    """Context in which a call that runs on `stream` allocates.  The caching
+    allocator hands freed memory out again in the order of the stream it was
+    allocated on: memory that `stream` uses has to come from that stream, or its
+    next owner (or its last one) uses it while `stream` does."""
+    import torch
+
+    if stream is None:
+        return contextlib.nullcontext()
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream)
+    return torch.cuda.stream(stream)
+
+
+def _for_caller(stream, *tensors):
+    """Marks tensors allocated on `stream` that the caller gets as used on its
+    current stream, where it reads (and may free) them."""
+    import torch
+
+    if stream is not None:
+        current = torch.cuda.current_stream()
+        for t in tensors:
+            if t is not None:
+                t.record_stream(current)
+
+
 def _require(t, dtype, shape, name):
     import torch
 
@@ -154,15 +181,16 @@ def syndrome(code: Code, bits, stream=None):
 
     b = int(bits.shape[0])
     _require(bits, torch.uint8, (b, code.N), "bits")
-    out = torch.empty((b, code.M), dtype=torch.uint8, device=bits.device)
+    with _on(stream):
+        out = torch.empty((b, code.M), dtype=torch.uint8, device=bits.device)
+    _for_caller(stream, out)
     if b < 2 or b * code.E < _PACKED_SYNDROME_GATHERS:
         check(lib.met_syndrome(code.handle, bits.data_ptr(), b, out.data_ptr(), _stream_ptr(stream)))
         return out
     n = ctypes.c_size_t()
     check(lib.met_syndrome_workspace_bytes(code.handle, b, ctypes.byref(n)))
-    ws = torch.empty(n.value, dtype=torch.uint8, device=bits.device)
-    if stream is not None:
-        ws.record_stream(stream)  # the words are freed here while `stream` may still use them
+    with _on(stream):
+        ws = torch.empty(n.value, dtype=torch.uint8, device=bits.device)
     check(lib.met_syndrome_ex(code.handle, bits.data_ptr(), b, out.data_ptr(), ws.data_ptr(), n.value,
                               _stream_ptr(stream)))
     return out
@@ -177,8 +205,10 @@ def mdr_bob(y, bits, d: int = 8, stream=None):
     b, n = int(y.shape[0]), int(y.shape[1])
     _require(y, torch.float32, (b, n), "y")
     _require(bits, torch.uint8, (b, n), "bits")
-    alpha = torch.empty((b, n), dtype=torch.float32, device=y.device)
-    ynorm = torch.empty((b, max(n // d, 1)), dtype=torch.float32, device=y.device)
+    with _on(stream):
+        alpha = torch.empty((b, n), dtype=torch.float32, device=y.device)
+        ynorm = torch.empty((b, max(n // d, 1)), dtype=torch.float32, device=y.device)
+    _for_caller(stream, alpha, ynorm)
     check(lib.met_mdr_bob(y.data_ptr(), bits.data_ptr(), b, n, int(d), alpha.data_ptr(), ynorm.data_ptr(),
                           _stream_ptr(stream)))
     return alpha, ynorm
@@ -193,7 +223,9 @@ def mdr_alice(x, alpha, ynorm, sigma_z2: float, d: int = 8, stream=None):
     _require(x, torch.float32, (b, n), "x")
     _require(alpha, torch.float32, (b, n), "alpha")
     _require(ynorm, torch.float32, (b, max(n // d, 1)), "ynorm")
-    llr = torch.empty((b, n), dtype=torch.float32, device=x.device)
+    with _on(stream):
+        llr = torch.empty((b, n), dtype=torch.float32, device=x.device)
+    _for_caller(stream, llr)
     check(lib.met_mdr_alice(x.data_ptr(), alpha.data_ptr(), ynorm.data_ptr(), float(sigma_z2), b, n, int(d),
                             llr.data_ptr(), _stream_ptr(stream)))
     return llr
@@ -237,15 +269,17 @@ def decode(code: Code, llr, syn, max_iter: int, fixed_iters: bool = False, poste
     _require(llr, torch.float32, (b, code.N), "llr")
     _require(syn, torch.uint8, (b, code.M), "syn")
     need = workspace_bytes(code, b, fixed_iters, posterior, deg1_skip, c2v_fp16, c2v_q8)
-    if workspace is None or workspace.numel() < need:
-        workspace = torch.empty(need + 256, dtype=torch.uint8, device=dev)
+    with _on(stream):
+        if workspace is None or workspace.numel() < need:
+            workspace = torch.empty(need + 256, dtype=torch.uint8, device=dev)
+        bits = torch.empty((b, code.N), dtype=torch.uint8, device=dev)
+        iters = torch.empty(b, dtype=torch.int32, device=dev)
+        conv = torch.empty(b, dtype=torch.uint8, device=dev)
+        post = torch.empty((b, code.N), dtype=torch.float32, device=dev) if posterior else None
+    _for_caller(stream, bits, iters, conv, post)
     off = (-workspace.data_ptr()) % 256
     ws_ptr = workspace.data_ptr() + off
     ws_len = workspace.numel() - off
-    bits = torch.empty((b, code.N), dtype=torch.uint8, device=dev)
-    iters = torch.empty(b, dtype=torch.int32, device=dev)
-    conv = torch.empty(b, dtype=torch.uint8, device=dev)
-    post = torch.empty((b, code.N), dtype=torch.float32, device=dev) if posterior else None
     tuning = met_tuning()
     tuning.check_steps_per_wave = int(check_steps_per_wave)
     tuning.variable_chunk = int(variable_chunk)
@@ -360,44 +394,49 @@ class BatchedDecoder:
 
         if not jobs:
             raise ValueError("no jobs")
-        dev = jobs[0].llr.device
         for j in jobs:
             b = int(j.llr.shape[0])
             _require(j.llr, torch.float32, (b, j.code.N), "llr")
             _require(j.syn, torch.uint8, (b, j.code.M), "syn")
         if outputs is None:
-            outputs = []
-            for j in jobs:
-                b = int(j.llr.shape[0])
-                outputs.append(DecodeOutput(torch.empty((b, j.code.N), dtype=torch.uint8, device=dev),
-                                            torch.empty(b, dtype=torch.int32, device=dev),
-                                            torch.empty(b, dtype=torch.uint8, device=dev), None))
-        self._ensure_workspace(jobs)
+            outputs = self._outputs(jobs, stream)
+        self._ensure_workspace(jobs, stream)
         arr = _job_structs(jobs, outputs)
         ws_len = self.workspace.numel() - (self._ws_ptr - self.workspace.data_ptr())
         check(lib.met_decode_batched(arr, len(jobs), ctypes.c_void_p(self._ws_ptr), ws_len,
                                      ctypes.byref(self.tuning), _stream_ptr(stream)))
         return outputs
 
-    def _ensure_workspace(self, jobs):
+    @staticmethod
+    def _outputs(jobs, stream):
+        import torch
+
+        dev = jobs[0].llr.device
+        with _on(stream):
+            outs = [DecodeOutput(torch.empty((int(j.llr.shape[0]), j.code.N), dtype=torch.uint8, device=dev),
+                                 torch.empty(int(j.llr.shape[0]), dtype=torch.int32, device=dev),
+                                 torch.empty(int(j.llr.shape[0]), dtype=torch.uint8, device=dev), None) for j in jobs]
+        for o in outs:
+            _for_caller(stream, o.bits, o.iterations, o.converged)
+        return outs
+
+    def _ensure_workspace(self, jobs, stream):
         import torch
 
         need = batched_workspace_bytes(jobs)
         if self.workspace is None or self.workspace.numel() - 256 < need:
-            self.workspace = torch.empty(need + 256, dtype=torch.uint8, device=jobs[0].llr.device)
+            with _on(stream):
+                self.workspace = torch.empty(need + 256, dtype=torch.uint8, device=jobs[0].llr.device)
             self._ws_ptr = self.workspace.data_ptr() + (-self.workspace.data_ptr()) % 256
+        # kept between calls that may run on different streams
+        self.workspace.record_stream(stream if stream is not None else torch.cuda.current_stream())
 
     def autotune(self, jobs, probe_iters: int = 0, stream=None) -> dict:
         """Picks this decoder's launch shape for `jobs` with the library's
         autotuner (short timed runs of the same jobs; cached per process).
         Overwrites nothing but scratch outputs; returns the chosen shape."""
-        import torch
-
-        dev = jobs[0].llr.device
-        outs = [DecodeOutput(torch.empty((int(j.llr.shape[0]), j.code.N), dtype=torch.uint8, device=dev),
-                             torch.empty(int(j.llr.shape[0]), dtype=torch.int32, device=dev),
-                             torch.empty(int(j.llr.shape[0]), dtype=torch.uint8, device=dev), None) for j in jobs]
-        self._ensure_workspace(jobs)
+        outs = self._outputs(jobs, stream)
+        self._ensure_workspace(jobs, stream)
         arr = _job_structs(jobs, outs)
         best = met_tuning()
         ms = ctypes.c_float()

@@ -14,6 +14,7 @@ import ctypes
 import math
 
 from ._lib import check, lib
+from .api import _for_caller, _on
 
 
 def default_checkpoint_interval(iterations: int) -> int:
@@ -57,12 +58,14 @@ def forward(code, llr, syn, weights, ckpt_every: int = 0, workspace=None, stream
     b, iters = int(llr.shape[0]), int(weights.shape[1])
     k = ckpt_every or default_checkpoint_interval(iters)
     need = workspace_bytes(code, b, iters, k)
-    if workspace is None or workspace.numel() < need + 256:
-        workspace = torch.empty(need + 256, dtype=torch.uint8, device=llr.device)
+    with _on(stream):
+        if workspace is None or workspace.numel() < need + 256:
+            workspace = torch.empty(need + 256, dtype=torch.uint8, device=llr.device)
+        post = torch.empty((b, code.N), dtype=torch.float32, device=llr.device)
+        bits = torch.empty((b, code.N), dtype=torch.uint8, device=llr.device)
+        conv = torch.empty(b, dtype=torch.uint8, device=llr.device)
+    _for_caller(stream, post, bits, conv, workspace)
     ws, wsl = _aligned(workspace)
-    post = torch.empty((b, code.N), dtype=torch.float32, device=llr.device)
-    bits = torch.empty((b, code.N), dtype=torch.uint8, device=llr.device)
-    conv = torch.empty(b, dtype=torch.uint8, device=llr.device)
     check(lib.met_wbp_forward(code.handle, llr.data_ptr(), syn.data_ptr(), b, iters, weights.data_ptr(), k,
                               post.data_ptr(), bits.data_ptr(), conv.data_ptr(), ws, wsl, _stream(stream)))
     return post, bits, conv, workspace
@@ -75,8 +78,10 @@ def backward(code, grad_posterior, weights, ckpt_every: int, workspace, stream=N
     _check_weights(code, weights)
     b, iters = int(grad_posterior.shape[0]), int(weights.shape[1])
     k = ckpt_every or default_checkpoint_interval(iters)
-    g = grad_posterior.contiguous().float()
-    out = torch.empty_like(weights)
+    with _on(stream):
+        g = grad_posterior.contiguous().float()
+        out = torch.empty_like(weights)
+    _for_caller(stream, out)
     ws, wsl = _aligned(workspace)
     check(lib.met_wbp_backward(code.handle, g.data_ptr(), b, iters, weights.data_ptr(), k, out.data_ptr(), ws, wsl,
                                _stream(stream)))
