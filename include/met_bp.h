@@ -413,6 +413,23 @@ int met_decode_ex(const met_code *c, const float *llr, const uint8_t *syn, int32
                   uint32_t flags, uint8_t *bits, int32_t *iters, uint8_t *converged, float *posterior,
                   void *workspace, size_t ws_bytes, const met_tuning *tuning, void *stream);
 
+/* met_decode by teams whatever the sizes (met_decode chooses between teams and
+ * launches by size), with the team's shape given: for measurements, and for
+ * tests of conditions that a whole idle device does not show.  Results are
+ * met_decode's.  MET_NO_COMPACT and MET_NO_DEG1_SKIP are refused; the workspace
+ * must hold the teams' states (met_decode_workspace_bytes covers the widths that
+ * met_decode takes).  Errors: as met_decode, MET_EINVAL for bad options. */
+typedef struct {
+  int32_t frames;      /* frames per group: 1, 2, 4, 8 or 16; at least 4 with
+                          reduced message storage */
+  int32_t dies;        /* 1..8: only workgroups on the first `dies` accelerator
+                          dies take part, as on a partitioned device; 0: all */
+  int32_t reserved[6]; /* must be 0 */
+} met_team_options;
+int met_decode_teams(const met_code *c, const float *llr, const uint8_t *syn, int32_t B, int32_t max_iter,
+                     uint32_t flags, uint8_t *bits, int32_t *iters, uint8_t *converged, float *posterior,
+                     void *workspace, size_t ws_bytes, const met_team_options *options, void *stream);
+
 /* ---- Batched decoding ------------------------------------------------------
  * Several decode jobs -- possibly different codes (rates), batch sizes and
  * iteration budgets -- in one HIP graph (set-up, iterations, outputs; cached

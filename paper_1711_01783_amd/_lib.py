@@ -79,6 +79,10 @@ class met_tuning(ctypes.Structure):
                 ("interleave", ctypes.c_int32), ("reserved", ctypes.c_int32 * 3)]
 
 
+class met_team_options(ctypes.Structure):
+    _fields_ = [("frames", ctypes.c_int32), ("dies", ctypes.c_int32), ("reserved", ctypes.c_int32 * 6)]
+
+
 class met_job(ctypes.Structure):
     _fields_ = [("code", ctypes.c_void_p), ("llr", ctypes.c_void_p), ("syn", ctypes.c_void_p),
                 ("B", ctypes.c_int32), ("max_iter", ctypes.c_int32), ("flags", ctypes.c_uint32),
@@ -123,6 +127,8 @@ def _load():
         "met_decode_noalloc": (ctypes.c_int, [P, P, P, i32, i32, u32, P, P, P, P, P]),
         "met_last_error": (ctypes.c_char_p, []),
         "met_decode_ex": (ctypes.c_int, [P, P, P, i32, i32, u32, P, P, P, P, P, sz, ctypes.POINTER(met_tuning), P]),
+        "met_decode_teams": (ctypes.c_int, [P, P, P, i32, i32, u32, P, P, P, P, P, sz, ctypes.POINTER(met_team_options),
+                                            P]),
         "met_wbp_workspace_bytes": (ctypes.c_int, [P, i32, i32, i32, ctypes.POINTER(sz)]),
         "met_wbp_forward": (ctypes.c_int, [P, P, P, i32, i32, P, i32, P, P, P, P, sz, P]),
         "met_wbp_backward": (ctypes.c_int, [P, P, i32, i32, P, i32, P, P, sz, P]),

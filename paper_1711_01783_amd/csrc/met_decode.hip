@@ -687,6 +687,18 @@ extern "C" int met_decode_workspace_bytes(const met_code *c, int32_t B, uint32_t
   });
 }
 
+// Buffers and iteration budget of a decode.
+static int check_buffers(const float *llr, const uint8_t *syn, int32_t max_iter, const uint8_t *bits,
+                         const int32_t *iters, const uint8_t *converged, const float *posterior,
+                         const void *workspace) {
+  if (!llr || !syn || !bits || !iters || !converged || !workspace) return fail(MET_EINVAL, "NULL buffer");
+  if (max_iter < 1 || max_iter > 1000000) return fail(MET_EINVAL, "max_iter = %d outside 1..10^6", max_iter);
+  if (((uintptr_t)llr & 3) || ((uintptr_t)posterior & 3) || ((uintptr_t)iters & 3))
+    return fail(MET_EINVAL, "misaligned float/int buffer");
+  if ((uintptr_t)workspace & 255) return fail(MET_EINVAL, "workspace must be 256-byte aligned");
+  return MET_OK;
+}
+
 // `whole`: the workspace must hold all that met_decode_workspace_bytes counts;
 // otherwise what the launches need is enough (and the team decoder is used
 // where it fits).
@@ -695,11 +707,8 @@ static int decode_checked(const met_code *c, const float *llr, const uint8_t *sy
                           void *workspace, size_t ws_bytes, bool whole, const met_tuning *tuning, void *stream) {
   int rc = validate_decode(c, B, flags);
   if (rc) return rc;
-  if (!llr || !syn || !bits || !iters || !converged || !workspace) return fail(MET_EINVAL, "NULL buffer");
-  if (max_iter < 1 || max_iter > 1000000) return fail(MET_EINVAL, "max_iter = %d outside 1..10^6", max_iter);
-  if (((uintptr_t)llr & 3) || ((uintptr_t)posterior & 3) || ((uintptr_t)iters & 3))
-    return fail(MET_EINVAL, "misaligned float/int buffer");
-  if ((uintptr_t)workspace & 255) return fail(MET_EINVAL, "workspace must be 256-byte aligned");
+  rc = check_buffers(llr, syn, max_iter, bits, iters, converged, posterior, workspace);
+  if (rc) return rc;
   int ipw = 4, chunk = 16;
   if (tuning) {
     const int s = tuning->check_steps_per_wave;
@@ -726,8 +735,10 @@ static int decode_checked(const met_code *c, const float *llr, const uint8_t *sy
   // launches it asks for.
   const bool shaped = tuning && (tuning->check_steps_per_wave || tuning->variable_chunk);
   if (!shaped && !(flags & (MET_NO_COMPACT | MET_NO_DEG1_SKIP))) {
-    const int tw = met::team_width(c, B, posterior != nullptr, c2v_bytes(flags), max_iter,
-                                   !(flags & MET_FIXED_ITERS), ws_bytes);
+    int tw = 0;
+    rc = met::team_width(c, B, posterior != nullptr, c2v_bytes(flags), max_iter, !(flags & MET_FIXED_ITERS), ws_bytes,
+                         &tw);
+    if (rc) return rc;
     if (tw)
       return met::team_decode(c, d, tw, llr, syn, B, max_iter, flags, bits, iters, converged, posterior,
                               static_cast<char *>(workspace), (hipStream_t)stream);
@@ -754,6 +765,35 @@ extern "C" int met_decode_ex(const met_code *c, const float *llr, const uint8_t 
   met::clear_error();
   return decode_checked(c, llr, syn, B, max_iter, flags, bits, iters, converged, posterior, workspace, ws_bytes, true,
                         tuning, stream);
+  });
+}
+
+extern "C" int met_decode_teams(const met_code *c, const float *llr, const uint8_t *syn, int32_t B, int32_t max_iter,
+                                uint32_t flags, uint8_t *bits, int32_t *iters, uint8_t *converged, float *posterior,
+                                void *workspace, size_t ws_bytes, const met_team_options *options, void *stream) { return met::guarded("met_decode_teams", [&]() -> int {
+  met::clear_error();
+  int rc = validate_decode(c, B, flags);
+  if (rc) return rc;
+  rc = check_buffers(llr, syn, max_iter, bits, iters, converged, posterior, workspace);
+  if (rc) return rc;
+  if (flags & (MET_NO_COMPACT | MET_NO_DEG1_SKIP))
+    return fail(MET_EINVAL, "MET_NO_COMPACT and MET_NO_DEG1_SKIP select the launches, not the teams");
+  if (!options) return fail(MET_EINVAL, "NULL options");
+  const met_team_options &o = *options;
+  const int W = o.frames;
+  if (W != 1 && W != 2 && W != 4 && W != 8 && W != 16) return fail(MET_EINVAL, "%d frames per group", W);
+  if (c2v_bytes(flags) != sizeof(float) && W < 4)
+    return fail(MET_EINVAL, "reduced message storage needs groups of at least 4 frames, not %d", W);
+  if (o.dies < 0 || o.dies > met::kTeamSlots) return fail(MET_EINVAL, "dies = %d outside 0..%d", o.dies, met::kTeamSlots);
+  for (int32_t r : o.reserved)
+    if (r) return fail(MET_EINVAL, "reserved option fields must be 0");
+  if (!met::team_fits(c, B, posterior != nullptr, c2v_bytes(flags), W, ws_bytes))
+    return fail(MET_EINVAL, "workspace of %zu bytes does not hold groups of %d frames", ws_bytes, W);
+  const met::DeviceCode *d = nullptr;
+  rc = met::device_code(c, &d);
+  if (rc) return rc;
+  return met::team_decode(c, d, W, llr, syn, B, max_iter, flags, bits, iters, converged, posterior,
+                          static_cast<char *>(workspace), (hipStream_t)stream, options);
   });
 }
 

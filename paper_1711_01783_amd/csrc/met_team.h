@@ -7,7 +7,7 @@
 
 namespace met {
 
-constexpr int kTeamSlots = 8;  // groups in work at once: one per XCD
+constexpr int kTeamSlots = 8;  // groups in work at once, at most: one per XCD
 
 struct TeamClass {
   int32_t shape, tile0, first_check, n_checks, first_msg, first_leaf;
@@ -31,6 +31,7 @@ struct TeamJob {
   // offsets of a slot's arrays in bytes (c2v at 0); an array ends where the next begins
   uint32_t off_P, off_L2, off_Lphi, off_Lraw, off_P1, off_syn, off_B1, slot_bytes;
   int32_t n_slots, expected, lanes_per_vn;
+  int32_t dies;           // workgroups on an XCD of this number or above take no part
   int32_t n_classes, main_tiles, check_tiles;  // main: the (3,1) class in cls[0], if any
   TeamClass cls[kMaxClasses];
 };
@@ -41,12 +42,16 @@ size_t team_slot(const met_code *c, int W, bool post, size_t c2v_bytes, TeamJob 
 // Bytes ahead of the slots in the workspace.
 size_t team_control_bytes();
 
-// Frames per group with which the team decoder takes this decode, or 0 where
-// the per-phase launches are the better path or the workspace is too small.
-int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, int max_iter, bool early, size_t ws_bytes);
+// *width: frames per group with which the team decoder takes this decode, or 0
+// where the per-phase launches are the better path or the workspace is too small.
+int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, int max_iter, bool early, size_t ws_bytes,
+               int *width);
+
+// Whether the teams' states in groups of W frames fit in a workspace.
+bool team_fits(const met_code *c, int B, bool post, size_t c2v_bytes, int W, size_t ws_bytes);
 
 int team_decode(const met_code *c, const DeviceCode *d, int W, const float *llr, const uint8_t *syn, int B,
                 int max_iter, uint32_t flags, uint8_t *bits, int32_t *iters, uint8_t *conv, float *post,
-                char *ws, hipStream_t st);
+                char *ws, hipStream_t st, const met_team_options *opt = nullptr);
 
 }  // namespace met

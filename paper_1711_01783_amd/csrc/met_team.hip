@@ -9,7 +9,9 @@
 // team's workgroups alone, and a team whose frames have all stopped takes the
 // next group.  No launch, host round trip or device-wide barrier remains
 // inside a decode, and a frame that needs many iterations holds up only the
-// few frames of its group.
+// few frames of its group.  Teams take every group, their first one too, from
+// one counter, so that however many teams form (a partitioned device shows
+// fewer dies) all groups are decoded.
 //
 // Coherence inside a team.  All workgroups of a team share one L2, so data
 // written by one is visible to the others once its stores are acknowledged
@@ -50,7 +52,7 @@ struct TeamControl {
   uint32_t next_group, pad1[31];
   struct {
     uint32_t count, pad0[31];
-    uint32_t pub, pad1[31];             // members + 256 (slot + 1), set once
+    uint64_t pub, pad1[15];             // members + 256 (slot + 1) + 65536 group, set once
   } reg[kXccIds];
   uint64_t flag[kXccIds][2][kMaxTeam];  // epoch in the low word, payload in the high one
 };
@@ -506,30 +508,39 @@ __device__ __forceinline__ void variable_tile(const GroupState &s, const int32_t
 // ---- The team -----------------------------------------------------------------
 
 struct TeamShared {
-  uint32_t rank, n, slot, err;
+  uint32_t rank, n, slot, group, err;
   uint32_t word;    // OR of the waves' payloads
   uint32_t result;  // OR of the members' payloads
   int32_t stop[16]; // iteration at which each frame of the group stopped
 };
 
+__device__ __forceinline__ uint32_t next_group(TeamControl *ctl) {
+  return __hip_atomic_fetch_add(&ctl->next_group, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Registers the workgroup with its XCD's team; false if it has no part in it.
-__device__ bool join_team(TeamControl *ctl, uint32_t xcc, uint32_t expected, uint32_t n_slots, TeamShared &sh) {
+__device__ bool join_team(TeamControl *ctl, uint32_t xcc, const TeamJob &job, TeamShared &sh) {
+  if (xcc >= (uint32_t)job.dies) return false;
   if (threadIdx.x == 0) {
     auto &r = ctl->reg[xcc];
     sh.err = 0;
     sh.word = 0;
     const uint32_t rank = __hip_atomic_fetch_add(&r.count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    uint32_t pub = 0;
+    uint64_t pub = 0;
     if (rank & kClosed) {
       pub = 1;  // too late: no slot
     } else if (rank == 0) {
       const uint64_t t0 = wall_clock64();
-      while (__hip_atomic_load(&r.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < expected &&
+      // the team's memory, and its first group (none may be left)
+      const uint32_t slot = __hip_atomic_fetch_add(&ctl->next_slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t g = (uint32_t)job.G;
+      if (slot < (uint32_t)job.n_slots) g = next_group(ctl);
+      while (__hip_atomic_load(&r.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)job.expected &&
              wall_clock64() - t0 < kFormTicks) {
       }
-      const uint32_t slot = __hip_atomic_fetch_add(&ctl->next_slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const uint32_t n = __hip_atomic_fetch_or(&r.count, kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      pub = min(n, (uint32_t)kMaxTeam) | (slot < n_slots ? (slot + 1) << 8 : 0u);
+      pub = min(n, (uint32_t)kMaxTeam);
+      if (g < (uint32_t)job.G) pub |= (slot + 1) << 8 | (uint64_t)g << 16;
       __hip_atomic_store(&r.pub, pub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {
       for (uint32_t i = 0; i < kPollLimit; ++i) {
@@ -539,8 +550,9 @@ __device__ bool join_team(TeamControl *ctl, uint32_t xcc, uint32_t expected, uin
       }
     }
     sh.rank = rank;
-    sh.n = pub & 255u;
-    sh.slot = pub >> 8;  // slot + 1, 0: nothing to do
+    sh.n = (uint32_t)pub & 255u;
+    sh.slot = (uint32_t)(pub >> 8) & 255u;  // slot + 1, 0: nothing to do
+    sh.group = (uint32_t)(pub >> 16);
   }
   __syncthreads();
   return sh.slot != 0 && sh.rank < sh.n;
@@ -747,7 +759,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
   __shared__ uint8_t s_code[std::is_same<CT, q8lut_t>::value ? kLutSize : 1];
   TeamControl *ctl = reinterpret_cast<TeamControl *>(job.ws);
   const uint32_t xcc = xcc_id();
-  if (!join_team(ctl, xcc, (uint32_t)job.expected, (uint32_t)job.n_slots, sh)) return;
+  if (!join_team(ctl, xcc, job, sh)) return;
   if constexpr (std::is_class<CT>::value)
     for (int i = threadIdx.x; i < 128; i += kTeamBlock) s_q8[i] = kQ8Table.v[i];
   if constexpr (std::is_same<CT, q8lut_t>::value)
@@ -773,7 +785,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
   s.B1 = buf(job.off_B1, job.slot_bytes);
   s.b1_half = (job.slot_bytes - job.off_B1) / 2;
 
-  uint32_t g = slot;
+  uint32_t g = sh.group;
   while (g < (uint32_t)job.G) {
     const uint32_t frames = min((uint32_t)W, (uint32_t)job.B - g * W);
     uint32_t act = (1u << frames) - 1u;
@@ -822,11 +834,10 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
     }
     __syncthreads();  // sh.stop
     if (sh.err) return;
+    uint32_t next = 0;
+    if (rank == 0 && threadIdx.x == 0) next = next_group(ctl);  // waited for after the outputs
     output_phase<W>(job, s, g, wave, waves, sh);
-    if (job.G <= job.n_slots) return;
-    if (rank == 0 && threadIdx.x == 0)
-      sh.word = (uint32_t)job.n_slots +
-                __hip_atomic_fetch_add(&ctl->next_group, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (rank == 0 && threadIdx.x == 0) sh.word = next;
     g = barrier(sh);
     if (sh.err) return;
   }
@@ -842,6 +853,16 @@ void launch_reduced(int W, const TeamJob &job, unsigned grid, hipStream_t st) {
   W == 4   ? launch_team<4, CT>(job, grid, st)
   : W == 8 ? launch_team<8, CT>(job, grid, st)
            : launch_team<16, CT>(job, grid, st);
+}
+
+// Dies that the device shows: eight, or fewer where it is partitioned.
+constexpr int kCusPerDie = 32;
+int device_dies(int *dies, int *cus) {
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  HIP_TRY(hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev));
+  *dies = std::max(1, std::min(*cus / kCusPerDie, kTeamSlots));
+  return MET_OK;
 }
 
 // Lanes per variable node: as many as still leave one tile per wave of a full
@@ -906,7 +927,11 @@ size_t team_slot(const met_code *c, int W, bool post, size_t c2v_bytes, TeamJob 
 // N = 65536: 1 frame 1.1 / 0.5, 16 2.4 / 1.8, 32 3.0 / 1.8, 64 3.1 / 3.6.  A team that
 // would be slower if every frame ran its whole budget is not taken, nor one whose
 // states leave the Infinity Cache (64 frames of N = 10^6 in groups of 8: 87 ms).
-int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, int max_iter, bool early, size_t ws_bytes) {
+int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, int max_iter, bool early, size_t ws_bytes,
+               int *width) {
+  *width = 0;
+  int dies = 0, cus = 0;
+  if (const int rc = device_dies(&dies, &cus)) return rc;
   const double E = 1e-6 * (double)c->E12;
   const int plain_w = choose_interleave(B);
   const double FE = E * ((B + plain_w - 1) / plain_w) * plain_w * (c2v_bytes == sizeof(float) ? 2.5 : 2.0);
@@ -917,24 +942,27 @@ int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, int max_it
   double best_t = early && plain_w == 64 ? fixed + 0.5 * FE : whole;
   for (int W : {16, 8, 4, 2, 1}) {
     if (c2v_bytes != sizeof(float) && W < 4) continue;
-    const int G = (B + W - 1) / W, rounds = (G + kTeamSlots - 1) / kTeamSlots;
-    const size_t slot = team_slot(c, W, post, c2v_bytes, nullptr), all = slot * std::min(G, kTeamSlots);
+    const int G = (B + W - 1) / W, rounds = (G + dies - 1) / dies;
+    const size_t slot = team_slot(c, W, post, c2v_bytes, nullptr), all = slot * std::min(G, dies);
     if (slot >= kMaxSlotBytes || team_control_bytes() + all > ws_bytes || all > kMaxTeamBytes) continue;
     const double it = (4.5 + (c2v_bytes == 1 ? 20 + 16 * W : 32 + 17.5 * W) * E) * (slot > (8u << 20) ? 1.15 : 1.0);
     if (rounds * it > whole) continue;
     const double m = std::min(1.0, std::pow((double)W / B, 0.2));
-    const double t = early && rounds > 1 ? it * (std::max(1.0, m * G / kTeamSlots) + m) : rounds * it;
+    const double t = early && rounds > 1 ? it * (std::max(1.0, m * G / dies) + m) : rounds * it;
     if (t < best_t) {
       best = W;
       best_t = t;
     }
   }
-  return best;
+  *width = best;
+  return MET_OK;
 }
 
 int team_decode(const met_code *c, const DeviceCode *d, int W, const float *llr, const uint8_t *syn, int B,
                 int max_iter, uint32_t flags, uint8_t *bits, int32_t *iters, uint8_t *conv, float *post,
-                char *ws, hipStream_t st) {
+                char *ws, hipStream_t st, const met_team_options *opt) {
+  int dies = 0, cus = 0;
+  if (const int rc = device_dies(&dies, &cus)) return rc;
   const size_t cb = (flags & MET_C2V_Q8) ? 1 : (flags & MET_C2V_FP16) ? 2 : 4;
   TeamJob job{};
   job.edge_msgvn = d->edge_msgvn;
@@ -961,7 +989,8 @@ int team_decode(const met_code *c, const DeviceCode *d, int W, const float *llr,
   job.G = (B + W - 1) / W;
   job.max_iter = max_iter;
   job.early = !(flags & MET_FIXED_ITERS);
-  job.n_slots = std::min(job.G, kTeamSlots);
+  job.n_slots = std::min(job.G, dies);
+  job.dies = opt && opt->dies ? opt->dies : kXccIds;
   job.off_slots = team_control_bytes();
   job.lanes_per_vn = lanes_per_vn(c, W);
   team_slot(c, W, post != nullptr, cb, &job);
@@ -979,10 +1008,7 @@ int team_decode(const met_code *c, const DeviceCode *d, int W, const float *llr,
     tiles += (int32_t)((k.n_checks + per - 1) / per);
   }
   job.check_tiles = tiles;
-  int dev = 0, cus = 0;
-  HIP_TRY(hipGetDevice(&dev));
-  HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  job.expected = std::max(1, std::min(cus / kXcds, kMaxTeam));
+  job.expected = std::min(cus, kCusPerDie);
   hipLaunchKernelGGL(k_team_clear, dim3(1), dim3(kBlock), 0, st, reinterpret_cast<uint32_t *>(ws));
   {
     ScopedTimer t(st, "k_team");
@@ -1005,6 +1031,12 @@ int team_decode(const met_code *c, const DeviceCode *d, int W, const float *llr,
   }
   HIP_TRY(hipGetLastError());
   return MET_OK;
+}
+
+// Whether the teams' states in groups of W frames fit in ws_bytes.
+bool team_fits(const met_code *c, int B, bool post, size_t c2v_bytes, int W, size_t ws_bytes) {
+  const size_t slot = team_slot(c, W, post, c2v_bytes, nullptr);
+  return slot < kMaxSlotBytes && team_control_bytes() + slot * std::min((B + W - 1) / W, kTeamSlots) <= ws_bytes;
 }
 
 }  // namespace met
