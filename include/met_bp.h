@@ -271,7 +271,11 @@ int met_decode_workspace_bytes(const met_code *c, int32_t B, uint32_t flags, int
  *              | MET_NO_DEG1_SKIP and/or | MET_C2V_FP16 or | MET_C2V_Q8 (with
  *              | MET_CHECK_LUT)
  *   bits:      dev uint8 [B][N] output, hard decisions at each frame's stop
- *   iters:     dev int32 [B] output, iterations run (1..max_iter)
+ *   iters:     dev int32 [B] output, iterations run (1..max_iter).  Negative,
+ *              with converged 0: the frame has no result (its bits and posterior are
+ *              undefined), since a workgroup that decodes it waited in vain for
+ *              the others of its team, which is never expected to happen; the
+ *              wait is bounded, so that the call ends in any case
  *   converged: dev uint8 [B] output, 1 iff H bits = syn
  *   posterior: dev float32 [B][N] output, or NULL
  *   workspace: dev, 256-byte aligned, at least met_decode_workspace_bytes();
@@ -424,7 +428,10 @@ typedef struct {
                           reduced message storage */
   int32_t dies;        /* 1..8: only workgroups on the first `dies` accelerator
                           dies take part, as on a partitioned device; 0: all */
-  int32_t reserved[6]; /* must be 0 */
+  int32_t polls;       /* polls after which a workgroup gives up waiting for its
+                          team; 0: 2^22, seconds (a tiny number makes the
+                          teams give up: iters < 0) */
+  int32_t reserved[5]; /* must be 0 */
 } met_team_options;
 int met_decode_teams(const met_code *c, const float *llr, const uint8_t *syn, int32_t B, int32_t max_iter,
                      uint32_t flags, uint8_t *bits, int32_t *iters, uint8_t *converged, float *posterior,

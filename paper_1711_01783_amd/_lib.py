@@ -80,7 +80,8 @@ class met_tuning(ctypes.Structure):
 
 
 class met_team_options(ctypes.Structure):
-    _fields_ = [("frames", ctypes.c_int32), ("dies", ctypes.c_int32), ("reserved", ctypes.c_int32 * 6)]
+    _fields_ = [("frames", ctypes.c_int32), ("dies", ctypes.c_int32), ("polls", ctypes.c_int32),
+                ("reserved", ctypes.c_int32 * 5)]
 
 
 class met_job(ctypes.Structure):

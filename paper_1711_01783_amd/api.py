@@ -243,7 +243,7 @@ def workspace_bytes(code: Code, frames: int, fixed_iters: bool = False, posterio
 @dataclass
 class DecodeOutput:
     bits: "object"       # uint8 [B, N]
-    iterations: "object" # int32 [B]
+    iterations: "object" # int32 [B]; negative: no result (see met_decode), never expected
     converged: "object"  # uint8 [B]
     posterior: "object"  # float32 [B, N] or None
 

@@ -40,25 +40,33 @@ namespace {
 
 constexpr int kTeamBlock = 1024;
 constexpr int kTeamWaves = kTeamBlock / 64;
-constexpr int kXccIds = 16;             // values of the XCC_ID register
 constexpr int kMaxTeam = 64;            // workgroups of one team
 constexpr uint32_t kClosed = 0x80000000u;
 constexpr uint64_t kFormTicks = 2000;   // 20 us of the 100 MHz counter
-constexpr uint32_t kPollLimit = 1u << 22;  // polls of about 0.4 us
+constexpr uint32_t kPollLimit = 1u << 22;  // polls of about 0.4 us (TeamJob::poll_limit)
 
 // Control words at the start of the workspace, cleared before the launch.
 struct TeamControl {
-  uint32_t next_slot, pad0[31];
-  uint32_t next_group, pad1[31];
+  uint64_t taken, pad0[15];             // groups taken, and slots in the high word
   struct {
     uint32_t count, pad0[31];
     uint64_t pub, pad1[15];             // members + 256 (slot + 1) + 65536 group, set once
-  } reg[kXccIds];
-  uint64_t flag[kXccIds][2][kMaxTeam];  // epoch in the low word, payload in the high one
+  } reg[kTeamSlots];
+  uint64_t flag[kTeamSlots][2][kMaxTeam];  // epoch in the low word, payload in the high one
 };
 
-__global__ __launch_bounds__(kBlock) void k_team_clear(uint32_t *ctl) {
-  for (size_t i = threadIdx.x; i < sizeof(TeamControl) / 4; i += kBlock) ctl[i] = 0u;
+// Outcome (iterations) of frames that no team has taken, and of those whose team
+// gave up.
+constexpr int32_t kUntaken = -1, kGivenUp = -2;
+constexpr int32_t kSatisfied = 1 << 30;  // in TeamShared::stop
+
+__global__ __launch_bounds__(kTeamBlock) void k_team_clear(uint32_t *ctl, int32_t *iters, uint8_t *converged,
+                                                           int32_t B) {
+  for (size_t i = threadIdx.x; i < sizeof(TeamControl) / 4; i += kTeamBlock) ctl[i] = 0u;
+  for (int32_t f = threadIdx.x; f < B; f += kTeamBlock) {
+    iters[f] = kUntaken;
+    converged[f] = 0;
+  }
 }
 
 // ---- Memory -----------------------------------------------------------------
@@ -509,13 +517,18 @@ __device__ __forceinline__ void variable_tile(const GroupState &s, const int32_t
 
 struct TeamShared {
   uint32_t rank, n, slot, group, err;
+  uint32_t last;    // no group is left for this team after the present one
   uint32_t word;    // OR of the waves' payloads
   uint32_t result;  // OR of the members' payloads
-  int32_t stop[16]; // iteration at which each frame of the group stopped
+  int32_t stop[16]; // iteration at which each frame of the group stopped, and kSatisfied
 };
 
-__device__ __forceinline__ uint32_t next_group(TeamControl *ctl) {
-  return __hip_atomic_fetch_add(&ctl->next_group, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// The next group that nobody has taken (low word), and with `slots` = 1 the next
+// slot (high word).  One addition for both: there are 8 slots, one per die, or
+// one per group if there are fewer groups, so that a team without a slot finds
+// no group left either.
+__device__ __forceinline__ uint64_t take_group(TeamControl *ctl, uint32_t slots) {
+  return __hip_atomic_fetch_add(&ctl->taken, (uint64_t)slots << 32 | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Registers the workgroup with its XCD's team; false if it has no part in it.
@@ -531,19 +544,17 @@ __device__ bool join_team(TeamControl *ctl, uint32_t xcc, const TeamJob &job, Te
       pub = 1;  // too late: no slot
     } else if (rank == 0) {
       const uint64_t t0 = wall_clock64();
-      // the team's memory, and its first group (none may be left)
-      const uint32_t slot = __hip_atomic_fetch_add(&ctl->next_slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      uint32_t g = (uint32_t)job.G;
-      if (slot < (uint32_t)job.n_slots) g = next_group(ctl);
+      const uint64_t first = take_group(ctl, 1);  // waited for after the loop
       while (__hip_atomic_load(&r.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)job.expected &&
              wall_clock64() - t0 < kFormTicks) {
       }
       const uint32_t n = __hip_atomic_fetch_or(&r.count, kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       pub = min(n, (uint32_t)kMaxTeam);
-      if (g < (uint32_t)job.G) pub |= (slot + 1) << 8 | (uint64_t)g << 16;
+      const uint32_t slot = (uint32_t)(first >> 32), g = (uint32_t)first;
+      if (g < (uint32_t)job.G && slot < (uint32_t)job.n_slots) pub |= (slot + 1) << 8 | (uint64_t)g << 16;
       __hip_atomic_store(&r.pub, pub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {
-      for (uint32_t i = 0; i < kPollLimit; ++i) {
+      for (uint32_t i = 0; i < job.poll_limit; ++i) {
         pub = __hip_atomic_load(&r.pub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (pub) break;
         __builtin_amdgcn_s_sleep(1);
@@ -560,10 +571,11 @@ __device__ bool join_team(TeamControl *ctl, uint32_t xcc, const TeamJob &job, Te
 
 // Barrier of the team's workgroups; returns the OR of everything the members
 // put into sh.word before it.  sh.err is set if a member never came (it cannot:
-// every member is running), and the caller leaves.
+// every member is running), and the caller marks its group's frames and leaves;
+// no member passes the barrier after the next one then, so the team ends.
 struct TeamBarrier {
   TeamControl *ctl;
-  uint32_t xcc, rank, n, epoch;
+  uint32_t xcc, rank, n, poll_limit, epoch;
   __device__ uint32_t operator()(TeamShared &sh) {
     ++epoch;
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -581,14 +593,14 @@ struct TeamBarrier {
       for (;; ++i) {
         v = threadIdx.x < n ? __hip_atomic_load(fl + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : epoch;
         if (__all((uint32_t)v == epoch)) break;
-        if (i == kPollLimit) break;
+        if (i == poll_limit) break;
       }
       uint32_t w = (uint32_t)(v >> 32);
 #pragma unroll
       for (int d = 32; d >= 1; d >>= 1) w |= __shfl_xor(w, d);
       if (threadIdx.x == 0) {
         sh.result = w;
-        if (i == kPollLimit) sh.err = 1;
+        if (i == poll_limit) sh.err = 1;
       }
     }
     __syncthreads();
@@ -751,6 +763,23 @@ __device__ __forceinline__ void variable_phase(const TeamJob &job, const GroupSt
   }
 }
 
+// A frame's outcome, written by its team's first member, and the mark of a
+// member that gave up, before that or after: the mark stays.  The waits keep
+// converged at 0 with it: the flag is stored before the outcome is offered, and
+// cleared after the mark.
+__device__ __forceinline__ void give_up(const TeamJob &job, uint32_t f) {
+  (void)__hip_atomic_exchange(job.iters + f, kGivenUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  job.converged[f] = 0;
+}
+__device__ __forceinline__ bool set_outcome(const TeamJob &job, uint32_t f, int32_t stop) {
+  job.converged[f] = (uint8_t)((stop & kSatisfied) != 0);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  int32_t was = kUntaken;
+  return __hip_atomic_compare_exchange_strong(job.iters + f, &was, stop & ~kSatisfied, __ATOMIC_RELAXED,
+                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 template <int W, typename CT>
 __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
   __shared__ TeamShared sh;
@@ -770,7 +799,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
   __syncthreads();
   const Tables tab{s_q8, s_phi, s_code};
   const uint32_t rank = sh.rank, n = sh.n, slot = sh.slot - 1;
-  TeamBarrier barrier{ctl, xcc, rank, n, 0};
+  TeamBarrier barrier{ctl, xcc, rank, n, job.poll_limit, 0};
   const uint32_t wave = rank + n * (uint32_t)wave_id(), waves = n * kTeamWaves;
   char *base = job.ws + job.off_slots + (size_t)slot * job.slot_bytes;
   auto buf = [&](uint32_t off, uint32_t end) { return buffer_of(base + off, end - off); };
@@ -789,15 +818,15 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
   while (g < (uint32_t)job.G) {
     const uint32_t frames = min((uint32_t)W, (uint32_t)job.B - g * W);
     uint32_t act = (1u << frames) - 1u;
-    if (threadIdx.x < W) {
-      sh.stop[threadIdx.x] = job.max_iter;
-      if (rank == 0 && threadIdx.x < frames) {
-        job.iters[g * W + threadIdx.x] = 0;
-        job.converged[g * W + threadIdx.x] = 0;
-      }
-    }
+    if (threadIdx.x < W) sh.stop[threadIdx.x] = job.max_iter;
     setup_phase<W>(job, s, g, wave, waves);
-    barrier(sh);
+    // where every group has been taken by now, the team need not meet again
+    // after its outputs
+    if (rank == 0 && threadIdx.x == 0 &&
+        (uint32_t)__hip_atomic_load(&ctl->taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (uint32_t)job.G)
+      sh.word = 1;
+    const uint32_t last = barrier(sh);
+    if (threadIdx.x == 0) sh.last = last;
     int it = 1;
     for (; it <= job.max_iter && !sh.err; ++it) {
       Phase ph;
@@ -811,13 +840,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
       const uint32_t unsat = barrier(sh);
       if (ph.test) {
         const uint32_t done = act & ~unsat;
-        if (threadIdx.x < W && ((done >> threadIdx.x) & 1u)) {
-          sh.stop[threadIdx.x] = it - 1;
-          if (rank == 0) {
-            job.iters[g * W + threadIdx.x] = it - 1;
-            job.converged[g * W + threadIdx.x] = 1;
-          }
-        }
+        if (threadIdx.x < W && ((done >> threadIdx.x) & 1u)) sh.stop[threadIdx.x] = (it - 1) | kSatisfied;
         act &= unsat;
         if (!act) break;
       }
@@ -826,17 +849,23 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
     }
     if (act && !sh.err) {  // frames that ran the whole budget
       test_phase<W>(job, s, job.max_iter, wave, waves, sh);
-      const uint32_t unsat = barrier(sh);
-      if (rank == 0 && threadIdx.x < W && ((act >> threadIdx.x) & 1u)) {
-        job.iters[g * W + threadIdx.x] = job.max_iter;
-        job.converged[g * W + threadIdx.x] = (uint8_t)!((unsat >> threadIdx.x) & 1u);
-      }
+      const uint32_t done = act & ~barrier(sh);
+      if (threadIdx.x < W && ((done >> threadIdx.x) & 1u)) sh.stop[threadIdx.x] |= kSatisfied;
     }
     __syncthreads();  // sh.stop
-    if (sh.err) return;
+    const bool mine = threadIdx.x < min((uint32_t)W, (uint32_t)job.B - g * W);  // a thread per frame
+    if (sh.err) {
+      if (mine) give_up(job, g * W + threadIdx.x);
+      return;
+    }
+    // (both waited for after the outputs)
     uint32_t next = 0;
-    if (rank == 0 && threadIdx.x == 0) next = next_group(ctl);  // waited for after the outputs
+    bool set = true;
+    if (rank == 0 && threadIdx.x == 0 && !sh.last) next = (uint32_t)take_group(ctl, 0);
+    if (rank == 0 && mine) set = set_outcome(job, g * W + threadIdx.x, sh.stop[threadIdx.x]);
     output_phase<W>(job, s, g, wave, waves, sh);
+    if (!set) job.converged[g * W + threadIdx.x] = 0;
+    if (sh.last) return;
     if (rank == 0 && threadIdx.x == 0) sh.word = next;
     g = barrier(sh);
     if (sh.err) return;
@@ -943,7 +972,7 @@ int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, int max_it
   for (int W : {16, 8, 4, 2, 1}) {
     if (c2v_bytes != sizeof(float) && W < 4) continue;
     const int G = (B + W - 1) / W, rounds = (G + dies - 1) / dies;
-    const size_t slot = team_slot(c, W, post, c2v_bytes, nullptr), all = slot * std::min(G, dies);
+    const size_t slot = team_slot(c, W, post, c2v_bytes, nullptr), all = slot * std::min(G, kTeamSlots);
     if (slot >= kMaxSlotBytes || team_control_bytes() + all > ws_bytes || all > kMaxTeamBytes) continue;
     const double it = (4.5 + (c2v_bytes == 1 ? 20 + 16 * W : 32 + 17.5 * W) * E) * (slot > (8u << 20) ? 1.15 : 1.0);
     if (rounds * it > whole) continue;
@@ -989,8 +1018,9 @@ int team_decode(const met_code *c, const DeviceCode *d, int W, const float *llr,
   job.G = (B + W - 1) / W;
   job.max_iter = max_iter;
   job.early = !(flags & MET_FIXED_ITERS);
-  job.n_slots = std::min(job.G, dies);
-  job.dies = opt && opt->dies ? opt->dies : kXccIds;
+  job.n_slots = std::min(job.G, kTeamSlots);
+  job.dies = opt && opt->dies ? opt->dies : kTeamSlots;
+  job.poll_limit = opt && opt->polls ? (uint32_t)opt->polls : kPollLimit;
   job.off_slots = team_control_bytes();
   job.lanes_per_vn = lanes_per_vn(c, W);
   team_slot(c, W, post != nullptr, cb, &job);
@@ -1009,7 +1039,7 @@ int team_decode(const met_code *c, const DeviceCode *d, int W, const float *llr,
   }
   job.check_tiles = tiles;
   job.expected = std::min(cus, kCusPerDie);
-  hipLaunchKernelGGL(k_team_clear, dim3(1), dim3(kBlock), 0, st, reinterpret_cast<uint32_t *>(ws));
+  hipLaunchKernelGGL(k_team_clear, dim3(1), dim3(kTeamBlock), 0, st, reinterpret_cast<uint32_t *>(ws), iters, conv, B);
   {
     ScopedTimer t(st, "k_team");
     const unsigned grid = (unsigned)cus;
