@@ -431,7 +431,10 @@ typedef struct {
   int32_t polls;       /* polls after which a workgroup gives up waiting for its
                           team; 0: 2^22, seconds (a tiny number makes the
                           teams give up: iters < 0) */
-  int32_t reserved[5]; /* must be 0 */
+  int32_t late_us;     /* 0..10000: seven of every eight workgroups of a die
+                          come to their team 1 to 7 times this much later, as
+                          where other work holds compute units */
+  int32_t reserved[4]; /* must be 0 */
 } met_team_options;
 int met_decode_teams(const met_code *c, const float *llr, const uint8_t *syn, int32_t B, int32_t max_iter,
                      uint32_t flags, uint8_t *bits, int32_t *iters, uint8_t *converged, float *posterior,

@@ -81,7 +81,7 @@ class met_tuning(ctypes.Structure):
 
 class met_team_options(ctypes.Structure):
     _fields_ = [("frames", ctypes.c_int32), ("dies", ctypes.c_int32), ("polls", ctypes.c_int32),
-                ("reserved", ctypes.c_int32 * 5)]
+                ("late_us", ctypes.c_int32), ("reserved", ctypes.c_int32 * 4)]
 
 
 class met_job(ctypes.Structure):

@@ -786,6 +786,7 @@ extern "C" int met_decode_teams(const met_code *c, const float *llr, const uint8
     return fail(MET_EINVAL, "reduced message storage needs groups of at least 4 frames, not %d", W);
   if (o.dies < 0 || o.dies > met::kTeamSlots) return fail(MET_EINVAL, "dies = %d outside 0..%d", o.dies, met::kTeamSlots);
   if (o.polls < 0) return fail(MET_EINVAL, "polls = %d", o.polls);
+  if (o.late_us < 0 || o.late_us > 10000) return fail(MET_EINVAL, "late_us = %d outside 0..10000", o.late_us);
   for (int32_t r : o.reserved)
     if (r) return fail(MET_EINVAL, "reserved option fields must be 0");
   if (!met::team_fits(c, B, posterior != nullptr, c2v_bytes(flags), W, ws_bytes))

@@ -32,6 +32,7 @@ struct TeamJob {
   uint32_t off_P, off_L2, off_Lphi, off_Lraw, off_P1, off_syn, off_B1, slot_bytes;
   int32_t n_slots, expected, lanes_per_vn;
   int32_t dies;           // workgroups on an XCD of this number or above take no part
+  uint32_t late_ticks;    // delays of workgroups (tests), in ticks of 10 ns
   uint32_t poll_limit;    // polls after which a workgroup gives up waiting for its team
   int32_t n_classes, main_tiles, check_tiles;  // main: the (3,1) class in cls[0], if any
   TeamClass cls[kMaxClasses];

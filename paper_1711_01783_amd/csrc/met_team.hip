@@ -23,10 +23,14 @@
 //
 // Forming teams.  A workgroup reads the number of its XCD and registers with
 // that XCD's counter.  The first to register waits until the expected number
-// has arrived, or 20 us, and closes the registration; the team is who has
-// registered by then.  A workgroup that comes later exits.  Nobody ever waits
-// for a workgroup that is not running, so concurrent launches on other streams
-// or in other processes cannot block each other; they only make teams smaller.
+// has arrived, or 20 us; the team is who has registered by then.  Where other
+// work holds compute units at that moment, it is joined by those that come
+// later: the first member admits them at the end of an iteration, and hands
+// them the state of the decode.  Nobody ever waits for a workgroup that is not
+// running, so concurrent launches on other streams or in other processes cannot
+// block each other; they only make teams smaller while they run.  (Teams that
+// kept their first size: one frame of N = 65536 beside 64-frame decodes of
+// N = 300000 ran up to 11 ms, against 0.66 ms in the median.)
 //
 // The arithmetic is that of met_gpu.h's kernels, operation by operation, so
 // the results equal the per-phase launches' bit for bit.
@@ -41,7 +45,7 @@ namespace {
 constexpr int kTeamBlock = 1024;
 constexpr int kTeamWaves = kTeamBlock / 64;
 constexpr int kMaxTeam = 64;            // workgroups of one team
-constexpr uint32_t kClosed = 0x80000000u;
+constexpr uint32_t kEnded = 0x80000000u;
 constexpr uint64_t kFormTicks = 2000;   // 20 us of the 100 MHz counter
 constexpr uint32_t kPollLimit = 1u << 22;  // polls of about 0.4 us (TeamJob::poll_limit)
 
@@ -51,6 +55,8 @@ struct TeamControl {
   struct {
     uint32_t count, pad0[31];
     uint64_t pub, pad1[15];             // members + 256 (slot + 1) + 65536 group, set once
+    uint32_t grown, pad2[31];           // members with those admitted since, or kEnded
+    uint32_t state[5], stop[16], pad3[11];  // for those: epoch, group, iteration, frames that run, last
   } reg[kTeamSlots];
   uint64_t flag[kTeamSlots][2][kMaxTeam];  // epoch in the low word, payload in the high one
 };
@@ -518,6 +524,7 @@ __device__ __forceinline__ void variable_tile(const GroupState &s, const int32_t
 struct TeamShared {
   uint32_t rank, n, slot, group, err;
   uint32_t last;    // no group is left for this team after the present one
+  uint32_t epoch, it, act;  // where a member that was admitted later begins; it = 0: at the start
   uint32_t word;    // OR of the waves' payloads
   uint32_t result;  // OR of the members' payloads
   int32_t stop[16]; // iteration at which each frame of the group stopped, and kSatisfied
@@ -531,24 +538,34 @@ __device__ __forceinline__ uint64_t take_group(TeamControl *ctl, uint32_t slots)
   return __hip_atomic_fetch_add(&ctl->taken, (uint64_t)slots << 32 | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// A check's messages are read through the first-level cache, by the workgroup
+// that wrote them.  Where the checks change hands that cache may hold older ones.
+__device__ __forceinline__ void forget_cached() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
+
+__device__ __forceinline__ uint32_t ld_agent(const uint32_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Registers the workgroup with its XCD's team; false if it has no part in it.
 __device__ bool join_team(TeamControl *ctl, uint32_t xcc, const TeamJob &job, TeamShared &sh) {
   if (xcc >= (uint32_t)job.dies) return false;
   if (threadIdx.x == 0) {
     auto &r = ctl->reg[xcc];
-    sh.err = 0;
-    sh.word = 0;
+    const uint32_t expected = (uint32_t)job.expected;
+    if (job.late_ticks) {  // every eighth workgroup of a die comes in time
+      const uint64_t t0 = wall_clock64();
+      const uint64_t late = (uint64_t)job.late_ticks * (blockIdx.x / kTeamSlots % 8);
+      while (wall_clock64() - t0 < late) __builtin_amdgcn_s_sleep(8);
+    }
     const uint32_t rank = __hip_atomic_fetch_add(&r.count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     uint64_t pub = 0;
-    if (rank & kClosed) {
-      pub = 1;  // too late: no slot
-    } else if (rank == 0) {
+    if (rank == 0) {
       const uint64_t t0 = wall_clock64();
       const uint64_t first = take_group(ctl, 1);  // waited for after the loop
-      while (__hip_atomic_load(&r.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)job.expected &&
-             wall_clock64() - t0 < kFormTicks) {
-      }
-      const uint32_t n = __hip_atomic_fetch_or(&r.count, kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t n;
+      do {
+        n = ld_agent(&r.count);
+      } while (n < expected && wall_clock64() - t0 < kFormTicks);
       pub = min(n, (uint32_t)kMaxTeam);
       const uint32_t slot = (uint32_t)(first >> 32), g = (uint32_t)first;
       if (g < (uint32_t)job.G && slot < (uint32_t)job.n_slots) pub |= (slot + 1) << 8 | (uint64_t)g << 16;
@@ -560,10 +577,35 @@ __device__ bool join_team(TeamControl *ctl, uint32_t xcc, const TeamJob &job, Te
         __builtin_amdgcn_s_sleep(1);
       }
     }
+    sh.err = 0;
+    sh.word = 0;
     sh.rank = rank;
     sh.n = (uint32_t)pub & 255u;
     sh.slot = (uint32_t)(pub >> 8) & 255u;  // slot + 1, 0: nothing to do
     sh.group = (uint32_t)(pub >> 16);
+    sh.epoch = sh.it = sh.act = sh.last = 0;
+    if (sh.slot && rank >= sh.n) {
+      // too late for the start: until the first member admits it or ends
+      sh.slot = 0;
+      for (uint64_t i = 0; rank < expected && i < (uint64_t)job.poll_limit * 64; ++i) {
+        const uint32_t grown = ld_agent(&r.grown);
+        if (grown == kEnded) break;
+        if (rank < grown) {
+          // (the words below were in the L2 before `grown`)
+          asm volatile("" ::: "memory");
+          sh.slot = (uint32_t)(pub >> 8) & 255u;
+          sh.n = grown;
+          sh.epoch = ld_agent(&r.state[0]);
+          sh.group = ld_agent(&r.state[1]);
+          sh.it = ld_agent(&r.state[2]);
+          sh.act = ld_agent(&r.state[3]);
+          sh.last = ld_agent(&r.state[4]);
+          for (int f = 0; f < 16; ++f) sh.stop[f] = (int32_t)ld_agent(&r.stop[f]);
+          break;
+        }
+        __builtin_amdgcn_s_sleep(16);
+      }
+    }
   }
   __syncthreads();
   return sh.slot != 0 && sh.rank < sh.n;
@@ -607,6 +649,24 @@ struct TeamBarrier {
     return sh.result;
   }
 };
+
+// The first member hands the state after iteration `it - 1` to new members, which
+// begin with check update `it` and the team's barrier after it.
+__device__ void admit(TeamControl *ctl, uint32_t xcc, const TeamShared &sh, uint32_t n, uint32_t epoch, uint32_t g,
+                      int it, uint32_t act) {
+  if (threadIdx.x >= 64) return;
+  auto &r = ctl->reg[xcc];
+  if (threadIdx.x < 16) r.stop[threadIdx.x] = (uint32_t)sh.stop[threadIdx.x];
+  if (threadIdx.x == 0) {
+    r.state[0] = epoch;
+    r.state[1] = g;
+    r.state[2] = (uint32_t)it;
+    r.state[3] = act;
+    r.state[4] = sh.last;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (threadIdx.x == 0) __hip_atomic_store(&r.grown, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 template <int W, typename CT>
 __device__ __forceinline__ void check_phase(const TeamJob &job, const GroupState &s, const Phase &ph,
@@ -798,9 +858,9 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
     }
   __syncthreads();
   const Tables tab{s_q8, s_phi, s_code};
-  const uint32_t rank = sh.rank, n = sh.n, slot = sh.slot - 1;
-  TeamBarrier barrier{ctl, xcc, rank, n, job.poll_limit, 0};
-  const uint32_t wave = rank + n * (uint32_t)wave_id(), waves = n * kTeamWaves;
+  const uint32_t rank = sh.rank, slot = sh.slot - 1;
+  TeamBarrier barrier{ctl, xcc, rank, sh.n, job.poll_limit, sh.epoch};
+  uint32_t wave = rank + barrier.n * (uint32_t)wave_id(), waves = barrier.n * kTeamWaves;
   char *base = job.ws + job.off_slots + (size_t)slot * job.slot_bytes;
   auto buf = [&](uint32_t off, uint32_t end) { return buffer_of(base + off, end - off); };
   GroupState s;
@@ -815,19 +875,23 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
   s.b1_half = (job.slot_bytes - job.off_B1) / 2;
 
   uint32_t g = sh.group;
+  int it = (int)sh.it;
+  if (it) forget_cached();
+  uint32_t act = sh.act;
   while (g < (uint32_t)job.G) {
-    const uint32_t frames = min((uint32_t)W, (uint32_t)job.B - g * W);
-    uint32_t act = (1u << frames) - 1u;
-    if (threadIdx.x < W) sh.stop[threadIdx.x] = job.max_iter;
-    setup_phase<W>(job, s, g, wave, waves);
-    // where every group has been taken by now, the team need not meet again
-    // after its outputs
-    if (rank == 0 && threadIdx.x == 0 &&
-        (uint32_t)__hip_atomic_load(&ctl->taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (uint32_t)job.G)
-      sh.word = 1;
-    const uint32_t last = barrier(sh);
-    if (threadIdx.x == 0) sh.last = last;
-    int it = 1;
+    if (it == 0) {
+      act = (1u << min((uint32_t)W, (uint32_t)job.B - g * W)) - 1u;
+      if (threadIdx.x < W) sh.stop[threadIdx.x] = job.max_iter;
+      setup_phase<W>(job, s, g, wave, waves);
+      // where every group has been taken by now, the team need not meet again
+      // after its outputs
+      if (rank == 0 && threadIdx.x == 0 &&
+          (uint32_t)__hip_atomic_load(&ctl->taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (uint32_t)job.G)
+        sh.word = 1;
+      const uint32_t last = barrier(sh);
+      if (threadIdx.x == 0) sh.last = last;
+      it = 1;
+    }
     for (; it <= job.max_iter && !sh.err; ++it) {
       Phase ph;
       ph.first = it == 1;
@@ -845,7 +909,19 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
         if (!act) break;
       }
       variable_phase<W, CT>(job, s, act, wave, waves, tab);
-      barrier(sh);
+      // a team that is not complete takes in who has registered since
+      if (rank == 0 && threadIdx.x == 0 && barrier.n < (uint32_t)job.expected && it < job.max_iter) {
+        const uint32_t n = min(ld_agent(&ctl->reg[xcc].count), (uint32_t)job.expected);
+        if (n > barrier.n) sh.word = n;
+      }
+      const uint32_t grown = barrier(sh);
+      if (grown && !sh.err) {
+        forget_cached();
+        barrier.n = grown;
+        wave = rank + grown * (uint32_t)wave_id();
+        waves = grown * kTeamWaves;
+        if (rank == 0) admit(ctl, xcc, sh, grown, barrier.epoch, g, it + 1, act);
+      }
     }
     if (act && !sh.err) {  // frames that ran the whole budget
       test_phase<W>(job, s, job.max_iter, wave, waves, sh);
@@ -856,7 +932,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
     const bool mine = threadIdx.x < min((uint32_t)W, (uint32_t)job.B - g * W);  // a thread per frame
     if (sh.err) {
       if (mine) give_up(job, g * W + threadIdx.x);
-      return;
+      break;
     }
     // (both waited for after the outputs)
     uint32_t next = 0;
@@ -865,11 +941,14 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
     if (rank == 0 && mine) set = set_outcome(job, g * W + threadIdx.x, sh.stop[threadIdx.x]);
     output_phase<W>(job, s, g, wave, waves, sh);
     if (!set) job.converged[g * W + threadIdx.x] = 0;
-    if (sh.last) return;
+    if (sh.last) break;
     if (rank == 0 && threadIdx.x == 0) sh.word = next;
     g = barrier(sh);
-    if (sh.err) return;
+    if (sh.err) break;
+    it = 0;
   }
+  if (rank == 0 && threadIdx.x == 0)
+    __hip_atomic_store(&ctl->reg[xcc].grown, kEnded, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 template <int W, typename CT>
@@ -1020,6 +1099,7 @@ int team_decode(const met_code *c, const DeviceCode *d, int W, const float *llr,
   job.early = !(flags & MET_FIXED_ITERS);
   job.n_slots = std::min(job.G, kTeamSlots);
   job.dies = opt && opt->dies ? opt->dies : kTeamSlots;
+  job.late_ticks = opt ? 100u * (uint32_t)opt->late_us : 0u;
   job.poll_limit = opt && opt->polls ? (uint32_t)opt->polls : kPollLimit;
   job.off_slots = team_control_bytes();
   job.lanes_per_vn = lanes_per_vn(c, W);
