@@ -666,12 +666,21 @@ static size_t c2v_bytes(uint32_t flags) {
   return (flags & MET_C2V_FP16) ? sizeof(met::half_t) : sizeof(float);
 }
 
+// Flags that select the launches whatever the size.
+constexpr uint32_t kLaunchFlags = MET_NO_COMPACT | MET_NO_DEG1_SKIP;
+
 // The layout a decode with these flags runs on: the code's own, or its view
 // with degree-1 variable nodes iterated.
 static int decode_layout(const met_code *c, uint32_t flags, const met_code **out) {
   if (flags & MET_NO_DEG1_SKIP) return met::all_vns_view(c, out);
   *out = c;
   return MET_OK;
+}
+
+// What the launches need, and the teams where they may run.
+static size_t workspace_need(const met_code *c, int32_t B, uint32_t flags, bool post) {
+  const size_t plan = met::make_plan(c, B, post, false, met::choose_interleave(B), c2v_bytes(flags)).total;
+  return (flags & MET_NO_DEG1_SKIP) ? plan : std::max(plan, met::team_bytes(c, B, post, c2v_bytes(flags)));
 }
 
 extern "C" int met_decode_workspace_bytes(const met_code *c, int32_t B, uint32_t flags, int32_t want_posterior,
@@ -682,7 +691,7 @@ extern "C" int met_decode_workspace_bytes(const met_code *c, int32_t B, uint32_t
   if (!bytes) return fail(MET_EINVAL, "NULL bytes");
   rc = decode_layout(c, flags, &c);
   if (rc) return rc;
-  *bytes = met::make_plan(c, B, want_posterior != 0, false, met::choose_interleave(B), c2v_bytes(flags)).total;
+  *bytes = workspace_need(c, B, flags, want_posterior != 0);
   return MET_OK;
   });
 }
@@ -725,7 +734,7 @@ static int decode_checked(const met_code *c, const float *llr, const uint8_t *sy
   if (rc) return rc;
   const int W = met::choose_interleave(B);
   const met::Plan pl = met::make_plan(c, B, posterior != nullptr, false, W, c2v_bytes(flags));
-  const size_t need = whole ? pl.total : pl.launch_total;
+  const size_t need = whole ? workspace_need(c, B, flags, posterior != nullptr) : pl.total;
   if (ws_bytes < need) return fail(MET_EINVAL, "workspace of %zu bytes, %zu needed", ws_bytes, need);
   const met::DeviceCode *d = nullptr;
   rc = met::device_code(c, &d);
@@ -734,7 +743,7 @@ static int decode_checked(const met_code *c, const float *llr, const uint8_t *sy
   // shapes, for uncompacted groups or for degree-1 nodes iterated gets the
   // launches it asks for.
   const bool shaped = tuning && (tuning->check_steps_per_wave || tuning->variable_chunk);
-  if (!shaped && !(flags & (MET_NO_COMPACT | MET_NO_DEG1_SKIP))) {
+  if (!shaped && !(flags & kLaunchFlags)) {
     int tw = 0;
     rc = met::team_width(c, B, posterior != nullptr, c2v_bytes(flags), max_iter, !(flags & MET_FIXED_ITERS), ws_bytes,
                          &tw);
@@ -776,7 +785,7 @@ extern "C" int met_decode_teams(const met_code *c, const float *llr, const uint8
   if (rc) return rc;
   rc = check_buffers(llr, syn, max_iter, bits, iters, converged, posterior, workspace);
   if (rc) return rc;
-  if (flags & (MET_NO_COMPACT | MET_NO_DEG1_SKIP))
+  if (flags & kLaunchFlags)
     return fail(MET_EINVAL, "MET_NO_COMPACT and MET_NO_DEG1_SKIP select the launches, not the teams");
   if (!options) return fail(MET_EINVAL, "NULL options");
   const met_team_options &o = *options;
@@ -845,8 +854,8 @@ extern "C" int met_decode_noalloc(const met_code *c, const float *llr, const uin
   if (flags & MET_NO_DEG1_SKIP)
     return fail(MET_EINVAL, "MET_NO_DEG1_SKIP builds a second layout of the code (allocates): not here");
   const met::Plan pl = met::make_plan(c, B, posterior != nullptr, false, met::choose_interleave(B), c2v_bytes(flags));
-  if (pl.launch_total > kScratchBytes)
-    return fail(MET_EINVAL, "decode needs %zu bytes of workspace, the fixed scratch array holds %zu", pl.launch_total,
+  if (pl.total > kScratchBytes)
+    return fail(MET_EINVAL, "decode needs %zu bytes of workspace, the fixed scratch array holds %zu", pl.total,
                 kScratchBytes);
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));

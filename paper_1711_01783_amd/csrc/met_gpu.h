@@ -1179,8 +1179,7 @@ struct Plan {
   int W = 64, G = 1;
   size_t off_c2v = 0, off_P = 0, off_L2 = 0, off_Lphi = 0, off_Lraw = 0, off_P1 = 0, off_synw = 0, off_B1 = 0,
          off_unsat = 0, off_active = 0, off_slot = 0, off_ctab = 0, off_flag = 0;
-  size_t launch_total = 0;  // what the per-phase launches need
-  size_t total = 0;         // with the extra room of the team decoder (its slots reuse the arrays above)
+  size_t total = 0;
   bool lraw = false, p1 = false;
 };
 
@@ -1225,10 +1224,6 @@ Plan make_plan(const met_code *c, int B, bool post, bool weighted, int W, size_t
   pl.off_slot = take(GW * sizeof(int32_t));
   pl.off_ctab = take(compact_table_bytes(pl.G));
   pl.off_flag = take(sizeof(uint32_t));
-  pl.launch_total = o;
-  // control words, padding, and twice the bytes of the syndrome and decision
-  // words where a group of 64 is cut into groups of 8 or 16
-  if (!weighted) (void)take((64u << 10) + (W == 64 ? (size_t)pl.G * 8 * (c->M + 2 * c->EL) : 0));
   pl.total = o;
   return pl;
 }

@@ -49,6 +49,9 @@ size_t team_control_bytes();
 int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, int max_iter, bool early, size_t ws_bytes,
                int *width);
 
+// Bytes of workspace with which team_width is free in its choice.
+size_t team_bytes(const met_code *c, int B, bool post, size_t c2v_bytes);
+
 // Whether the teams' states in groups of W frames fit in a workspace.
 bool team_fits(const met_code *c, int B, bool post, size_t c2v_bytes, int W, size_t ws_bytes);
 

@@ -1143,6 +1143,18 @@ int team_decode(const met_code *c, const DeviceCode *d, int W, const float *llr,
   return MET_OK;
 }
 
+// What the widest groups take that team_width would choose on eight dies: none
+// wider than the narrowest that hold the batch in one round.
+size_t team_bytes(const met_code *c, int B, bool post, size_t c2v_bytes) {
+  size_t most = 0;
+  const int narrowest = c2v_bytes == sizeof(float) ? 1 : 4;
+  for (int W = narrowest; W <= 16 && (W == narrowest || B > W / 2 * kTeamSlots); W *= 2) {
+    const size_t slot = team_slot(c, W, post, c2v_bytes, nullptr), all = slot * std::min((B + W - 1) / W, kTeamSlots);
+    if (slot < kMaxSlotBytes && all <= kMaxTeamBytes) most = std::max(most, team_control_bytes() + all);
+  }
+  return most;
+}
+
 // Whether the teams' states in groups of W frames fit in ws_bytes.
 bool team_fits(const met_code *c, int B, bool post, size_t c2v_bytes, int W, size_t ws_bytes) {
   const size_t slot = team_slot(c, W, post, c2v_bytes, nullptr);
