@@ -296,12 +296,13 @@ int met_decode(const met_code *c, const float *llr, const uint8_t *syn, int32_t 
  * graph capture, tight serving loops, harnesses that forbid hipMalloc).  The
  * same decoder, arguments and results as met_decode without the workspace
  * arguments: the workspace is a fixed array of MET_NOALLOC_SCRATCH_BYTES bytes
- * inside the library, one per device, held from the library's first use of a
+ * (and 1 MiB for frames' flags) inside the library, one per device, held from the library's first use of a
  * device until the process ends.  No call allocates, frees or uploads:
  *   - the code's adjacency must already be on the current device (an earlier
  *     met_decode or met_syndrome on that device uploads it); else MET_ESTATE;
- *   - decodes whose workspace (met_decode_workspace_bytes) exceeds the array
- *     fail with MET_EINVAL (without posteriors the array holds, at the three
+ *   - decodes whose arrays exceed MET_NOALLOC_SCRATCH_BYTES fail with
+ *     MET_EINVAL (met_decode_workspace_bytes also counts the 1 KiB of flags per
+ *     group of frames and the room that teams would like; without posteriors the array holds, at the three
  *     profiles' sizes, N = 65536 with up to 192 frames, N = 2^18 with 32,
  *     N = 10^6 with 4);
  *   - MET_NO_DEG1_SKIP (which builds a second layout) is MET_EINVAL;

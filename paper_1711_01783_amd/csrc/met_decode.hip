@@ -822,7 +822,14 @@ extern "C" int met_decode(const met_code *c, const float *llr, const uint8_t *sy
 // the host it is only a stand-in): the device address is looked up once per
 // device with hipGetSymbolAddress and kept.
 namespace {
-constexpr size_t kScratchBytes = (size_t)MET_NOALLOC_SCRATCH_BYTES;
+// A decode is taken if its arrays with one word of flags per group fit in
+// MET_NOALLOC_SCRATCH_BYTES; the bytes that the flags take beyond that word
+// have room of their own, so that they shut out no decode.
+size_t flag_bytes_beyond_words(int G) {
+  return 2 * (size_t)G * met::kUnsatWords * sizeof(uint64_t) - met::align256(2 * (size_t)G * sizeof(uint64_t));
+}
+constexpr size_t kScratchBytes =
+    (size_t)MET_NOALLOC_SCRATCH_BYTES + 2 * (size_t)met::kMaxGroups * met::kUnsatWords * sizeof(uint64_t);
 static __device__ __align__(256) char scratch[kScratchBytes];
 
 std::mutex g_scratch_mu;
@@ -854,9 +861,10 @@ extern "C" int met_decode_noalloc(const met_code *c, const float *llr, const uin
   if (flags & MET_NO_DEG1_SKIP)
     return fail(MET_EINVAL, "MET_NO_DEG1_SKIP builds a second layout of the code (allocates): not here");
   const met::Plan pl = met::make_plan(c, B, posterior != nullptr, false, met::choose_interleave(B), c2v_bytes(flags));
-  if (pl.total > kScratchBytes)
-    return fail(MET_EINVAL, "decode needs %zu bytes of workspace, the fixed scratch array holds %zu", pl.total,
-                kScratchBytes);
+  const size_t need = pl.total - flag_bytes_beyond_words(pl.G);
+  if (need > (size_t)MET_NOALLOC_SCRATCH_BYTES)
+    return fail(MET_EINVAL, "decode needs %zu bytes of workspace, the fixed scratch array holds %zu", need,
+                (size_t)MET_NOALLOC_SCRATCH_BYTES);
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
   if (dev < 0 || dev >= met::kMaxDevices) return fail(MET_EINVAL, "device %d beyond %d", dev, met::kMaxDevices);

@@ -1,5 +1,6 @@
 """Workspaces hold what the path that runs needs: the team decoder's room only where a
-decode may run by teams, and none in the batched form."""
+decode may run by teams, none in the batched form, and the fixed array of
+met_decode_noalloc takes every decode that fits without the frames' flag bytes."""
 import ctypes
 
 import pytest
@@ -61,3 +62,28 @@ def test_a_workspace_for_more_frames_serves_fewer():
         for kw in (dict(c2v_fp16=True), dict(c2v_q8=True, posterior=True)):
             need = [met.workspace_bytes(code, b, **kw) for b in range(33, 300)]
             assert need == sorted(need)
+
+
+@pytest.mark.parametrize("n,b", [(4209, 3904), (4357, 3776), (4096, 3968), (65536, 192)])
+def test_noalloc_takes_what_it_took(n, b):
+    """Decodes whose arrays fit in the fixed array with a word of flags per group are
+    not refused for their size (they fail later: the code is on no device), and
+    those beyond it are."""
+    code = met.Code.build(PROFILES["r0.1"], n, 3)
+    size = _lib.MET_NOALLOC_SCRATCH_BYTES
+
+    def before(frames):  # with one word per group and buffer for the flags
+        g = -(-frames // 64)
+        return _launches(code, frames) - FLAGS * g + _a256(16 * g)
+
+    assert before(b) <= size < before(b + 64)
+    P = ctypes.c_void_p
+
+    def call(frames):
+        return _lib.lib.met_decode_noalloc(code.handle, P(256), P(256), frames, 10, 0, P(256), P(256), P(256), None, None)
+
+    def refused(frames):
+        rc = call(frames)
+        return rc == -1 and "scratch" in _lib.lib.met_last_error().decode()
+
+    assert not refused(b) and refused(b + 64)
