@@ -169,10 +169,13 @@ def _require(t, dtype, shape, name):
         raise ValueError("%s must be contiguous" % name)
 
 
-# Bits gathered (frames x edges) from which the packed syndrome pays: below, the
-# one plain launch (4.1 us per million gathers) is hidden by the call's own 10 us
-# on the host, to which the workspace and the second launch add 4.
-_PACKED_SYNDROME_GATHERS = 8000000
+# Bits gathered (frames x edges) from which the packed syndrome pays.  Calls in a
+# row, and alone with the wait for the result (us, plain / packed; N = 4096 to
+# 10^6, 2 to 256 frames): 4 million gathers 10-14 / 15.4 and 26-31 / 26-30, 8
+# million 17-25 / 15.4 and 34-42 / 27-36, 16 million 32-49 / 15-16 and 49-67 /
+# 30-36.  (The plain launch takes 2 to 3 us per million, of which the call's own
+# 10 us on the host hide the first; workspace and second launch add 5 there.)
+_PACKED_SYNDROME_GATHERS = 6000000
 
 
 def syndrome(code: Code, bits, stream=None):
