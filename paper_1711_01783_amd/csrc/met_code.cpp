@@ -94,8 +94,7 @@ struct PairCounts {
 
 }  // namespace
 
-// Derived structures for the decoder: message/leaf split, VN edge lists,
-// check classes.
+// Edge types of a run of checks of one shape (CheckClass::types).
 static int32_t class_types(const met_code *c, const CheckClass &k) {
   if (k.n_msg == 0) return -1;
   const int8_t *m = c->edge_type_msg.data() + k.first_msg, *l = c->leaf_type.data() + k.first_leaf;
@@ -107,6 +106,8 @@ static int32_t class_types(const met_code *c, const CheckClass &k) {
   return m[0] | (nl ? l[0] << 8 : 0);
 }
 
+// Derived structures for the decoder: message/leaf split, VN edge lists,
+// check classes.
 int finalize_code(met_code *c, bool skip_deg1) {
   const int64_t N = c->N, M = c->M, E = c->E;
   std::vector<int32_t> deg(N, 0);

@@ -474,7 +474,7 @@ __device__ __forceinline__ uint32_t leaf_bit(uint32_t neg_l, uint32_t neg_c, flo
 
 // The same with the signs as conditions, which are scalar lane masks.
 __device__ __forceinline__ bool leaf_cond(bool neg_l, bool neg_c, float S, float A) {
-  const bool decided = !(isinf(A) & isinf(S));
+  const bool decided = !((int)isinf(A) & (int)isinf(S));
   return (neg_l & neg_c & decided) | ((neg_l != neg_c) & (((S < A) & neg_c) | ((S > A) & neg_l)));
 }
 

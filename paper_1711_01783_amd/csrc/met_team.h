@@ -34,7 +34,7 @@ struct TeamJob {
   int32_t dies;           // workgroups on an XCD of this number or above take no part
   uint32_t late_ticks;    // delays of workgroups (tests), in ticks of 10 ns
   uint32_t poll_limit;    // polls after which a workgroup gives up waiting for its team
-  int32_t n_classes, main_tiles, check_tiles;  // main: the (3,1) class in cls[0], if any
+  int32_t n_classes, check_tiles;
   TeamClass cls[kMaxClasses];
 };
 

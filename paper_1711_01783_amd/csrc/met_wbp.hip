@@ -71,10 +71,10 @@ __device__ __forceinline__ float expm1_nonpos(float y) {
   return y > -0.35f ? series : direct;
 }
 
-// Adjoint of one check's update: compile-time shape (NM message + NL leaf
-// inputs) when NM > 0, run-time degrees (up to MET_MAX_CHECK_DEGREE) otherwise.
 constexpr int kMaxAdjDegree = 16;  // run-time-degree checks in weighted BP
 
+// Adjoint of one check's update: compile-time shape (NM message + NL leaf
+// inputs) when NM > 0, run-time degrees (up to kMaxAdjDegree) otherwise.
 //
 // UNI: the class has one type of message edges and another of leaf edges (every
 // class of the built profiles; ClassArgs.types), so a lane sums two values
@@ -301,8 +301,9 @@ __global__ __launch_bounds__(kBlock) void k_check_adj(const AdjParams p, const C
 
 // The classes of compiled shapes but the largest in one launch: each lasts 5-14
 // us however few its checks are (32 frames of N = 262144: 14.2 + 6.6 + 4.8 us
-// apart, 14.8 together; training step 13.3 to 12.5 ms).  The largest keeps a launch of its own: beside the wide
-// bodies' 120 registers it would have half of its waves in flight.
+// apart, 14.8 together; training step 13.3 to 12.5 ms).  The largest keeps a
+// launch of its own: beside the wide bodies' 120 registers it would have half of
+// its waves in flight.
 struct AdjSet {
   int32_t n;
   int32_t block0[kMaxClasses + 1];  // first block of each class, and the end
