@@ -398,86 +398,98 @@ __device__ __forceinline__ void check_tile(const GroupState &s, const int32_t *e
   }
 }
 
-// Run-time degrees, frame by frame.  The suffix sums of a check are kept in
-// private memory and its inputs formed twice: few checks take this path, and
+// Run-time degrees, one lane per frame.  A check's inputs are formed once, U
+// message rows at a time, and kept with their suffix sums in private memory:
 // arrays of the largest degree in registers would set the whole kernel's
 // register count.
 template <int W, typename CT>
 __device__ __forceinline__ void check_tile_generic(const GroupState &s, const TeamJob &job, const TeamClass &c,
                                                    uint32_t tile, const Phase &ph, const Tables &tab,
                                                    uint32_t &unsat) {
-  constexpr int F = kFramesPerLane<W>, LPI = W / F;
-  const uint32_t lane = threadIdx.x & 63, wl = lane % LPI;
-  const uint32_t i = tile * (64 / LPI) + lane / LPI;
+  constexpr int FW = kFramesPerLane<W>, WPI = W / FW, U = 8;
+  const uint32_t lane = threadIdx.x & 63, w = lane % W;
+  const uint32_t i = tile * (64 / W) + lane / W;
   const bool valid = i < (uint32_t)c.n_checks;
   const uint32_t chk = (uint32_t)c.first_check + (valid ? i : 0u);
   const uint32_t m0 = (uint32_t)job.chk_msg_ptr[chk], l0 = (uint32_t)job.chk_leaf_ptr[chk];
   const int nm = (int)((uint32_t)job.chk_msg_ptr[chk + 1] - m0);
-  const int n = nm + (int)((uint32_t)job.chk_leaf_ptr[chk + 1] - l0);
+  const int nl = (int)((uint32_t)job.chk_leaf_ptr[chk + 1] - l0);
   const uint32_t b1_in = ((ph.it - 1) & 1) ? s.b1_half : 0u, b1_out = (ph.it & 1) ? s.b1_half : 0u;
-  const uint32_t sb = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(s.syn, chk * LPI + wl, 0, kSc1);
-  uint32_t word = 0;
+  const bool on = (ph.act >> w) & 1u;
+  auto bit_of = [&](rsrc_t r, uint32_t at) {
+    return ((uint8_t)__builtin_amdgcn_raw_buffer_load_b8(r, at + w / FW, 0, kSc1) >> (w % FW)) & 1u;
+  };
+  float in[MET_MAX_CHECK_DEGREE], suf[MET_MAX_CHECK_DEGREE];  // inputs in the phi domain with their signs
+  float run = 0.0f;
+  uint32_t parity = bit_of(s.syn, chk * WPI), tot = parity;
 #pragma unroll 1
-  for (int f = 0; f < F; ++f) {
-    const uint32_t w = wl * F + f;
-    const bool on = (ph.act >> w) & 1u;
-    // phi-domain input k with its sign; *decided: the parity of its decision
-    auto input = [&](int k, uint32_t *decided) {
-      if (k < nm) {
-        float pv[1], cv[1] = {0.0f};
-        ld_f32<1, kSc1>(ph.first ? s.L2 : s.P, ((uint32_t)job.edge_msgvn[m0 + k] * W + w) * 4u, pv);
-        if (!ph.first) ld_msgs<1, CT, 0>(s.c2v, (m0 + k) * W + w, tab, cv);
-        *decided ^= (uint32_t)(pv[0] < 0.0f);
-        const float x = clamp_llr(pv[0] - cv[0]);
-        return copysignf(phi(fabsf(x)), x);
-      }
-      const uint32_t le = l0 + (k - nm);
-      float lf[1];
-      ld_f32<1, kSc1>(s.Lphi, (le * W + w) * 4u, lf);
-      if (ph.test)
-        *decided ^= ((uint8_t)__builtin_amdgcn_raw_buffer_load_b8(s.B1, b1_in + le * LPI + wl, 0, kSc1) >> f) & 1u;
-      return lf[0];
-    };
-    float suf[MET_MAX_CHECK_DEGREE];
-    float run = 0.0f;
-    uint32_t parity = (sb >> f) & 1u, tot = parity, unused = 0;
+  for (int l = nl - 1; l >= 0; --l) {
+    float lf[1];
+    ld_f32<1, kSc1>(s.Lphi, ((l0 + l) * W + w) * 4u, lf);
+    if (ph.test) parity ^= bit_of(s.B1, b1_in + (l0 + l) * WPI);
+    in[nm + l] = lf[0];
+    suf[nm + l] = run;
+    run = run + fabsf(lf[0]);
+    tot ^= sign_bit(lf[0]);
+  }
 #pragma unroll 1
-    for (int k = n - 1; k >= 0; --k) {
-      const float a = input(k, &parity);
-      suf[k] = run;
-      run = run + fabsf(a);
-      tot ^= sign_bit(a);
+  for (int k = nm; k > 0; k -= U) {
+    uint32_t vi[U];
+    float pv[U][1], cv[U][1];
+#pragma unroll
+    for (int u = 0; u < U; ++u) vi[u] = (uint32_t)job.edge_msgvn[m0 + max(k - 1 - u, 0)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      ld_f32<1, kSc1>(ph.first ? s.L2 : s.P, (vi[u] * W + w) * 4u, pv[u]);
+      cv[u][0] = 0.0f;
+      if (!ph.first) ld_msgs<1, CT, 0>(s.c2v, (m0 + max(k - 1 - u, 0)) * W + w, tab, cv[u]);
     }
-    if (ph.test && valid) word |= (parity & 1u) << w;
-    run = 0.0f;
-#pragma unroll 1
-    for (int k = 0; k < n; ++k) {
-      const float a = input(k, &unused);
-      const float S = run + suf[k];
-      run = run + fabsf(a);
-      const uint32_t neg = sign_bit(a), neg_c = (tot ^ neg) & 1u;
-      const float mag = phi(S);
-      if (k < nm) {
-        const float out[1] = {neg_c ? -mag : mag};
-        if (valid) st_msgs<1, CT>(s.c2v, (m0 + k) * W + w, out);
-      } else if (ph.decide && valid && on) {
-        const uint32_t le = l0 + (k - nm), at = b1_out + le * LPI + wl;
-        const uint32_t bit = leaf_bit(neg, neg_c, S, fabsf(a));
-        // this thread's own byte: the decisions of its F frames, one by one
-        const uint32_t was = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(s.B1, at, 0, kSc1);
-        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)((was & ~(1u << f)) | (bit << f)), s.B1, at, 0, 0);
-        if (ph.post) {
-          float lr[1];
-          const uint32_t off = (le * W + w) * 4u;
-          ld_f32<1, kSc1>(s.Lraw(), off, lr);
-          const float p1[1] = {lr[0] + 1.0f * (neg_c ? -mag : mag)};
-          st_f32<1>(s.P1(ph.it), off, p1);
-        }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (k - 1 - u >= 0) {
+        parity ^= (uint32_t)(pv[u][0] < 0.0f);
+        const float x = clamp_llr(pv[u][0] - cv[u][0]);
+        const float a = phi(fabsf(x));
+        in[k - 1 - u] = copysignf(a, x);
+        suf[k - 1 - u] = run;
+        run = run + a;
+        tot ^= sign_bit(x);
       }
+  }
+  if (ph.test) {
+    const uint64_t bad[1] = {__ballot((parity & (uint32_t)valid) != 0u)};
+    unsat |= frames_of<W, 1>(bad);
+  }
+  run = 0.0f;
+#pragma unroll 1
+  for (int k = 0; k < nm; ++k) {
+    const float a = in[k], mag = phi(run + suf[k]);
+    run = run + fabsf(a);
+    const float out[1] = {(tot ^ sign_bit(a)) & 1u ? -mag : mag};
+    if (valid) st_msgs<1, CT>(s.c2v, (m0 + k) * W + w, out);
+  }
+  const int leaves = ph.decide && valid ? nl : 0;
+#pragma unroll 1
+  for (int l = 0; __any(l < leaves); ++l) {
+    const bool has = l < leaves;
+    const float a = has ? in[nm + l] : 0.0f, S = run + (has ? suf[nm + l] : 0.0f);
+    run = run + fabsf(a);
+    const uint32_t neg = sign_bit(a), neg_c = (tot ^ neg) & 1u, le = l0 + l;
+    const uint64_t ones = __ballot(has && leaf_bit(neg, neg_c, S, fabsf(a)));
+    if (has && w % FW == 0) {  // the byte of FW frames
+      const uint32_t at = b1_out + le * WPI + w / FW, own = (ph.act >> w) & ((1u << FW) - 1u);
+      const uint32_t was = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(s.B1, at, 0, kSc1);
+      __builtin_amdgcn_raw_buffer_store_b8((uint8_t)((was & ~own) | ((uint32_t)(ones >> lane) & own)), s.B1, at, 0, 0);
+    }
+    if (has && on && ph.post) {
+      const float mag = phi(S);
+      float lr[1];
+      const uint32_t off = (le * W + w) * 4u;
+      ld_f32<1, kSc1>(s.Lraw(), off, lr);
+      const float p1[1] = {lr[0] + 1.0f * (neg_c ? -mag : mag)};
+      st_f32<1>(s.P1(ph.it), off, p1);
     }
   }
-#pragma unroll
-  for (int w = 0; w < W; ++w) unsat |= __ballot((word >> w) & 1u) ? 1u << w : 0u;
 }
 
 // Variable update of 64 / (W K) nodes: K lanes share a node's edges, each with U
@@ -1113,7 +1125,7 @@ int team_decode(const met_code *c, const DeviceCode *d, int W, const float *llr,
     t.n_checks = (int32_t)k.n_checks;
     t.first_msg = (int32_t)k.first_msg;
     t.first_leaf = (int32_t)k.first_leaf;
-    const bool wide = k.shape != kShapeGeneric && kShapeMsg[k.shape] > 4;
+    const bool wide = k.shape == kShapeGeneric || kShapeMsg[k.shape] > 4;
     const int per = 64 / (wide ? W : W / std::min(W, 4));  // checks per wave, as check_tile
     tiles += (int32_t)((k.n_checks + per - 1) / per);
   }
