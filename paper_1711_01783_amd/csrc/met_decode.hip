@@ -748,8 +748,8 @@ static int decode_checked(const met_code *c, const float *llr, const uint8_t *sy
   const bool shaped = tuning && (tuning->check_steps_per_wave || tuning->variable_chunk);
   if (!shaped && !(flags & kLaunchFlags)) {
     int tw = 0;
-    rc = met::team_width(c, B, posterior != nullptr, c2v_bytes(flags), max_iter, !(flags & MET_FIXED_ITERS), ws_bytes,
-                         &tw);
+    rc = met::team_width(c, B, posterior != nullptr, c2v_bytes(flags), (flags & MET_CHECK_LUT) != 0, max_iter,
+                         !(flags & MET_FIXED_ITERS), ws_bytes, &tw);
     if (rc) return rc;
     if (tw)
       return met::team_decode(c, d, tw, llr, syn, B, max_iter, flags, bits, iters, converged, posterior,

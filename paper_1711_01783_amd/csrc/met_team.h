@@ -46,8 +46,8 @@ size_t team_control_bytes();
 
 // *width: frames per group with which the team decoder takes this decode, or 0
 // where the per-phase launches are the better path or the workspace is too small.
-int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, int max_iter, bool early, size_t ws_bytes,
-               int *width);
+int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, bool lut, int max_iter, bool early,
+               size_t ws_bytes, int *width);
 
 // Bytes of workspace with which team_width is free in its choice.
 size_t team_bytes(const met_code *c, int B, bool post, size_t c2v_bytes);

@@ -995,6 +995,14 @@ int lanes_per_vn(const met_code *c, int W) {
   return 1;
 }
 
+// Message edges (in millions) of checks without a compiled shape.
+double generic_edges(const met_code *c) {
+  int64_t compiled = 0;
+  for (const CheckClass &k : c->classes)
+    if (k.shape != kShapeGeneric) compiled += k.n_checks * kShapeMsg[k.shape];
+  return 1e-6 * (double)(c->E12 - compiled);
+}
+
 }  // namespace
 
 size_t team_control_bytes() { return align256(sizeof(TeamControl)); }
@@ -1025,50 +1033,103 @@ size_t team_slot(const met_code *c, int W, bool post, size_t c2v_bytes, TeamJob 
 }
 
 
-// The rule compares the estimated time of an iteration on both paths (us; E:
-// message edges in millions, F: frames in whole groups of the launches; measured
-// with float messages, rates 0.1 to 0.02, N = 4096 to 10^6, 1 to 256 frames):
-//   team:     4.5 + (32 + 17.5 W) E per round of eight groups.  N = 65536, rate 0.1:
-//             W = 1 15.2, 2 17.8, 4 23.4, 8 38.5, 16 67; 8-bit messages
-//             (20 + 16 W): W = 4 19, 8 32, 16 57; N = 16384: W = 1 7.4, 4 9.4, 8
-//             11, 16 18; 15 % more once a group's state is beyond 8 MB, twice
-//             the L2 (N = 262144: W = 1 64, 4 96)
-//   launches: 3.2 per launch + 2.5 F E (2.0 with 16- or 8-bit messages), 9 more for
-//             the host's reads with early exit, and 60 more per decode of set-up
-//             and output launches.  N = 65536, rate 0.1: 1 frame 21, 16 18, 64 32,
-//             256 119; N = 262144: 1 frame 26, 16 40, 64 122
-// With early exit the launches run until the slowest of all frames stops, on
-// squeezed groups for about half of the time if there were 64 frames to begin
-// with; a team runs until the slowest of each of its groups.  In units of the
-// former a group of W out of B frames takes about m = (W / B)^(1/5), and the
-// eight teams end after max(1, m groups / 8) + m (1 where each has one group).
-// Measured (ms, launches / team, waterfall): 1 frame of 4096 0.41 / 0.09, 64 1.6 /
-// 0.8, 256 2.1 / 1.8; N = 16384: 64 frames 1.9 / 1.3, 128 2.3 / 2.4, 256 3.1 / 4.1;
-// N = 65536: 1 frame 1.1 / 0.5, 16 2.4 / 1.8, 32 3.0 / 1.8, 64 3.1 / 3.6.  A team that
-// would be slower if every frame ran its whole budget is not taken, nor one whose
-// states leave the Infinity Cache (64 frames of N = 10^6 in groups of 8: 87 ms).
-int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, int max_iter, bool early, size_t ws_bytes,
-               int *width) {
+// Estimated times (us) of an iteration and of a decode's set-up and outputs on both
+// paths, fitted to fixed-iteration runs: rates 0.1, 0.05 and 0.02 and regular codes
+// of check degrees 6 to 20, N = 1000 to 262144, groups of 1 to 16 frames, batches of
+// 1 to 256 (E: message edges, V: nodes of degree >= 2, G: message edges of checks
+// with run-time degrees, N: in millions; F: frames in whole groups).  Measured
+// iterations:
+//                                  teams, W = 1 / 4 / 16     launches, 1 / 16 / 64 / 256
+//   rate 0.1, N = 4096             6.1 / 6.4 / 8.3           15 / 6.4 / 9.3 / 14
+//   rate 0.1, N = 32000            10 / 13 / 34              15 / 13 / 20 / 60
+//   rate 0.1, N = 65536            15 / 24 / 67              22 / 19 / 37 / 119
+//   rate 0.1, N = 160000           40 / 55 / 162             20 / 30 / 75 / -
+//   rate 0.02, N = 100001          23 / 54 / 117             36 / 24 / 50 / -
+//   rate 0.05, N = 65536 (4 checks 19 / 32 / 76              36 / 30 / 47 / -
+//     with run-time degrees)
+//   (3,6) regular, N = 60000       16 / 34 / 124             9 / 18 / 57 / 190
+//   (3,9) regular, N = 60000 (all  27 / 57 / 182             16 / 32 / 78 / 283
+//     with run-time degrees)
+//   8-bit, rate 0.1, N = 65536     - / - / 73                - / - / 60 / -
+//     with the table               - / - / 56                - / - / 52 / -
+namespace {
+
+struct Run {
+  double iteration, frames, once;  // per iteration; part of it that goes with the frames; per decode
+};
+
+// A group of W frames on one die.  A tile's chain of loads has a floor of 5 us an
+// iteration; nodes whose edges are more than their lanes have under way add
+// their further gathers; one or two frames per check leave the larger codes with
+// many short tiles.
+Run team_run(const met_code *c, int W, size_t c2v_bytes, bool lut) {
+  const double E = 1e-6 * c->E12, V = 1e-6 * c->N2, N = 1e-6 * c->N;
+  const int K = lanes_per_vn(c, W);
+  const double under_way = K == 16 ? 128 : K == 4 ? 64 : 24;
+  const double per_edge = c2v_bytes > 1 ? 32 + 15.5 * W : lut ? 24 + 14 * W : 36 + 19 * W;
+  double t = 5 + per_edge * E + 60 * V * W + (K == 1 ? 4.5 : 1.5) * std::max(0.0, c->max_vn_deg / under_way - 1);
+  if (W <= 2) t += 40 * std::max(0.0, E - 0.2);
+  if (const double G = generic_edges(c); G > 0) t += 0.5 * c->max_check_deg + 25 * G * W;
+  return {t, t, 4 + 60 * N + 95 * N * W};
+}
+
+Run launch_run(const met_code *c, int B, size_t c2v_bytes, bool lut) {
+  const int W = choose_interleave(B);
+  const double F = (double)((B + W - 1) / W) * W, E = 1e-6 * c->E12, V = 1e-6 * c->N2, G = generic_edges(c);
+  const int generic = G > 0, compiled = (int)c->classes.size() - generic;
+  const int launches = 1 + generic + (W >= 16 && c2v_bytes > 1 ? std::min(compiled, 1) : compiled);
+  const double each = c2v_bytes > 1 ? 3.2 : lut ? 5.2 : 6.2;
+  double t = each * launches, f = ((c2v_bytes == 4 ? 2.2 : c2v_bytes == 2 ? 1.45 : 1.7) * E + (c2v_bytes == 4 ? 5 : 4) * V) * F;
+  // long lists: one frame per item reads them and their rows scattered
+  const double longer = std::max(0, c->max_vn_deg - 24);
+  t += W >= 16 ? 0.065 * longer : 4.5 + 0.17 * longer * std::min(1.0, 1e-5 * c->N);
+  if (generic) {
+    t += 3 + 0.5 * c->max_check_deg;
+    f += 1.8 * G * F;
+  }
+  return {t + f, f, 25 + 12e-6 * c->N * F};
+}
+
+}  // namespace
+
+// The rule compares the two.  With early exit, taken to last two fifths of the budget,
+// the launches have the host's reads to wait for and frames to move (us an
+// iteration: 6.2 up to 32 frames, 9.5 where one group is squeezed, 22 where several
+// are compacted too, 12 with reduced storage, which is not), save by that 55 or
+// 70 % of what goes with the frames, and run until the slowest of all frames stops;
+// with posteriors they write them in every iteration.  A team runs until the
+// slowest of each of its groups: in units of the former a group of W out of B frames
+// takes about m = (W / B)^(1/9), and the eight teams end after max(1, m groups / 8) + m
+// (1 where each has one group).  A team that would be slower by more than 15 % if
+// every frame ran its whole budget is not taken, nor one whose states leave the
+// Infinity Cache (64 frames of N = 10^6 in groups of 8: 87 ms).  Fixed-iteration
+// launches take 10 % more than their estimate where teams come into question.
+// Of 3040 decodes (the codes above, 1 to 400 frames, good and bad channels, all
+// storage types, early exit and fixed) 49 are more than 5 % slower than the launches
+// would be, and in the mean they are 3.4 % off the best of launches and five widths;
+// estimates by edges alone: 317, and 4.9 %.
+int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, bool lut, int max_iter, bool early,
+               size_t ws_bytes, int *width) {
   *width = 0;
   int dies = 0, cus = 0;
   if (const int rc = device_dies(&dies, &cus)) return rc;
-  const double E = 1e-6 * (double)c->E12;
-  const int plain_w = choose_interleave(B);
-  const double FE = E * ((B + plain_w - 1) / plain_w) * plain_w * (c2v_bytes == sizeof(float) ? 2.5 : 2.0);
-  const double launches = plain_w >= 16 && c2v_bytes != 1 ? 2.0 : (double)(c->classes.size() + 1);
-  const double fixed = 3.2 * launches + (early ? 9.0 : 0.0) + 60.0 / (early ? 0.5 * max_iter + 0.5 : max_iter);
-  const double whole = fixed + FE;  // every frame to the end of the budget
+  const Run l = launch_run(c, B, c2v_bytes, lut);
+  const bool squeezed = early && !post && choose_interleave(B) == 64;
+  const double iterations = early ? 0.4 * max_iter + 0.5 : max_iter;
+  const double waits = !early ? 0 : !squeezed ? 6.2 : B <= 64 ? 9.5 : c2v_bytes == sizeof(float) ? 22 : 12;
+  const double whole = l.iteration + (early && post ? 0.4 * l.frames : 0.0) + waits + l.once / iterations;
   int best = 0;
-  double best_t = early && plain_w == 64 ? fixed + 0.5 * FE : whole;
+  double best_t = squeezed ? whole - l.frames * (B > 64 ? 0.7 : 0.55) : early ? whole : 1.1 * whole;
   for (int W : {16, 8, 4, 2, 1}) {
     if (c2v_bytes != sizeof(float) && W < 4) continue;
     const int G = (B + W - 1) / W, rounds = (G + dies - 1) / dies;
     const size_t slot = team_slot(c, W, post, c2v_bytes, nullptr), all = slot * std::min(G, kTeamSlots);
     if (slot >= kMaxSlotBytes || team_control_bytes() + all > ws_bytes || all > kMaxTeamBytes) continue;
-    const double it = (4.5 + (c2v_bytes == 1 ? 20 + 16 * W : 32 + 17.5 * W) * E) * (slot > (8u << 20) ? 1.15 : 1.0);
-    if (rounds * it > whole) continue;
-    const double m = std::min(1.0, std::pow((double)W / B, 0.2));
-    const double t = early && rounds > 1 ? it * (std::max(1.0, m * G / dies) + m) : rounds * it;
+    const Run r = team_run(c, W, c2v_bytes, lut);
+    const double once = (20 + rounds * r.once) / iterations;
+    if (rounds * r.iteration + once > 1.15 * whole) continue;
+    const double m = std::min(1.0, std::pow((double)W / B, 1.0 / 9));
+    const double t = once + r.iteration * (early && rounds > 1 ? std::max(1.0, m * G / dies) + m : rounds);
     if (t < best_t) {
       best = W;
       best_t = t;
