@@ -886,6 +886,9 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
   s.B1 = buf(job.off_B1, job.slot_bytes);
   s.b1_half = (job.slot_bytes - job.off_B1) / 2;
 
+  // the last wave, which has the least to set up and put out, keeps the books
+  // (numbers from 0 in it, beyond every frame elsewhere)
+  const uint32_t clerk = threadIdx.x - (kTeamBlock - 64);
   uint32_t g = sh.group;
   int it = (int)sh.it;
   if (it) forget_cached();
@@ -897,9 +900,9 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
       setup_phase<W>(job, s, g, wave, waves);
       // where every group has been taken by now, the team need not meet again
       // after its outputs
-      if (rank == 0 && threadIdx.x == 0 &&
+      if (rank == 0 && clerk == 0 &&
           (uint32_t)__hip_atomic_load(&ctl->taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (uint32_t)job.G)
-        sh.word = 1;
+        atomicOr(&sh.word, 1u);
       const uint32_t last = barrier(sh);
       if (threadIdx.x == 0) sh.last = last;
       it = 1;
@@ -941,18 +944,18 @@ __global__ __launch_bounds__(kTeamBlock) void k_team(const TeamJob job) {
       if (threadIdx.x < W && ((done >> threadIdx.x) & 1u)) sh.stop[threadIdx.x] |= kSatisfied;
     }
     __syncthreads();  // sh.stop
-    const bool mine = threadIdx.x < min((uint32_t)W, (uint32_t)job.B - g * W);  // a thread per frame
+    const bool mine = clerk < min((uint32_t)W, (uint32_t)job.B - g * W);  // a thread per frame
     if (sh.err) {
-      if (mine) give_up(job, g * W + threadIdx.x);
+      if (mine) give_up(job, g * W + clerk);
       break;
     }
     // (both waited for after the outputs)
     uint32_t next = 0;
     bool set = true;
     if (rank == 0 && threadIdx.x == 0 && !sh.last) next = (uint32_t)take_group(ctl, 0);
-    if (rank == 0 && mine) set = set_outcome(job, g * W + threadIdx.x, sh.stop[threadIdx.x]);
+    if (rank == 0 && mine) set = set_outcome(job, g * W + clerk, sh.stop[clerk]);
     output_phase<W>(job, s, g, wave, waves, sh);
-    if (!set) job.converged[g * W + threadIdx.x] = 0;
+    if (!set) job.converged[g * W + clerk] = 0;
     if (sh.last) break;
     if (rank == 0 && threadIdx.x == 0) sh.word = next;
     g = barrier(sh);
