@@ -239,6 +239,22 @@ def roofline(kernel: str, bytes_total: float, launches: int, total_ms: float, tr
     }
 
 
+def check_launches(kt: dict, main: str, check_bytes: dict, var_bytes: float):
+    """(name, bytes, launches, ms) that price the check updates of a plain decode:
+    the launches of the class `main` where it has its own, else all check
+    launches together (one launch may hold every class, and one decode may
+    change over to that when frames stop), with the variable update where a
+    team decodes in one launch."""
+    if "k_team" not in kt and "k_check_set" not in kt:
+        return (main, check_bytes.get(main, 0.0), *kt.get(main, (0, 0.0)))
+    names = [k for k in kt if k.startswith("k_check") or k == "k_team"]
+    total = sum(check_bytes.values())
+    if "k_team" in kt:
+        names += [k for k in kt if k == "k_variable"]
+        total += var_bytes
+    return "+".join(sorted(names)), total, sum(kt[k][0] for k in names), sum(kt[k][1] for k in names)
+
+
 def timed(fn, steps: int, warmup: int):
     """Runs fn warmup times, then `steps` times between two events with the
     decoder's per-launch timing on; returns (elapsed ms, kernel times, last out)."""
@@ -479,9 +495,8 @@ def run_mix(args, cpu) -> dict:
         roof["materialised_16B_model"] = {
             "bytes_per_step": round(mat),
             "step_frac": round(mat / (g_ms / args.steps * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
-    pl, pms = p_kt.get("k_check<3,1>", (0, 0.0))
-    plain_roof = roofline("k_check<3,1>", check_bytes.get("k_check<3,1>", 0.0) * args.steps, pl, pms,
-                          measured_traffic("k_check<3,1>", wl))
+    pk, pbytes, pl, pms = check_launches(p_kt, "k_check<3,1>", check_bytes, var_bytes)
+    plain_roof = roofline(pk, pbytes * args.steps, pl, pms, measured_traffic(pk, wl))
     return {
         "value": round(b_val, 3),
         "ms_per_step": round(g_ms / args.steps, 3),
@@ -508,7 +523,7 @@ def run_mix(args, cpu) -> dict:
         "measured_copy_GBps": round(copy_gbps, 1),
         "ms_per_step_with_launch_timing": round(b_ms / args.steps, 3),
         "frac_of_measured_copy": {bk: round(roof["achieved"] / copy_gbps, 4),
-                                  "k_check<3,1>": round(plain_roof["achieved"] / copy_gbps, 4)},
+                                  pk: round(plain_roof["achieved"] / copy_gbps, 4)},
         "graph_replay": {"value": round(total_bits / (g_ms * 1e-3) / 1e6, 3),
                          "ms_per_step": round(g_ms / args.steps, 3)},
         "identical_outputs": bool(same),
@@ -561,11 +576,7 @@ def run_single(args, cpu) -> dict:
     dom = max(classes, key=lambda c: c["n_checks"] * (c["n_msg"] + c["n_leaf"]))
     kname = "k_check<%d,%d>" % (dom["n_msg"], dom["n_leaf"])
     wl = "%s N=%d B=%d snr=%g max_iter=%d %s" % (prof, n, B, snr, max_iter, "early-exit" if early else "fixed")
-    kbytes = cls[kname]
-    if kname not in kt:  # one launch for all check classes, or for the whole decode
-        kname = "k_team" if "k_team" in kt else "k_check_set"
-        kbytes = sum(cls.values()) + (var if kname == "k_team" else 0.0)
-    kl, kms = kt.get(kname, (0, 0.0))
+    kname, kbytes, kl, kms = check_launches(kt, kname, cls, var)
     rec = {
         "value": round(value, 3),
         "ms_per_step": round(ms / args.steps, 3),
@@ -696,7 +707,9 @@ def wbp_rooflines(code, frames: int, ktimes: dict) -> dict:
     out = {}
     lw, msw = ktimes.get("k_check_weighted", (0, 0.0))
     if lw:
-        iters = lw / max(1, len(classes))
+        # one launch for all classes of compiled shapes, or one for each: the
+        # iterations are counted by the variable updates
+        iters = ktimes.get("k_variable", (lw, 0.0))[0]
         out["k_check_weighted"] = roofline("k_check_weighted (all classes of one iteration)", fwd * frames * iters,
                                            int(iters), msw, None)
     la, msa = ktimes.get("k_check_adj", (0, 0.0))
