@@ -959,6 +959,7 @@ __device__ __forceinline__ void variable_body(const VarParams &p, int64_t bx, in
       for (int gg = threadIdx.x; gg < p.G; gg += kBlock) {
         const uint64_t a = p.active[gg];  // only this block writes the mask
         uint64_t u = 0;
+#pragma unroll 8
         for (int w = 0; w < W; ++w) u |= (uint64_t)unsat_frame(p.unsat, gg, w) << w;
         const uint64_t done = a & ~u;
         if (done) {
