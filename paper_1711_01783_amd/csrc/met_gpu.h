@@ -589,8 +589,7 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
   // Iteration 1 of the special mode reads rows whose values it drops.  32 frames
   // per row, N = 262144: decode 58.9 to 50.2 us a launch, weighted 69.4 to 61.7;
   // half-used rows of N = 10^6 199 to 181.  (With a wave per check the indices
-  // are scalar and the order does not matter; 8-bit messages with the lookup
-  // table take 2 % more.)
+  // are scalar and the order does not matter.)
   const CT *c_in = reinterpret_cast<const CT *>(MODE == M_SPECIAL && first ? p.c2v : p.c2v_in);
   int32_t vi[IPW][NM > 0 ? NM : 1];
   auto gather = [&](int k, int m) {
@@ -635,6 +634,26 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
     for (int k = 0; k < IPW; ++k)
 #pragma unroll
       for (int m = 0; m < NM; ++m) cv[k][m] = 0.0f;
+  // Waits count loads and stores together and in order, and a step's stores are
+  // conditional, so a wait for the loads of a later step is one for the stores of
+  // earlier steps too.  Updates of 8-bit messages wait once, here, and form their
+  // inputs (the empty statements keep that from being moved down again): (3,1)
+  // checks, N = 10^6, 64 frames, with tests and decisions 285 to 264 us with the
+  // table and 285 to 277 without, without them 249 to 238 and 259 to 255.  Float
+  // messages, where a step's arithmetic hides the next step's loads, get slower
+  // by it (280 to 304 us); 2-byte ones take the same either way.
+  constexpr bool ahead = sizeof(CT) == 1;
+  if constexpr (ahead)
+#pragma unroll
+    for (int k = 0; k < IPW; ++k) {
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        cv[k][m] = clamp_llr(pv[k][m] - cv[k][m]);
+        asm volatile("" : "+v"(cv[k][m]));
+      }
+#pragma unroll
+      for (int l = 0; l < NL; ++l) asm volatile("" : "+v"(lf[k][l]));
+    }
   // The update is bound by its arithmetic (6 phis of 19 instructions for a
   // (3,1) check), so the rest is kept short: signs stay in the top bits of the
   // inputs, and with a wave per check the parities of a test are words of lane
@@ -650,7 +669,7 @@ __device__ __forceinline__ void check_fixed_body(const CheckParams &p, const Cla
     uint32_t sgn[D], tot = frame_sign<W>(sw[k], w);  // top bits
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
-      const float x = clamp_llr(pv[k][m] - cv[k][m]);
+      const float x = ahead ? cv[k][m] : clamp_llr(pv[k][m] - cv[k][m]);
       if constexpr (lut)
         A[m] = tab_a[lut_index(fabsf(x))];
       else

@@ -1082,7 +1082,7 @@ Run launch_run(const met_code *c, int B, size_t c2v_bytes, bool lut) {
   const int generic = G > 0, compiled = (int)c->classes.size() - generic;
   const int launches = 1 + generic + (W >= 16 && c2v_bytes > 1 ? std::min(compiled, 1) : compiled);
   const double each = c2v_bytes > 1 ? 3.2 : lut ? 5.2 : 6.2;
-  double t = each * launches, f = ((c2v_bytes == 4 ? 2.2 : c2v_bytes == 2 ? 1.45 : 1.7) * E + (c2v_bytes == 4 ? 5 : 4) * V) * F;
+  double t = each * launches, f = ((c2v_bytes == 4 ? 2.2 : c2v_bytes == 2 ? 1.45 : lut ? 1.55 : 1.7) * E + (c2v_bytes == 4 ? 5 : 4) * V) * F;
   // long lists: one frame per item reads them and their rows scattered
   const double longer = std::max(0, c->max_vn_deg - 24);
   t += W >= 16 ? 0.065 * longer : 4.5 + 0.17 * longer * std::min(1.0, 1e-5 * c->N);
@@ -1108,8 +1108,8 @@ Run launch_run(const met_code *c, int B, size_t c2v_bytes, bool lut) {
 // Infinity Cache (64 frames of N = 10^6 in groups of 8: 87 ms).  Fixed-iteration
 // launches take 10 % more than their estimate where teams come into question.
 // Of 3040 decodes (the codes above, 1 to 400 frames, good and bad channels, all
-// storage types, early exit and fixed) 49 are more than 5 % slower than the launches
-// would be, and in the mean they are 3.4 % off the best of launches and five widths;
+// storage types, early exit and fixed) 54 are more than 5 % slower than the launches
+// would be, and in the mean they are 3.6 % off the best of launches and five widths;
 // estimates by edges alone: 317, and 4.9 %.
 int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, bool lut, int max_iter, bool early,
                size_t ws_bytes, int *width) {
