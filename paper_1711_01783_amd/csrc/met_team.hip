@@ -1097,20 +1097,20 @@ Run launch_run(const met_code *c, int B, size_t c2v_bytes, bool lut) {
 
 // The rule compares the two.  With early exit, taken to last two fifths of the budget,
 // the launches have the host's reads to wait for and frames to move (us an
-// iteration: 7.2 up to 32 frames, 25 where one group is squeezed, 16 where there
-// are several), save by that 90 or 70 % of what goes with the frames, and run until
+// iteration: 7.2 up to 32 frames, 12 where one group is squeezed, 16 where there
+// are several), save by that 80 or 70 % of what goes with the frames, and run until
 // the slowest of all frames stops; with posteriors they write them in every
 // iteration.  A team runs until the slowest of each of its groups: in units of the
 // former a group of W out of B frames takes about m = (W / B)^0.175, and the eight
 // teams end after max(1, m groups / 8) + 0.74 m (1 where each has one group).  (How
-// many frames never stop is not known beforehand: rate 0.02, N = 65536, 48 frames of a
-// good channel 7.0 ms by launches and 5.9 by teams, of a bad one 7.2 and 11.0.)  A team
+// many frames never stop is not known beforehand: rate 0.02, N = 40000, 48 frames of a
+// good channel 4.4 ms by launches and 3.6 by teams, of a bad one 4.5 and 6.8.)  A team
 // that would be slower by more than 15 % if every frame ran its whole budget is not
 // taken, nor one whose states leave the Infinity Cache (64 frames of N = 10^6 in
 // groups of 8: 87 ms).  Fixed-iteration launches take 10 % more than their estimate
 // where teams come into question.  Of 3400 decodes (the codes above, 1 to 400 frames,
-// good and bad channels, all storage types, early exit and fixed) 95 are more than
-// 5 % slower than the launches would be, and in the mean they are 3.2 % off the best
+// good and bad channels, all storage types, early exit and fixed) 84 are more than
+// 5 % slower than the launches would be, and in the mean they are 3.3 % off the best
 // of launches and five widths; estimates by edges alone: 255, and 4.7 %.
 int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, bool lut, int max_iter, bool early,
                size_t ws_bytes, int *width) {
@@ -1120,11 +1120,11 @@ int team_width(const met_code *c, int B, bool post, size_t c2v_bytes, bool lut, 
   const Run l = launch_run(c, B, c2v_bytes, lut);
   const bool squeezed = early && !post && choose_interleave(B) == 64;
   const double iterations = early ? 0.4 * max_iter + 0.5 : max_iter;
-  const double waits = !early ? 0 : !squeezed ? 7.2 : B <= 64 ? 25 : 16;
+  const double waits = !early ? 0 : !squeezed ? 7.2 : B <= 64 ? 12 : 16;
   const double whole =
       (l.iteration + (early && post ? 0.4 * l.frames : 0.0) + waits + l.once / iterations) * (early ? 1.0 : 1.1);
   int best = 0;
-  double best_t = squeezed ? whole - l.frames * (B > 64 ? 0.7 : 0.9) : whole;
+  double best_t = squeezed ? whole - l.frames * (B > 64 ? 0.7 : 0.8) : whole;
   for (int W : {16, 8, 4, 2, 1}) {
     if (c2v_bytes != sizeof(float) && W < 4) continue;
     const int G = (B + W - 1) / W, rounds = (G + dies - 1) / dies;
